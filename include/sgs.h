@@ -107,11 +107,14 @@ typedef struct {
  *   alpha_max 0.99   alpha is clamped to alpha_max
  *   T_min 1e-4       stop before a Gaussian that would take T below T_min
  *   tile             tile side in pixels: 8, 16 or 32
- *   lds_batch        Gaussians staged in LDS per batch (64, 128 or 256)
+ *   lds_batch        Gaussians staged in LDS per batch (64, 128 or 256), at
+ *                    most: the library stages fewer where that many would
+ *                    leave too few workgroups per CU
  *   persistent       0: one workgroup per tile; 1: persistent workgroups
  *                    that pull (view, tile) items from a queue
  *   lds_batch_bwd    Gaussians staged per batch by the render backward
- *                    (64, 128 or 256; 0 = the same as lds_batch)
+ *                    (64, 128 or 256; 0 = chosen by the library from
+ *                    the tile, n_feat and the gradients, at most lds_batch)
  */
 typedef struct {
     float z_near, blur, guard, alpha_min, alpha_max, T_min;

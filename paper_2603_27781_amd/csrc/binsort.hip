@@ -1164,7 +1164,7 @@ hipError_t launch_binsort(const uint32_t* rect, const int32_t* touched, int n,
                            gu.flag);
         if (total_tiles > 0) {
             const int2* rg = reinterpret_cast<const int2*>(ranges);
-            const int run = tile_run(tile);
+            const int run = tile_run_log2(tile, total_tiles);
             uint32_t* long_list = reinterpret_cast<uint32_t*>(w + L.long_list);
             uint32_t* long_count = tickets + kMaxPasses;
             hipLaunchKernelGGL(k_tile_sort_short, dim3(tile_grid(total_tiles, run)), dim3(TSS_THREADS), 0, s, rg,

@@ -619,7 +619,8 @@ __global__ void __launch_bounds__(TS* TS) __attribute__((amdgpu_waves_per_eu(bwd
                                                        const float* __restrict__ T_final,
                                                        const int32_t* __restrict__ last,
                                                        const float* __restrict__ grad_out,
-                                                       float* __restrict__ records, int32_t* queue, int persistent) {
+                                                       float* __restrict__ records, int32_t* queue, int persistent,
+                                                       int run) {
     constexpr int NREAL = PARAMS ? 10 + F : 6;
     __shared__ float4 s_g0[B];
     __shared__ float4 s_g1[B];
@@ -628,7 +629,7 @@ __global__ void __launch_bounds__(TS* TS) __attribute__((amdgpu_waves_per_eu(bwd
     __shared__ int s_tile;
     __shared__ int s_max;
     if (!persistent) {
-        const int t = tile_of_block<TS>(blockIdx.x, total_tiles);
+        const int t = tile_of_block(blockIdx.x, total_tiles, run);
         if (t < 0) return;
         bwd_tile<TS, F, B, PARAMS>(t, rec, app, n, inst, inst_gid, ranges, views, n_views, P, c, T_final,
                                    last, grad_out, records, s_g0, s_g1, s_app, &s_max, s_acc);
@@ -817,7 +818,8 @@ hipError_t launch_bwd_t(const float* rec, const float* app, int n, const int32_t
                         const RasterConst& c, int persistent, const float* T_final, const int32_t* last,
                         const float* grad_out, float* records, int32_t* queue, hipStream_t s) {
     auto kern = k_render_bwd<TS, F, B, PARAMS>;
-    unsigned grid = total_tiles > 0 ? tile_grid<TS>(total_tiles) : 0u;
+    const int run = tile_run_log2(TS, total_tiles);
+    unsigned grid = total_tiles > 0 ? tile_grid(total_tiles, run) : 0u;
     if (persistent) {
         int dev = 0, cus = 0, per_cu = 0;
         (void)hipGetDevice(&dev);
@@ -832,7 +834,7 @@ hipError_t launch_bwd_t(const float* rec, const float* app, int n, const int32_t
     if (grid == 0) return hipGetLastError();
     hipLaunchKernelGGL(kern, dim3(grid), dim3(TS * TS), 0, s, reinterpret_cast<const float4*>(rec),
                        reinterpret_cast<const float4*>(app), n, inst, inst_gid, reinterpret_cast<const int2*>(ranges),
-                       views, n_views, total_tiles, P, c, T_final, last, grad_out, records, queue, persistent);
+                       views, n_views, total_tiles, P, c, T_final, last, grad_out, records, queue, persistent, run);
     return hipGetLastError();
 }
 

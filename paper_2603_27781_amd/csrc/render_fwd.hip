@@ -270,7 +270,7 @@ __global__ void __launch_bounds__(TS* TS)
                                                        const gs_view* __restrict__ views, int n_views,
                                                        int total_tiles, int64_t P, RasterConst c,
                                                        float* __restrict__ out, float* __restrict__ T_final,
-                                                       int32_t* __restrict__ last, int32_t* queue, int persistent,
+                                                       int32_t* __restrict__ last, int32_t* queue, int persistent, int run,
                                                        FusedLoss L, const float* __restrict__ Wt) {
     constexpr int AV = AppRec<F>::vec;
     __shared__ float4 s_g0[B];
@@ -279,7 +279,7 @@ __global__ void __launch_bounds__(TS* TS)
     __shared__ double s_red[LK > 0 ? 3 * (TS * TS / kWave) : 1];
     __shared__ int s_tile;
     if (!persistent) {
-        const int t = tile_of_block<TS>(blockIdx.x, total_tiles);
+        const int t = tile_of_block(blockIdx.x, total_tiles, run);
         if (t < 0) return;
         fwd_tile<TS, F, B, LK>(t, rec, app, n, inst, inst_gid, ranges, views, n_views, P, c, out, T_final, last, s_g0,
                                s_g1, s_app, total_tiles, L, Wt, s_red);
@@ -306,7 +306,8 @@ hipError_t launch_fwd_t(const float* rec, const float* app, int n, const int32_t
                         const RasterConst& c, int persistent, float* out, float* T_final, int32_t* last,
                         int32_t* queue, const FusedLoss& L, hipStream_t s) {
     auto kern = k_render_fwd<TS, F, B, LK>;
-    unsigned grid = total_tiles > 0 ? tile_grid<TS>(total_tiles) : 0u;
+    const int run = tile_run_log2(TS, total_tiles);
+    unsigned grid = total_tiles > 0 ? tile_grid(total_tiles, run) : 0u;
     if (persistent) {
         int dev = 0, cus = 0, per_cu = 0;
         (void)hipGetDevice(&dev);
@@ -321,7 +322,7 @@ hipError_t launch_fwd_t(const float* rec, const float* app, int n, const int32_t
     if (grid == 0) return hipGetLastError();
     hipLaunchKernelGGL(kern, dim3(grid), dim3(TS * TS), 0, s, reinterpret_cast<const float4*>(rec),
                        reinterpret_cast<const float4*>(app), n, inst, inst_gid, reinterpret_cast<const int2*>(ranges),
-                       views, n_views, total_tiles, P, c, out, T_final, last, queue, persistent, L, L.Wt);
+                       views, n_views, total_tiles, P, c, out, T_final, last, queue, persistent, run, L, L.Wt);
     return hipGetLastError();
 }
 
@@ -330,17 +331,20 @@ hipError_t launch_fwd_b(int B, const float* rec, const float* app, int n, const 
                         const int32_t* ranges, const gs_view* views, int n_views, int total_tiles, int64_t P,
                         const RasterConst& c, int persistent, float* out, float* T_final, int32_t* last,
                         int32_t* queue, const FusedLoss& L, hipStream_t s) {
-    switch (B) {
-        case 64:
-            return launch_fwd_t<TS, F, 64, LK>(rec, app, n, inst, inst_gid, ranges, views, n_views, total_tiles, P, c,
-                                               persistent, out, T_final, last, queue, L, s);
-        case 128:
-            return launch_fwd_t<TS, F, 128, LK>(rec, app, n, inst, inst_gid, ranges, views, n_views, total_tiles, P, c,
-                                                persistent, out, T_final, last, queue, L, s);
-        default:
+    // the batches fwd_batch gives for this tile and feature count
+    if constexpr (TS != 8 && !(TS == 16 && F > 16)) {
+        if (B == 256)
             return launch_fwd_t<TS, F, 256, LK>(rec, app, n, inst, inst_gid, ranges, views, n_views, total_tiles, P, c,
                                                 persistent, out, T_final, last, queue, L, s);
     }
+    if constexpr (TS != 8) {
+        if (B == 128)
+            return launch_fwd_t<TS, F, 128, LK>(rec, app, n, inst, inst_gid, ranges, views, n_views, total_tiles, P, c,
+                                                persistent, out, T_final, last, queue, L, s);
+    }
+    if (B != 64) return hipErrorInvalidValue;
+    return launch_fwd_t<TS, F, 64, LK>(rec, app, n, inst, inst_gid, ranges, views, n_views, total_tiles, P, c,
+                                       persistent, out, T_final, last, queue, L, s);
 }
 
 template <int F, int LK>

@@ -275,7 +275,8 @@ int gs_render_fwd(const float* rec, const float* app, int32_t n, int32_t n_feat,
     if (cfg->persistent && !queue) return GS_EINVAL;
     if (!aligned16(rec) || !aligned16(app)) return GS_EINVAL;
     return hip_status(launch_render_fwd(rec, app, n, n_feat, inst, inst_gid, tile_ranges, views_dev, n_views,
-                                        total_tiles, P, make_const(cfg), cfg->lds_batch, cfg->persistent, out,
+                                        total_tiles, P, make_const(cfg), fwd_batch(cfg->tile, n_feat, cfg->lds_batch),
+                                        cfg->persistent, out,
                                         T_final, last, queue, reinterpret_cast<hipStream_t>(stream)));
 }
 
@@ -314,7 +315,8 @@ int gs_render_fwd_loss(const float* rec, const float* app, int32_t n, int32_t n_
     if (ws_bytes < fused_loss_workspace_bytes(total_tiles)) return GS_ECAPACITY;
     if ((reinterpret_cast<uintptr_t>(ws) & 15u) != 0) return GS_EINVAL;
     return hip_status(launch_render_fwd_loss(rec, app, n, n_feat, inst, inst_gid, tile_ranges, views_dev, n_views,
-                                             total_tiles, P, make_const(cfg), cfg->lds_batch, cfg->persistent, out,
+                                             total_tiles, P, make_const(cfg), fwd_batch(cfg->tile, n_feat, cfg->lds_batch),
+                                             cfg->persistent, out,
                                              T_final, last, queue, rgb_target, depth_target, labels, decoder,
                                              n_feat > 0 ? n_classes : 0, weights, grad_out, loss, ws,
                                              reinterpret_cast<hipStream_t>(stream)));
@@ -494,7 +496,7 @@ int gs_render_bwd_records(const gs_gaussians* g, const float* rec, const float* 
     const size_t rec_bytes = (size_t)(capacity > 0 ? capacity : 1) * bwd_record_floats(g->n_feat, params) * sizeof(float);
     if (ws_bytes < rec_bytes) return GS_ECAPACITY;
     if (!aligned16(rec) || !aligned16(app) || !aligned16(ws)) return GS_EINVAL;
-    const int batch = cfg->lds_batch_bwd ? cfg->lds_batch_bwd : cfg->lds_batch;
+    const int batch = bwd_batch(cfg->tile, g->n_feat, params, cfg->lds_batch, cfg->lds_batch_bwd);
     return hip_status(launch_render_bwd(rec, app, g->n, g->n_feat, inst, inst_gid, tile_ranges, views_dev, n_views,
                                         total_tiles, P, make_const(cfg), batch, cfg->persistent, T_final, last,
                                         grad_out, params, static_cast<float*>(ws), queue,

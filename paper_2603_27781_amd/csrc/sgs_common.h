@@ -43,31 +43,33 @@ __host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; 
 
 // Tile order of the one-workgroup-per-tile launches.  Workgroup b runs on
 // XCD b mod 8, and each XCD has its own L2; neighbouring tiles share most of
-// their Gaussians, so the tiles go to the XCDs in runs of about 32 k pixels
-// of consecutive tiles (the runs dealt round-robin), and the tiles an XCD
-// has in flight are neighbours whose shared Gaussian records come from its
-// own L2 instead of each being fetched again by another XCD.
+// their Gaussians, so the tiles go to the XCDs in runs of consecutive tiles
+// (the runs dealt round-robin), and the tiles an XCD has in flight are
+// neighbours whose shared Gaussian records come from its own L2 instead of
+// each being fetched again by another XCD.
 constexpr int kXcds = 8;
-// Run length, in tiles, for tile side ts.
-__host__ __device__ constexpr int tile_run(int ts) { return 32768 / (ts * ts) > 8 ? 32768 / (ts * ts) : 8; }
-inline unsigned tile_grid(int total_tiles, int run) {
-    const int runs = (total_tiles + run - 1) / run;
-    return (unsigned)((runs + kXcds - 1) / kXcds * kXcds * run);
+// log2 of the run length in tiles: about 32 k pixels, less for an image of
+// under 64 such runs, so that every XCD gets eight runs and much the same
+// share of it.  (With runs of 128 tiles whatever the image, a 333x251 one
+// (336 tiles) used three XCDs and at 640x480 two XCDs had twice the tiles of
+// the others: backward at F = 16, 30 k Gaussians 107 -> 57 us, 200 k
+// Gaussians at 640x480 243 -> 201 us, forward 40 -> 26 and 87 -> 81 us.  One
+// round of longer runs: 69 and 229 us.)  A power of two, so that a workgroup
+// finds its tile with shifts.
+inline int tile_run_log2(int ts, int total_tiles) {
+    int run = 2;
+    while ((1 << run) * ts * ts < 32768 && (16 * kXcds << run) <= total_tiles) ++run;
+    return run;
+}
+inline unsigned tile_grid(int total_tiles, int run_log2) {
+    const int runs = (total_tiles + (1 << run_log2) - 1) >> run_log2;
+    return (unsigned)((runs + kXcds - 1) / kXcds * kXcds) << run_log2;
 }
 // The tile of workgroup b of a tile_grid launch, or -1 (no tile: exit).
-__device__ __forceinline__ int tile_of_block(int b, int total_tiles, int run) {
+__device__ __forceinline__ int tile_of_block(int b, int total_tiles, int run_log2) {
     const int x = b & (kXcds - 1), r = b / kXcds;
-    const int round = r / run;
-    const int t = (round * kXcds + x) * run + (r - round * run);
+    const int t = (((r >> run_log2) * kXcds + x) << run_log2) + (r & ((1 << run_log2) - 1));
     return t < total_tiles ? t : -1;
-}
-template <int TS>
-inline unsigned tile_grid(int total_tiles) {
-    return tile_grid(total_tiles, tile_run(TS));
-}
-template <int TS>
-__device__ __forceinline__ int tile_of_block(int b, int total_tiles) {
-    return tile_of_block(b, total_tiles, tile_run(TS));
 }
 
 // Index of the view owning global tile t (views sorted by tile_offset).
@@ -165,6 +167,29 @@ hipError_t launch_binsort(const uint32_t* rect, const int32_t* touched, int n,
                           const gs_view* views_dev, int n_views, int total_tiles, int tile, void* ws,
                           int64_t capacity, uint32_t* tile_keys, int32_t* inst, int32_t* inst_gid,
                           int32_t* pair_first, int32_t* ranges, int64_t* counts, hipStream_t s);
+
+// Gaussians staged per LDS batch: the caller's lds_batch at most (and its
+// lds_batch_bwd as it is), fewer where the staged batch would leave too few
+// workgroups per CU.  Forward: one wavefront per workgroup at tile 8 (78 us
+// with 64, 108 with 128; 1200x680, 1M Gaussians, F = 16), 144-byte records
+// at F = 32 (772 us with 128, 801 with 256; eight such views).
+inline int fwd_batch(int tile, int n_feat, int lds_batch) {
+    const int most = tile == 8 ? 64 : (tile == 16 && n_feat > 16 ? 128 : 256);
+    return lds_batch < most ? lds_batch : most;
+}
+// Backward, which also holds an accumulator of 10 + F (6 for the pose alone)
+// floats per staged Gaussian: at tile 16, 128 from 16 feature channels on
+// with parameter gradients (1249 against 1827 us at eight views and F = 16,
+// 2106 against 4291 us at F = 32), at 16 alone without (799 against 857 us;
+// at F = 32 256 is faster, 1205 against 1282 us, its registers being the
+// limit); at tile 8 64 (255 against 387 us, one view, F = 16); at tile 32
+// the four times larger workgroups fit as they are (323 us with 256, 410
+// with 128).
+inline int bwd_batch(int tile, int n_feat, bool params, int lds_batch, int lds_batch_bwd) {
+    if (lds_batch_bwd != 0) return lds_batch_bwd;
+    const int most = tile == 8 ? 64 : (tile == 16 && (params ? n_feat >= 16 : n_feat == 16) ? 128 : 256);
+    return lds_batch < most ? lds_batch : most;
+}
 
 hipError_t launch_render_fwd(const float* rec, const float* app, int n, int n_feat, const int32_t* inst,
                              const int32_t* inst_gid,

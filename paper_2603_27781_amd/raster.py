@@ -33,7 +33,7 @@ class Config:
     tile: int = 16
     lds_batch: int = 256
     persistent: int = 0
-    lds_batch_bwd: int = 0   # 0: same as lds_batch
+    lds_batch_bwd: int = 0   # 0: chosen by the library, at most lds_batch
 
     def c(self) -> GsConfig:
         return GsConfig(self.z_near, self.blur, self.guard, self.alpha_min, self.alpha_max, self.T_min, self.tile,
