@@ -184,8 +184,8 @@ int gs_project(const gs_gaussians* g, const gs_view* views, const gs_view* views
  * rasterization of Gaussians sorted in depth order).  Every visible
  * (view, Gaussian) pair emits one instance per tile of its rectangle; the
  * instances are sorted by (global tile id, binary32 depth, Gaussian index):
- * a stable device radix sort of the instances by tile, then each tile's
- * list by depth (its Gaussian-index order kept among equal depths).
+ * grouped by tile, then each tile's list by (depth, emission index), which
+ * ascends with the Gaussian index within a tile.
  * An instance is identified by its emission index e (pairs in (view, index)
  * order, each pair's tiles row by row), so the instances of one pair occupy the
  * contiguous range [pair_first[pair], pair_first[pair] + tiles_touched[pair]).
@@ -201,12 +201,13 @@ int gs_project(const gs_gaussians* g, const gs_view* views, const gs_view* views
  *                           (the lists are then truncated: read counts after
  *                           the stream completes and call again with
  *                           capacity >= counts[0]),
- *                           [3] 1 if a wait of the device sort's single-pass
- *                           scan gave up (a block's predecessor never
- *                           published within the spin limit): the later
- *                           binning kernels then stand down, every tile list
- *                           is left empty and the call's results must be
- *                           discarded (call again),
+ *                           [3] 1 if a wait of the binning gave up (a block's
+ *                           predecessor never published within the spin
+ *                           limit): the later binning kernels then stand
+ *                           down, every tile list (or, where the wait was
+ *                           the last kernel's, the list it was for) is left
+ *                           empty and the call's results must be discarded
+ *                           (call again),
  *                           [4] sticky: set whenever [2] or [3] is set, by
  *                           every call, and cleared only by the caller (write
  *                           0 to it), so that one check after many calls (a

@@ -1,30 +1,39 @@
 // Tile binning and depth sort (GS^3LAM Sec. 3.2.1: the tile-based rasterizer
 // of the cited 3DGS work sorts Gaussians in depth order per tile).
 //
-// Two stable sorts replace one wide-key sort:
-//   1. the visible (view, Gaussian) pairs, compacted in (view, index) order,
-//      each emit one instance per tile of their rectangle, keyed by global
-//      tile id, and the instances are radix-sorted by tile id (ceil(log2
-//      tiles) bits; stable, so each tile's list stays in index order);
-//   2. each tile's list is sorted by the binary32 bits of its pairs' camera
-//      depth, one workgroup per tile (stable counting passes in LDS).
-// So the final order is (view, tile, depth bits, Gaussian index).
+// Every visible (view, Gaussian) pair emits one instance per tile of its
+// rectangle; the instances are then grouped by tile and each tile's list is
+// sorted by (binary32 depth bits, emission index).  Emission runs in (view,
+// index) order and a Gaussian is in a tile's list once, so that key is
+// distinct and orders like (depth, Gaussian index): grouping by tile needs no
+// stable sort, and the final order (view, tile, depth, index) does not
+// depend on the order in which the groups were filled.  Six launches:
+//   1. k_bin_reset, or k_chunk_sums where there are many chunks of pairs: the
+//      call's state, and the second the instances of every chunk;
+//   2. k_emit: one workgroup per chunk of pairs of one view: instance offsets
+//      and emission; each instance counts itself into its tile in LDS, what
+//      the counter held is its place among the chunk's, and the chunk's
+//      counts become a row of a (chunk, tile) table;
+//   3. k_tile_scan: the table's columns to [start, end) of every tile and the
+//      first place of every (chunk, tile);
+//   4. k_place: each instance's sort key to its place;
+//   5. k_tile_sort_short, 6. k_tile_sort_long: the lists in order.
+// (An LSD radix sort by tile id before them, with the visible pairs compacted
+// and their offsets scanned first, took 19 launches, most of them of a few
+// microseconds.  Alone: one 1200x680 view of 1M Gaussians 87 -> 45 us, eight
+// such views 232 -> 147, 640x480 / 200k 134 -> 80, 320x240 / 60k 62 -> 28,
+// 16 mixed views of 2M 740 -> 502.  The kernels move 60 bytes per instance and
+// 20 per pair, about 40 us of the eight views' 147 at the rate of a copy; the
+// rest is latency and, in the sort, vector work.)
 //
 // Every count that the host does not know (visible pairs, instances) stays on
 // the device; grids are sized for the capacity and blocks beyond the count
 // exit early, so the whole pipeline is graph-capturable.
 //
-// Prefix sums take one launch where the input is short and two or three
-// where it is long.  The radix digit offsets (256 per block) are a single-pass scan with
-// decoupled look-back: a block takes a ticket, scans its tile, publishes its
-// total and reads the totals of the tiles before it until it meets a
-// published prefix; it only ever waits for blocks that took an earlier
-// ticket, which are already running, so every wait ends (the spin is bounded
-// all the same).  The long scan of the instance offsets (thousands of
-// tiles, where such a chain of waits costs more than it saves) writes tile
-// totals first, and each tile then sums the totals before it itself; the
-// compaction counts runs, scans the run counts in one block and ranks
-// inside a run with ballots.
+// Blocks that wait (the look-back of k_emit and k_tile_scan, the merge of
+// k_tile_sort_long) take a ticket first and wait only for blocks with earlier
+// tickets, which are already running and wait for none after them, so every
+// wait ends (the spin is bounded all the same).
 #include <cstdlib>
 
 #include "sgs_common.h"
@@ -59,13 +68,6 @@ __device__ __forceinline__ uint32_t lane_xor_u32(uint32_t v, int lane) {
     }
 }
 
-// Value of v in lane l (l wavefront-uniform), read into scalar registers.
-__device__ __forceinline__ int64_t read_lane_i64(int64_t v, int l) {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), l);
-    return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-
 // Sum of x over the 64 lanes, in every lane (integer: the order does not
 // matter), with one LDS crossbar step (J = 4) instead of six shuffles.
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x, int lane) {
@@ -78,49 +80,9 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x, int lane) {
     return x;
 }
 
-// Radix passes run on a fixed grid of at most RS_MAXBLK blocks; the device
-// side count is split into contiguous chunks (multiples of RS_THREADS), one
-// per block, so the digit histograms stay small whatever the capacity and
-// only blocks with elements do work.
-constexpr int RS_THREADS = 256;
-constexpr int RS_MAXBLK = 1024;
-constexpr int RS_WAVES = RS_THREADS / kWave;
-constexpr int RS_ITEMS = 4;                        // keys per thread per scatter tile
-constexpr int RS_TILE = RS_THREADS * RS_ITEMS;     // chunks are whole tiles
-
-int rs_blocks(int64_t n_max) {
-    const int64_t b = (n_max + RS_THREADS - 1) / RS_THREADS;
-    return (int)(b < RS_MAXBLK ? (b > 0 ? b : 1) : RS_MAXBLK);
-}
-
-__device__ __forceinline__ void rs_chunk(int64_t count, int nblk, int64_t& lo, int64_t& hi) {
-    const int64_t per = ((count + nblk - 1) / nblk + RS_TILE - 1) / RS_TILE * RS_TILE;
-    lo = (int64_t)blockIdx.x * per;
-    lo = lo < count ? lo : count;
-    hi = lo + per < count ? lo + per : count;
-}
-
-__device__ __forceinline__ int64_t eff_count(const int64_t* count_dev, int64_t n_max) {
-    if (count_dev == nullptr) return n_max;
-    const int64_t c = *count_dev;
-    return c < n_max ? c : n_max;
-}
-
-// ----------------------------------------------------------------------------
-// loaders for the generic exclusive scan
-// ----------------------------------------------------------------------------
-struct LoadU32 {
-    const uint32_t* p;
-    __device__ uint32_t operator()(int64_t i) const { return p[i]; }
-};
-
-// Sum of a[0 .. m) by the whole block (all threads get it): used by a block
-// to find its offset from the totals of the tiles before it, so that the
-// large scans need no top-level scan launch and no waiting between blocks.
-// The totals are few (one per tile) and were just written, so they are
-// read from L2.
+// Sum of a[0 .. m) by the whole block (all threads get it).
 template <int NT>
-__device__ __forceinline__ uint32_t block_sum_before(const uint32_t* __restrict__ a, int m, uint32_t* s_tmp) {
+__device__ __forceinline__ uint32_t block_sum(const uint32_t* __restrict__ a, int m, uint32_t* s_tmp) {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     uint32_t x = 0;
     for (int i = tid; i < m; i += NT) x += a[i];
@@ -134,684 +96,557 @@ __device__ __forceinline__ uint32_t block_sum_before(const uint32_t* __restrict_
     return t;
 }
 
-constexpr int TOP_THREADS = 1024;
-
-// Single-block exclusive scan of the block sums, total to *total (int64):
-// each of the TOP_THREADS threads takes a contiguous run of sums.
-__global__ void __launch_bounds__(TOP_THREADS) k_scan_top(uint32_t* block_sums, int nblocks, int64_t* total) {
-    __shared__ uint32_t s_tmp[TOP_THREADS / kWave];
-    const int per = (nblocks + TOP_THREADS - 1) / TOP_THREADS;
-    const int b0 = min(nblocks, (int)threadIdx.x * per), b1 = min(nblocks, b0 + per);
-    uint32_t sum = 0;
-    for (int b = b0; b < b1; ++b) sum += block_sums[b];
-    uint32_t tot;
-    uint32_t run = block_exclusive<TOP_THREADS>(sum, s_tmp, &tot);
-    for (int b = b0; b < b1; ++b) {
-        const uint32_t v = block_sums[b];
-        block_sums[b] = run;
-        run += v;
-    }
-    if (threadIdx.x == 0 && total != nullptr) *total = (int64_t)tot;
-}
-
-// Single-pass exclusive scan with decoupled look-back.  Status word of a
-// tile: bits 62-63 the state (0 not ready, 1 tile total, 2 inclusive prefix),
-// bits 0-31 the value.
-constexpr int LB_THREADS = 256;
-constexpr int LB_ITEMS = 8;
-constexpr int LB_TILE = LB_THREADS * LB_ITEMS;
+// ----------------------------------------------------------------------------
+// decoupled look-back
+// ----------------------------------------------------------------------------
+// Status word of a block: bits 62-63 the state (0 not ready, 1 the block's
+// totals, 2 inclusive prefixes), bits 32-61 one count (visible pairs), bits
+// 0-31 the other (instances).
 constexpr uint64_t LB_AGG = 1ull << 62;
 constexpr uint64_t LB_INC = 2ull << 62;
+constexpr uint64_t LB_VALUE = LB_AGG - 1;
 constexpr int LB_SPIN_MAX = 1 << 20;
 
-int64_t lb_tiles(int64_t n) { return (n + LB_TILE - 1) / LB_TILE; }
-
-__device__ __forceinline__ void lb_publish(uint64_t* st, uint64_t state, uint32_t value) {
-    __hip_atomic_store(st, state | value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ void lb_publish(uint64_t* st, uint64_t word) {
+    __hip_atomic_store(st, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __device__ __forceinline__ uint64_t lb_read(const uint64_t* st) {
     return __hip_atomic_load(st, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Where a look-back that gave up is recorded: the call's flag and the
-// caller's sticky flag (the low words of counts[3] and counts[4]), and how
-// many reads a wait may take.
+// Where a wait that gave up is recorded: the call's flag and the caller's
+// sticky flag (the low words of counts[3] and counts[4]), and how many reads
+// a wait may take.
 struct LbGiveUp {
     uint32_t* flag;
     uint32_t* sticky;
     int spin_limit;
 };
 
-// Exclusive prefix of tile `tile` (> 0) from the status words of the tiles
-// before it; called by one whole wavefront, which reads 64 of them at a
-// time, newest first.  Positions before tile 0 count as an inclusive 0.
+__device__ __forceinline__ void give_up(LbGiveUp gu) {
+    atomicOr(gu.flag, 1u);
+    atomicOr(gu.sticky, 1u);
+}
+
+// Exclusive prefix (both counts) of block `b` (> 0) from the status words of
+// the blocks before it; called by one whole wavefront, which reads 64 of them
+// at a time, newest first.  Positions before block 0 count as an inclusive 0.
 // A predecessor that has not published after gu.spin_limit further reads is
 // counted as 0 -- a short prefix -- and the give-up is recorded, so that the
 // binning's later kernels stand down and the caller sees it.
-__device__ uint32_t lb_lookback(const uint64_t* status, int tile, LbGiveUp gu) {
+__device__ uint64_t lb_lookback(const uint64_t* status, int b, LbGiveUp gu) {
     const int lane = threadIdx.x & (kWave - 1);
-    uint32_t prefix = 0;
-    for (int j = tile - 1;; j -= kWave) {
+    uint64_t prefix = 0;
+    for (int j = b - 1;; j -= kWave) {
         const int k = j - lane;
         uint64_t s = k >= 0 ? lb_read(status + k) : LB_INC;
         for (int spin = 0; __any((s >> 62) == 0) && spin < gu.spin_limit; ++spin)
             if ((s >> 62) == 0) s = lb_read(status + k);
-        if (__any((s >> 62) == 0) && lane == 0) {
-            atomicOr(gu.flag, 1u);
-            atomicOr(gu.sticky, 1u);
-        }
+        if (__any((s >> 62) == 0) && lane == 0) give_up(gu);
         const uint64_t inc = __ballot((s >> 62) == 2);
-        uint32_t v = (uint32_t)s;
+        uint64_t v = s & LB_VALUE;
         if (inc != 0 && lane > __builtin_ctzll(inc)) v = 0;  // stop at the nearest inclusive prefix
-        v = wave_sum_u32(v, lane);
-        prefix += v;
+        prefix += ((uint64_t)wave_sum_u32((uint32_t)(v >> 32), lane) << 32) + wave_sum_u32((uint32_t)v, lane);
         if (inc != 0) return prefix;
     }
 }
 
-// Ticket, tile scan and look-back shared by the single-pass kernels: returns
-// the exclusive prefix of this thread's items (excl added to the tile's
-// prefix) and the tile's total; all threads of the block call it.
-__device__ __forceinline__ uint32_t lb_block(uint32_t acc, int tile, uint64_t* status, uint32_t* s_tmp,
-                                             uint32_t* s_prefix, uint32_t* tile_total, LbGiveUp gu) {
-    uint32_t tot;
-    const uint32_t excl = block_exclusive<LB_THREADS>(acc, s_tmp, &tot);
+// Publishes the block's totals, looks back and publishes its inclusive
+// prefix; every thread gets the exclusive one.
+__device__ __forceinline__ uint64_t lb_exchange(uint64_t totals, int b, uint64_t* status, uint64_t* s_prefix,
+                                                LbGiveUp gu) {
     if (threadIdx.x < kWave) {
         const int lane = threadIdx.x;
-        uint32_t prefix = 0;
-        if (tile == 0) {
-            if (lane == 0) lb_publish(status, LB_INC, tot);
-        } else {
-            if (lane == 0) lb_publish(status + tile, LB_AGG, tot);
-            prefix = lb_lookback(status, tile, gu);
-            if (lane == 0) lb_publish(status + tile, LB_INC, prefix + tot);
+        uint64_t prefix = 0;
+        if (b > 0) {
+            if (lane == 0) lb_publish(status + b, LB_AGG | totals);
+            prefix = lb_lookback(status, b, gu);
         }
-        if (lane == 0) *s_prefix = prefix;
-    }
-    __syncthreads();
-    *tile_total = tot;
-    return *s_prefix + excl;
-}
-
-__device__ __forceinline__ int lb_ticket(uint32_t* ticket, int* s_tile) {
-    if (threadIdx.x == 0) *s_tile = (int)atomicAdd(ticket, 1u);
-    __syncthreads();
-    return *s_tile;
-}
-
-// Instance bookkeeping written by the last tile of the instance-offset scan.
-struct CountsOut {
-    int64_t* counts;         // (instances, visible pairs, overflow, look-back gave up, sticky)
-    int64_t* n_clamped;      // min(instances, capacity)
-    const int64_t* n_vis;
-    int64_t capacity;
-};
-
-// Two-step exclusive scan for long inputs: tile totals, then every tile
-// sums the totals before it and scans its own items (no top-level launch,
-// no waiting between blocks).  Tiles of LB_TILE items, LB_ITEMS consecutive
-// items per thread.
-template <class Load>
-__global__ void __launch_bounds__(LB_THREADS) k_tile_sums(Load ld, const int64_t* count_dev, int64_t n_max,
-                                                          uint32_t* __restrict__ sums) {
-    __shared__ uint32_t s_tmp[LB_THREADS / kWave];
-    const int64_t count = eff_count(count_dev, n_max);
-    const int64_t tbase = (int64_t)blockIdx.x * LB_TILE;
-    if (tbase >= count) return;  // uniform; no later tile reads this sum
-    const int64_t base = tbase + (int64_t)threadIdx.x * LB_ITEMS;
-    uint32_t acc = 0;
-#pragma unroll
-    for (int k = 0; k < LB_ITEMS; ++k)
-        if (base + k < count) acc += ld(base + k);
-    uint32_t tot;
-    block_exclusive<LB_THREADS>(acc, s_tmp, &tot);
-    if (threadIdx.x == 0) sums[blockIdx.x] = tot;
-}
-
-template <class Load>
-__global__ void __launch_bounds__(LB_THREADS) k_tile_scan(Load ld, const int64_t* count_dev, int64_t n_max,
-                                                          const uint32_t* __restrict__ sums, uint32_t* out,
-                                                          int64_t* total, CountsOut co) {
-    __shared__ uint32_t s_tmp[LB_THREADS / kWave];
-    const int64_t count = eff_count(count_dev, n_max);
-    const int64_t tbase = (int64_t)blockIdx.x * LB_TILE;
-    if (tbase >= count && blockIdx.x != 0) return;  // uniform
-    const uint32_t prefix = block_sum_before<LB_THREADS>(sums, (int)blockIdx.x, s_tmp);
-    const int64_t base = tbase + (int64_t)threadIdx.x * LB_ITEMS;
-    uint32_t v[LB_ITEMS];
-    uint32_t acc = 0;
-#pragma unroll
-    for (int k = 0; k < LB_ITEMS; ++k) {
-        v[k] = (base + k < count) ? ld(base + k) : 0u;
-        acc += v[k];
-    }
-    uint32_t tot;
-    uint32_t run = prefix + block_exclusive<LB_THREADS>(acc, s_tmp, &tot);
-#pragma unroll
-    for (int k = 0; k < LB_ITEMS; ++k) {
-        if (base + k < count) out[base + k] = run;
-        run += v[k];
-    }
-    if (threadIdx.x == 0 && tbase + LB_TILE >= count) {  // the last tile with items (tile 0 if none)
-        const int64_t I = (int64_t)prefix + tot;
-        if (total != nullptr) *total = I;
-        if (co.counts != nullptr) {
-            co.counts[0] = I;
-            co.counts[1] = *co.n_vis;
-            co.counts[2] = I > co.capacity ? 1 : 0;
-            co.counts[3] = 0;
-            if (I > co.capacity) co.counts[4] |= 1;  // sticky: only the caller clears it
-            *co.n_clamped = I < co.capacity ? I : co.capacity;
+        if (lane == 0) {
+            lb_publish(status + b, LB_INC | ((prefix + totals) & LB_VALUE));
+            *s_prefix = prefix;
         }
     }
+    __syncthreads();
+    return *s_prefix;
 }
 
-// Exclusive scan of ld(0 .. count) into out (in place allowed: a tile is
-// read before it is written and by no other block); *total <- the sum.
-// Grid: lb_tiles(n_max) blocks.
-template <class Load>
-__global__ void __launch_bounds__(LB_THREADS) k_scan_lb(Load ld, const int64_t* count_dev, int64_t n_max,
-                                                        uint64_t* status, uint32_t* ticket, uint32_t* out,
-                                                        int64_t* total, LbGiveUp gu) {
-    __shared__ uint32_t s_tmp[LB_THREADS / kWave];
-    __shared__ uint32_t s_prefix;
-    __shared__ int s_tile;
-    const int tile = lb_ticket(ticket, &s_tile);
-    const int64_t count = eff_count(count_dev, n_max);
-    const int64_t tbase = (int64_t)tile * LB_TILE;
-    if (tbase >= count && tile != 0) return;  // uniform: no later tile reads this one
-    const int64_t base = tbase + (int64_t)threadIdx.x * LB_ITEMS;
-    uint32_t v[LB_ITEMS];
-    uint32_t acc = 0;
-#pragma unroll
-    for (int k = 0; k < LB_ITEMS; ++k) {
-        v[k] = (base + k < count) ? ld(base + k) : 0u;
-        acc += v[k];
-    }
-    uint32_t tot;
-    uint32_t run = lb_block(acc, tile, status, s_tmp, &s_prefix, &tot, gu);
-#pragma unroll
-    for (int k = 0; k < LB_ITEMS; ++k) {
-        if (base + k < count) out[base + k] = run;
-        run += v[k];
-    }
-    if (threadIdx.x == 0 && total != nullptr && tbase + LB_TILE >= count) *total = (int64_t)s_prefix + tot;
-}
-
-// Single-pass scan for short inputs (few tiles: the look-back stays short).
-template <class Load>
-hipError_t exclusive_scan(Load ld, const int64_t* count_dev, int64_t n_max, uint64_t* status, uint32_t* ticket,
-                          uint32_t* out, int64_t* total, LbGiveUp gu, hipStream_t s) {
-    const int64_t nt = lb_tiles(n_max);
-    hipLaunchKernelGGL(k_scan_lb<Load>, dim3((unsigned)(nt > 0 ? nt : 1)), dim3(LB_THREADS), 0, s, ld, count_dev,
-                       n_max, status, ticket, out, total, gu);
-    return hipGetLastError();
-}
-
-// Two-step scan for long inputs; sums holds lb_tiles(n_max) words.
-template <class Load>
-hipError_t exclusive_scan_long(Load ld, const int64_t* count_dev, int64_t n_max, uint32_t* sums, uint32_t* out,
-                               int64_t* total, hipStream_t s, CountsOut co) {
-    const int64_t nt = lb_tiles(n_max) > 0 ? lb_tiles(n_max) : 1;
-    hipLaunchKernelGGL(k_tile_sums<Load>, dim3((unsigned)nt), dim3(LB_THREADS), 0, s, ld, count_dev, n_max, sums);
-    hipLaunchKernelGGL(k_tile_scan<Load>, dim3((unsigned)nt), dim3(LB_THREADS), 0, s, ld, count_dev, n_max, sums,
-                       out, total, co);
-    return hipGetLastError();
-}
-
-// Zeroes the look-back status words and tickets of one binning call and the
-// per-tile ranges (a fill kernel rather than a memset, so that graph replays
-// stay correct).
-__global__ void k_bin_reset(uint64_t* status, int64_t n_status, uint32_t* tickets, int n_tickets, uint32_t* ranges,
-                            int64_t n_ranges) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_status; i += stride) status[i] = 0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_ranges; i += stride) ranges[i] = 0;
-    if (blockIdx.x == 0 && (int)threadIdx.x < n_tickets) tickets[threadIdx.x] = 0;
+__device__ __forceinline__ int lb_ticket(uint32_t* ticket, int* s_block) {
+    if (threadIdx.x == 0) *s_block = (int)atomicAdd(ticket, 1u);
+    __syncthreads();
+    return *s_block;
 }
 
 // ----------------------------------------------------------------------------
-// stable LSD radix sort of (u32 key, u32 value), 8-bit digits
+// instance offsets and emission
 // ----------------------------------------------------------------------------
-// Key source of a radix pass: the (key, value) arrays of the previous pass.
-// (A source may also skip elements, key() returning false: the histogram
-// and the scatter then leave them out.)
-struct SrcKV {
-    const uint32_t* keys;
-    const uint32_t* vals;
-    __device__ bool key(int64_t i, uint32_t& k) const {
-        k = keys[i];
-        return true;
-    }
-    __device__ uint32_t val(int64_t i) const { return vals[i]; }
+constexpr int EM_THREADS = 1024, EM_WAVES = EM_THREADS / kWave;
+constexpr int EM_ITEMS = 16;                         // pairs per lane and pass at most
+constexpr int EM_PASS = EM_THREADS * EM_ITEMS;       // pairs per workgroup and pass at most
+constexpr int EM_RING = 2 * kWave;                   // queued visible pairs per wavefront
+constexpr int EM_LOOKBACK = 128;                     // up to this many chunks, offsets by look-back
+constexpr int EM_LDS_BYTES = 65536;                  // tile counters per workgroup at most (of 160 KB a CU)
+constexpr int SC_WAVES = 16, SC_THREADS = SC_WAVES * kWave;
+constexpr int SC_MAXBLK = 4096;                      // blocks of k_tile_scan at most
+
+// The words one call clears before it uses them.
+struct BinState {
+    uint32_t emit_ticket, scan_ticket, long_count, long_ticket;
+    int64_t instances, placed;  // all of them; those below the capacity
+    uint64_t emit_status[EM_LOOKBACK];
+    uint64_t scan_status[SC_MAXBLK];
 };
-// Key source whose value is the key's own position (the first pass of a
-// sort that carries the input order along, so nobody has to write it out).
-struct SrcKI {
-    const uint32_t* keys;
-    __device__ bool key(int64_t i, uint32_t& k) const {
-        k = keys[i];
-        return true;
-    }
-    __device__ uint32_t val(int64_t i) const { return (uint32_t)i; }
-};
-template <class Src>
-__global__ void __launch_bounds__(RS_THREADS) k_radix_hist(Src src, const int64_t* count_dev, int64_t n_max,
-                                                           int shift, uint32_t* __restrict__ hist, int nblk) {
-    __shared__ uint32_t h[256];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1);
-    h[tid] = 0;
-    __syncthreads();
-    int64_t lo, hi;
-    rs_chunk(eff_count(count_dev, n_max), nblk, lo, hi);
-    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    for (int64_t i0 = lo; i0 < hi; i0 += RS_THREADS) {
-        const int64_t i = i0 + tid;
-        uint32_t key = 0;
-        const bool valid = i < hi && src.key(i, key);
-        const uint32_t d = valid ? ((key >> shift) & 0xffu) : 0u;
-        const uint64_t peers = match_digit(d, valid);
-        if (valid && (peers & lt) == 0) atomicAdd(&h[d], (uint32_t)__popcll(peers));
-    }
-    __syncthreads();
-    hist[(int64_t)tid * nblk + blockIdx.x] = h[tid];
+static_assert(sizeof(BinState) % 4 == 0, "cleared as words");
+
+// Clears the call's state and the give-up flag (with a kernel, not a memset,
+// so that graph replays stay correct).
+__device__ __forceinline__ void bin_reset(BinState* st, int64_t* counts) {
+    const int stride = (int)(gridDim.x * blockDim.x), i0 = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    uint32_t* w = reinterpret_cast<uint32_t*>(st);
+    for (int i = i0; i < (int)(sizeof(BinState) / 4); i += stride) w[i] = 0;
+    if (i0 == 0) counts[3] = 0;
 }
 
-// Stable scatter of one pass, a tile of RS_TILE keys at a time: every key is
-// ranked inside the tile (wavefront ballots per row of RS_THREADS keys, then
-// per digit a prefix over the rows and wavefronts, then over the digits),
-// the tile is reordered by digit in LDS, and each digit's run of keys is
-// written to its global position as consecutive addresses, instead of every
-// key going to a different place.
-template <class Src>
-__global__ void __launch_bounds__(RS_THREADS) k_radix_scatter(Src src, const int64_t* count_dev, int64_t n_max,
-                                                              int shift, const uint32_t* __restrict__ offs,
-                                                              int nblk, uint32_t* __restrict__ keys_out,
-                                                              uint32_t* __restrict__ vals_out,
-                                                              const uint32_t* __restrict__ gave_up) {
-    constexpr int SLOTS = RS_ITEMS * RS_WAVES;  // (row, wavefront) slots of a tile
-    __shared__ uint32_t s_base[256];             // next global position per digit
-    __shared__ uint32_t s_lstart[256];           // first tile position per digit
-    __shared__ uint32_t s_cnt[SLOTS][256];       // per slot: count, then offset within the digit
-    __shared__ uint32_t s_key[RS_TILE];
-    __shared__ uint32_t s_val[RS_TILE];
-    __shared__ uint32_t s_tmp[RS_WAVES];
+__global__ void __launch_bounds__(256) k_bin_reset(BinState* st, int64_t* counts) { bin_reset(st, counts); }
+
+// Instances and visible pairs of every chunk of pairs.
+__global__ void __launch_bounds__(EM_THREADS) k_chunk_sums(const int32_t* __restrict__ touched, int n, int per_view,
+                                                           int64_t chunk, uint32_t* __restrict__ inst_sums,
+                                                           uint32_t* __restrict__ vis_sums, BinState* st,
+                                                           int64_t* counts) {
+    __shared__ uint32_t s_w[2][EM_WAVES];
+    bin_reset(st, counts);
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    int64_t lo, hi;
-    rs_chunk(eff_count(count_dev, n_max), nblk, lo, hi);
-    if (lo >= hi) return;  // uniform across the block
-    if (*gave_up) return;  // the digit offsets are not to be trusted (uniform)
-    s_base[tid] = offs[(int64_t)tid * nblk + blockIdx.x];
-    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    for (int64_t t0 = lo; t0 < hi; t0 += RS_TILE) {
+    const int v = (int)blockIdx.x / per_view;
+    const int64_t i0 = (int64_t)((int)blockIdx.x - v * per_view) * chunk, i1 = min(i0 + chunk, (int64_t)n);
+    const int32_t* src = touched + (int64_t)v * n;
+    uint32_t a = 0, b = 0;
+    for (int64_t j = i0; j < i1; j += EM_PASS) {
 #pragma unroll
-        for (int sl = 0; sl < SLOTS; ++sl) s_cnt[sl][tid] = 0;
-        __syncthreads();
-        uint32_t key[RS_ITEMS], val[RS_ITEMS], rank[RS_ITEMS];
-        bool valid[RS_ITEMS];
-#pragma unroll
-        for (int k = 0; k < RS_ITEMS; ++k) {
-            const int64_t i = t0 + k * RS_THREADS + tid;
-            key[k] = 0;
-            valid[k] = i < hi && src.key(i, key[k]);
-            val[k] = valid[k] ? src.val(i) : 0u;
-            const uint32_t d = (key[k] >> shift) & 0xffu;
-            const uint64_t peers = match_digit(d, valid[k]);
-            rank[k] = (uint32_t)__popcll(peers & lt);
-            if (valid[k] && rank[k] == 0) s_cnt[k * RS_WAVES + wave][d] = (uint32_t)__popcll(peers);
+        for (int k = 0; k < EM_ITEMS; ++k) {
+            const int64_t i = j + k * EM_THREADS + tid;
+            const int32_t c = i < i1 ? src[i] : 0;
+            a += (uint32_t)c;
+            b += c > 0 ? 1u : 0u;
         }
-        __syncthreads();
-        // thread d: offsets of digit d's slots, in tile order
-        uint32_t run = 0;
-#pragma unroll
-        for (int sl = 0; sl < SLOTS; ++sl) {
-            const uint32_t c = s_cnt[sl][tid];
-            s_cnt[sl][tid] = run;
-            run += c;
-        }
-        uint32_t nvalid;
-        s_lstart[tid] = block_exclusive<RS_THREADS>(run, s_tmp, &nvalid);
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < RS_ITEMS; ++k) {
-            if (valid[k]) {
-                const uint32_t d = (key[k] >> shift) & 0xffu;
-                const uint32_t p = s_lstart[d] + s_cnt[k * RS_WAVES + wave][d] + rank[k];
-                s_key[p] = key[k];
-                s_val[p] = val[k];
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < RS_ITEMS; ++k) {
-            const uint32_t p = (uint32_t)(k * RS_THREADS + tid);
-            if (p < nvalid) {
-                const uint32_t kk = s_key[p], vv = s_val[p];
-                const uint32_t d = (kk >> shift) & 0xffu;
-                const uint32_t g = s_base[d] + (p - s_lstart[d]);
-                if (g < n_max) {
-                    keys_out[g] = kk;
-                    vals_out[g] = vv;
-                }
-            }
-        }
-        __syncthreads();
-        s_base[tid] += run;
     }
-}
-
-// One radix pass from src into (ko, vo): digit histograms, their look-back
-// scan (status words and ticket zeroed beforehand; *total <- the number of
-// keys that took part), then the stable scatter.
-template <class Src>
-hipError_t radix_pass(Src src, const int64_t* count_dev, int64_t n_max, int shift, uint32_t* hist,
-                      uint64_t* status, uint32_t* ticket, int64_t* total, uint32_t* ko, uint32_t* vo, LbGiveUp gu,
-                      hipStream_t s) {
-    const int nblk = rs_blocks(n_max);
-    hipLaunchKernelGGL(k_radix_hist<Src>, dim3(nblk), dim3(RS_THREADS), 0, s, src, count_dev, n_max, shift, hist,
-                       nblk);
-    hipError_t e = exclusive_scan(LoadU32{hist}, nullptr, (int64_t)256 * nblk, status, ticket, hist, total, gu, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_radix_scatter<Src>, dim3(nblk), dim3(RS_THREADS), 0, s, src, count_dev, n_max, shift, hist,
-                       nblk, ko, vo, gu.flag);
-    return hipGetLastError();
-}
-
-// Sorts keys over `passes` 8-bit digits starting at bit 0, each key carrying
-// its input position as its value (vals is not read), ping-ponging with
-// (keys2, vals2); an even pass count ends in (keys, vals).
-// Pass p scans its digit offsets with status words status + p * spine_tiles
-// and ticket tickets[p] (all zeroed beforehand).
-hipError_t radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys2, uint32_t* vals2, const int64_t* count_dev,
-                      int64_t n_max, int passes, uint32_t* hist, uint64_t* status, int64_t spine_tiles,
-                      uint32_t* tickets, LbGiveUp gu, hipStream_t s) {
-    if (n_max <= 0) return hipSuccess;
-    uint32_t *ki = keys, *vi = vals, *ko = keys2, *vo = vals2;
-    for (int p = 0; p < passes; ++p) {
-        hipError_t e = (p == 0) ? radix_pass(SrcKI{ki}, count_dev, n_max, 0, hist, status, tickets, nullptr, ko,
-                                             vo, gu, s)
-                                : radix_pass(SrcKV{ki, vi}, count_dev, n_max, 8 * p, hist,
-                                             status + p * spine_tiles, tickets + p, nullptr, ko, vo, gu, s);
-        if (e != hipSuccess) return e;
-        uint32_t* t = ki; ki = ko; ko = t;
-        t = vi; vi = vo; vo = t;
+    a = wave_sum_u32(a, lane);
+    b = wave_sum_u32(b, lane);
+    if (lane == 0) {
+        s_w[0][wave] = a;
+        s_w[1][wave] = b;
     }
-    return hipGetLastError();
-}
-
-// ----------------------------------------------------------------------------
-// pipeline kernels
-// ----------------------------------------------------------------------------
-// Order-preserving compaction of the visible pairs in three steps: the
-// visible count of each run of CV_RUN consecutive pairs, an exclusive scan
-// of those counts (one block), then each run ranks its pairs with ballots
-// and writes (tile count, pair index) at its offset.
-constexpr int CV_THREADS = 256;
-constexpr int CV_RUN = 2048;
-
-__global__ void __launch_bounds__(CV_THREADS) k_count_visible(const int32_t* __restrict__ touched, int64_t vn,
-                                                              uint32_t* __restrict__ run_counts) {
-    __shared__ uint32_t s_w[CV_THREADS / kWave];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int64_t base = (int64_t)blockIdx.x * CV_RUN;
-    uint32_t c = 0;
-#pragma unroll
-    for (int k = 0; k < CV_RUN / CV_THREADS; ++k) {
-        const int64_t i = base + k * CV_THREADS + tid;
-        c += (i < vn && touched[i] > 0) ? 1u : 0u;
-    }
-    c = wave_sum_u32(c, lane);
-    if (lane == 0) s_w[wave] = c;
     __syncthreads();
     if (tid == 0) {
-        uint32_t t = 0;
-        for (int w = 0; w < CV_THREADS / kWave; ++w) t += s_w[w];
-        run_counts[blockIdx.x] = t;
+        uint32_t x = 0, y = 0;
+        for (int w = 0; w < EM_WAVES; ++w) {
+            x += s_w[0][w];
+            y += s_w[1][w];
+        }
+        inst_sums[blockIdx.x] = x;
+        vis_sums[blockIdx.x] = y;
     }
 }
 
-__global__ void __launch_bounds__(CV_THREADS) k_compact_visible(const int32_t* __restrict__ touched,
-                                                                const uint32_t* __restrict__ run_offs, int64_t vn,
-                                                                uint32_t* __restrict__ counts,
-                                                                uint32_t* __restrict__ vals) {
-    __shared__ uint32_t s_w[CV_THREADS / kWave];
+struct EmitArgs {
+    const int32_t* touched;
+    const uint4* rect;
+    const gs_view* views;
+    int n, n_views, tile, per_view;  // per_view: chunks of each view
+    int64_t chunk, capacity;
+    int items;       // pairs per lane and pass
+    int window;      // tiles counted at once
+    const uint32_t *inst_sums, *vis_sums;  // not read with the look-back
+    BinState* st;
+    uint32_t* table;
+    int stride;      // words between the table's entries
+    uint32_t *cell_e, *rank_e, *depth_e;
+    int32_t *inst_gid, *pair_first;
+    int64_t* counts;
+    LbGiveUp gu;
+};
+
+// The table: row b of view v (chunk b of it) starts at entry
+// per_view * tile_offset + b * (tiles of the view).
+__device__ __forceinline__ int64_t table_row(const gs_view& vw, int per_view, int b, int tiles_v) {
+    return (int64_t)per_view * vw.tile_offset + (int64_t)b * tiles_v;
+}
+
+// Emission of one chunk of pairs of one view.  The visible pair whose first
+// instance has emission index o writes one instance per tile of its
+// rectangle at o, o + 1, ... (row-major): its Gaussian (inst_gid), its
+// depth's binary32 bits (depth_e, which the projection stored with the
+// rectangle), its table entry (cell_e) and its place among the entry's
+// (rank_e).  pair_first[pair] = o, so the instances of a pair stay contiguous
+// in emission space whatever the tile lists do.
+//
+// The chunk's offset: with LOOKBACK (few chunks) a single-pass scan over the
+// chunks before it, otherwise the sums k_chunk_sums left (with many chunks
+// the chain of waits costs more than a second reading of the tile counts).
+//
+// Each wavefront walks its own contiguous part of the chunk, queues the
+// visible pairs in LDS and takes them up to 64 at a time, a pair per lane;
+// the lanes then stride over all of the group's instances together, so a pair
+// with many tiles does not stall its wavefront and the writes are contiguous
+// across lanes.  The pair of each instance: every pair whose first instance
+// falls in the current 64 marks that slot with its lane in LDS, and a
+// max-scan over the wavefront (DPP) carries the latest mark to every later
+// slot.
+//
+// Counting in LDS and not in memory: a returning atomic per instance on
+// counters in memory (eight sets, one per XCD) made this kernel 128 us at
+// eight 1200x680 views, 26 G atomics/s, against 57 us now.  The counters
+// are 16 bits wide (a pair is in a tile once, so a count is at most the
+// chunk's pairs), two to a word; WIDE, 32 bits, where a chunk has more pairs
+// than that.  A view of more tiles than the counters hold is counted in
+// several windows of tiles, the walk repeated for each.
+template <bool LOOKBACK, bool WIDE>
+__global__ void __launch_bounds__(EM_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) k_emit(EmitArgs A) {
+    extern __shared__ uint32_t s_cnt[];
+    __shared__ uint32_t s_tmp[EM_WAVES];
+    __shared__ uint64_t s_prefix;
+    __shared__ int s_block;
+    __shared__ uint16_t s_qpair[EM_WAVES][EM_RING];   // queued pairs: index in the wavefront's part of the pass,
+    __shared__ uint32_t s_qfirst[EM_WAVES][EM_RING];  // first instance in the pass
+    __shared__ uint2 s_info[EM_WAVES][kWave];  // (x0 | y0 << 16, rect width)
+    __shared__ uint2 s_who[EM_WAVES][kWave];   // (Gaussian, depth bits)
+    __shared__ int32_t s_mark[EM_WAVES][kWave];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int64_t base = (int64_t)blockIdx.x * CV_RUN;
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    uint32_t run = run_offs[blockIdx.x];
+    const int total_chunks = A.per_view * A.n_views;
+    const int ch = LOOKBACK ? lb_ticket(&A.st->emit_ticket, &s_block) : (int)blockIdx.x;
+    const int v = ch / A.per_view, cb = ch - v * A.per_view;
+    const gs_view& vw = A.views[v];
+    const int tiles_x = ceil_div(vw.width, A.tile), tiles_v = tiles_x * ceil_div(vw.height, A.tile);
+    const int64_t row = table_row(vw, A.per_view, cb, tiles_v);
+    const int64_t c0 = (int64_t)cb * A.chunk, c1 = min(c0 + A.chunk, (int64_t)A.n);
+    const int64_t vbase = (int64_t)v * A.n;
+    const int pass = EM_THREADS * A.items;
+    // this wavefront's pairs of the pass that starts at j: item k of lane l is
+    // pair j + wave * (64 items) + 64 k + l
+    auto tiles_of = [&](int64_t j, int k) {
+        const int64_t i = j + (int64_t)wave * (kWave * A.items) + k * kWave + lane;
+        return k < A.items && i < c1 ? A.touched[vbase + i] : 0;
+    };
+    // first instance of this wavefront within the pass, and the pass's totals
+    auto pass_offsets = [&](int64_t j, uint32_t& off, uint32_t& tot_i, uint32_t& tot_v) {
+        uint32_t ni = 0, nv = 0;
 #pragma unroll
-    for (int k = 0; k < CV_RUN / CV_THREADS; ++k) {
-        const int64_t i = base + k * CV_THREADS + tid;
-        const bool vis = i < vn && touched[i] > 0;
-        const uint64_t m = __ballot(vis);
-        if (lane == 0) s_w[wave] = (uint32_t)__popcll(m);
-        __syncthreads();
-        uint32_t off = run, tot = 0;
-#pragma unroll
-        for (int w = 0; w < CV_THREADS / kWave; ++w) {
-            if (w < wave) off += s_w[w];
-            tot += s_w[w];
+        for (int k = 0; k < EM_ITEMS; ++k) {
+            const int32_t c = tiles_of(j, k);
+            ni += (uint32_t)c;
+            nv += c > 0 ? 1u : 0u;
         }
-        if (vis) {
-            const uint32_t p = off + (uint32_t)__popcll(m & lt);
-            counts[p] = (uint32_t)touched[i];
-            vals[p] = (uint32_t)i;
+        const uint32_t e = block_exclusive<EM_THREADS>(ni, s_tmp, &tot_i);
+        off = (uint32_t)__builtin_amdgcn_readlane((int)e, 0);  // the lanes' pairs are interleaved
+        tot_v = 0;
+        if (LOOKBACK) block_exclusive<EM_THREADS>(nv, s_tmp, &tot_v);
+    };
+    // 1. the chunk's offset
+    uint64_t prefix;
+    const bool one_pass = c1 - c0 <= pass;
+    uint32_t off = 0, tot_i = 0, tot_v = 0;
+    pass_offsets(c0, off, tot_i, tot_v);
+    if constexpr (LOOKBACK) {
+        uint64_t tot = ((uint64_t)tot_v << 32) + tot_i;
+        for (int64_t j = c0 + pass; j < c1; j += pass) {  // uniform
+            uint32_t o2, ti, tv;
+            pass_offsets(j, o2, ti, tv);
+            tot += ((uint64_t)tv << 32) + ti;
         }
-        run += tot;
+        prefix = lb_exchange(tot, ch, A.st->emit_status, &s_prefix, A.gu);
+        if (ch == total_chunks - 1 && tid == 0) {
+            const int64_t I = (int64_t)(uint32_t)(prefix + tot);
+            A.st->instances = I;
+            A.counts[1] = (int64_t)((prefix + tot) >> 32);
+        }
+    } else {
+        prefix = block_sum<EM_THREADS>(A.inst_sums, ch, s_tmp);
+        if (ch == total_chunks - 1) {  // uniform
+            const uint32_t nv = block_sum<EM_THREADS>(A.vis_sums, total_chunks, s_tmp);
+            if (tid == 0) {
+                A.st->instances = (int64_t)(uint32_t)prefix + A.inst_sums[ch];
+                A.counts[1] = nv;
+            }
+        }
+    }
+    if (ch == total_chunks - 1 && tid == 0) {
+        const int64_t I = A.st->instances;
+        A.st->placed = I < A.capacity ? I : A.capacity;
+        A.counts[0] = I;
+        A.counts[2] = I > A.capacity ? 1 : 0;
+        if (I > A.capacity) atomicOr(A.gu.sticky, 1u);  // sticky: only the caller clears it
+    }
+    const int64_t first = (int64_t)(uint32_t)prefix;
+
+    // 2. the walk, once per window of tiles
+    for (int w0 = 0; w0 < tiles_v; w0 += A.window) {
+        const int wn = min(A.window, tiles_v - w0);
+        const int words = WIDE ? wn : (wn + 1) / 2;
         __syncthreads();
+        for (int i = tid; i < words; i += EM_THREADS) s_cnt[i] = 0;
+        __syncthreads();
+        int64_t done = 0;  // instances of the passes before
+        for (int64_t j = c0; j < c1; j += pass) {
+            if (!(j == c0 && (w0 == 0 || one_pass))) pass_offsets(j, off, tot_i, tot_v);
+            uint32_t run = off;  // first instance of the next pair, within the pass
+            int head = 0, tail = 0;
+            const uint32_t wpair = (uint32_t)(j + (int64_t)wave * (kWave * A.items));
+            // emits the queued pairs [head, head + ng), one per lane
+            auto emit = [&](int ng) {
+                uint32_t my_start = 0, my_end = 0;
+                const int q0 = head & (EM_RING - 1);
+                const uint32_t gstart = s_qfirst[wave][q0];
+                if (lane < ng) {
+                    const int q = (head + lane) & (EM_RING - 1);
+                    const uint32_t i = wpair + s_qpair[wave][q], f = s_qfirst[wave][q];
+                    const uint4 r = A.rect[vbase + i];
+                    const uint32_t x0 = r.x & 0xffffu, y0 = r.x >> 16, x1 = r.y & 0xffffu, y1 = r.y >> 16;
+                    const uint32_t wr = x1 - x0 + 1, hr = y1 - y0 + 1;
+                    my_start = f - gstart;
+                    my_end = my_start + wr * hr;
+                    if (w0 == 0) A.pair_first[vbase + i] = (int32_t)(first + done + f);
+                    s_info[wave][lane] = make_uint2(x0 | (y0 << 16), wr);
+                    s_who[wave][lane] = make_uint2(i, r.z);
+                }
+                const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)my_end, ng - 1);
+                const int64_t o_g = first + done + gstart;
+                int carry = 0;  // the pair of the last instance before the current 64
+                for (uint32_t b0 = 0; b0 < total; b0 += kWave) {
+                    s_mark[wave][lane] = -1;
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    // starts strictly increase (a visible pair has an
+                    // instance), so a slot is marked at most once
+                    if (lane < ng && my_start >= b0 && my_start < b0 + kWave) s_mark[wave][my_start - b0] = lane;
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    const int lo = max(wave_max_scan(s_mark[wave][lane]), carry);
+                    carry = __builtin_amdgcn_readlane(lo, kWave - 1);
+                    const uint32_t k = b0 + lane;
+                    const int64_t o = o_g + k;
+                    const uint2 info = s_info[wave][lo], who = s_who[wave][lo];
+                    // row and column of the instance in the rectangle (width
+                    // info.y): the quotient is below 2^16, so a float estimate
+                    // is within one of it and one correction step makes it exact
+                    const uint32_t li = k - (s_qfirst[wave][(head + lo) & (EM_RING - 1)] - gstart);
+                    uint32_t q = (uint32_t)((float)li * __builtin_amdgcn_rcpf((float)info.y));
+                    int32_t r = (int32_t)(li - q * info.y);
+                    if (r < 0) {
+                        --q;
+                        r += (int32_t)info.y;
+                    } else if (r >= (int32_t)info.y) {
+                        ++q;
+                        r -= (int32_t)info.y;
+                    }
+                    const int t = (int)((info.x >> 16) + q) * tiles_x + (int)(info.x & 0xffffu) + r;
+                    if (k < total && o < A.capacity) {
+                        if (w0 == 0) {
+                            A.inst_gid[o] = (int32_t)who.x;
+                            A.depth_e[o] = who.y;
+                        }
+                        if (t >= w0 && t < w0 + wn) {
+                            uint32_t rank;
+                            if constexpr (WIDE) {
+                                rank = atomicAdd(&s_cnt[t - w0], 1u);
+                            } else {
+                                const int sh = ((t - w0) & 1) * 16;
+                                rank = (atomicAdd(&s_cnt[(t - w0) >> 1], 1u << sh) >> sh) & 0xffffu;
+                            }
+                            A.cell_e[o] = (uint32_t)(row + t);
+                            A.rank_e[o] = rank;
+                        }
+                    }
+                }
+                head += ng;
+                // the next group rewrites this wavefront's LDS
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            };
+            // one round per 64 pairs (the next ones' counts in flight), and a
+            // last one for what is left in the queue
+            int32_t next = tiles_of(j, 0);
+            for (int k = 0; k <= A.items; ++k) {
+                const int32_t c = next;
+                next = tiles_of(j, k + 1);
+                const uint32_t incl = (uint32_t)wave_add_scan(c);
+                const uint64_t m = __builtin_amdgcn_ballot_w64(c > 0);
+                if (c > 0) {
+                    const int q = (tail + (int)__popcll(m & lt)) & (EM_RING - 1);
+                    s_qpair[wave][q] = (uint16_t)(k * kWave + lane);
+                    s_qfirst[wave][q] = run + incl - (uint32_t)c;
+                }
+                run += (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+                tail += (int)__popcll(m);
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                const int ng = min(tail - head, kWave);
+                if (ng == kWave || (k == A.items && ng > 0)) emit(ng);
+            }
+            done += tot_i;
+        }
+        __syncthreads();
+        for (int i = tid; i < wn; i += EM_THREADS) {
+            const uint32_t x = WIDE ? s_cnt[i] : (s_cnt[i >> 1] >> ((i & 1) * 16)) & 0xffffu;
+            A.table[(row + w0 + i) * A.stride] = x;
+        }
     }
 }
 
-// Emission: the visible pair at compacted position i writes one instance
-// per tile of its rectangle at emission indices offs[i] .. offs[i] + touched - 1
-// (row-major over the rectangle): key = global tile id (the first tile-sort
-// pass attaches the emission index as the value).  inst_gid[e] keeps the Gaussian of emission index e,
-// depth_e[e] the binary32 bits of its pair's camera depth (the per-tile sort
-// key, read there by emission index instead of through inst_gid and the
-// pair's projected record: one gather per instance instead of two dependent
-// ones; the projection stores the bits in the pair's rectangle entry, so
-// this kernel reads them with the rectangle), pair_first[pair] the first
-// emission index of the pair, so that the
-// instances of one (view, Gaussian) pair stay contiguous in emission space
-// after the tile sort has reordered them.
-// Each wavefront takes 64 consecutive pairs and its lanes stride over all of
-// their instances together, 64 at a time, so a pair with many tiles does
-// not stall its wavefront and the writes are contiguous across lanes.  The
-// pair of each instance: every pair whose first instance falls in the
-// current 64 marks that slot with its lane in LDS, and a max-scan over the
-// wavefront (DPP) carries the latest mark to every later slot.
-__global__ void __launch_bounds__(256) k_emit(const uint32_t* __restrict__ vis_vals,
-                                              const uint32_t* __restrict__ offs, const int64_t* n_vis,
-                                              const uint4* __restrict__ rect, const gs_view* __restrict__ views,
-                                              int n, int tile, int64_t capacity,
-                                              uint32_t* __restrict__ keys, int32_t* __restrict__ inst_gid,
-                                              uint32_t* __restrict__ depth_e, int32_t* __restrict__ pair_first) {
-    __shared__ uint32_t s_start[4][kWave];
-    __shared__ uint4 s_info[4][kWave];  // (x0 | y0 << 16, rect width, tile base, tiles per row)
-    __shared__ int32_t s_gid[4][kWave];
-    __shared__ uint32_t s_depth[4][kWave];
-    __shared__ int32_t s_mark[4][kWave];
+// ----------------------------------------------------------------------------
+// tile ranges and placement
+// ----------------------------------------------------------------------------
+// [start, end) of every tile (0, 0 where it has no instance, and everywhere
+// when a wait gave up), and each table entry <- the first place of its
+// instances: a single-pass scan over blocks of `rounds` groups of 64 tiles.
+// A group's tiles lie across the lanes of a wavefront, its chunks are shared
+// out over the wavefronts.
+__global__ void __launch_bounds__(SC_THREADS) k_tile_scan(uint32_t* table, int stride, const gs_view* views,
+                                                          int n_views, int tile, int per_view, int tiles, int rounds,
+                                                          int2* ranges, BinState* st, LbGiveUp gu) {
+    __shared__ uint32_t s_part[SC_WAVES][kWave];
+    __shared__ uint32_t s_at[kWave];
+    __shared__ uint32_t s_sum;
+    __shared__ uint64_t s_prefix;
+    __shared__ int s_block;
+    const int b = lb_ticket(&st->scan_ticket, &s_block);
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int64_t nv = *n_vis;
-    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + (int64_t)wave * kWave;
-    if (i0 >= nv) return;  // uniform across the wavefront
-    const int64_t i = i0 + lane;
-    const bool valid = i < nv;
-    int64_t o_i = 0, end_i = 0;
-    if (valid) {
-        const uint32_t pair = vis_vals[i];
-        const int v = (int)(pair / (uint32_t)n);
-        const uint32_t gid = pair - (uint32_t)v * (uint32_t)n;
-        const uint4 r = rect[pair];
-        const uint32_t x0 = r.x & 0xffffu, y0 = r.x >> 16, x1 = r.y & 0xffffu, y1 = r.y >> 16;
-        const uint32_t wr = x1 - x0 + 1, hr = y1 - y0 + 1;
-        o_i = offs[i];
-        end_i = o_i + (int64_t)wr * hr;
-        pair_first[pair] = (int32_t)o_i;
-        s_info[wave][lane] = make_uint4(x0 | (y0 << 16), wr, (uint32_t)views[v].tile_offset,
-                                        (uint32_t)ceil_div(views[v].width, tile));
-        s_gid[wave][lane] = (int32_t)gid;
-        s_depth[wave][lane] = r.z;
-    }
-    const int64_t o_w = read_lane_i64(o_i, 0);  // lane 0 is valid
-    s_start[wave][lane] = (uint32_t)(o_i - o_w);
-    const int nvalid = (int)__popcll(__ballot(valid));
-    const int64_t total = read_lane_i64(end_i, nvalid - 1) - o_w;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const int64_t my_start = valid ? o_i - o_w : -1;
-    int carry = 0;  // the pair of the last instance before the current 64
-    for (int64_t base = 0; base < total; base += kWave) {
-        const int64_t k = base + lane;
-        s_mark[wave][lane] = -1;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        // starts strictly increase (a visible pair has an instance), so a
-        // slot is marked at most once
-        if (my_start >= base && my_start < base + kWave) s_mark[wave][my_start - base] = lane;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const int lo = max(wave_max_scan(s_mark[wave][lane]), carry);
-        carry = __builtin_amdgcn_readlane(lo, kWave - 1);
-        if (k >= total) continue;
-        const uint4 info = s_info[wave][lo];
-        const uint32_t li = (uint32_t)(k - s_start[wave][lo]);
-        // row and column of instance li in the rectangle (width info.y):
-        // the quotient is below 2^16, so a float estimate is within one of
-        // it and one correction step makes it exact
-        int64_t q = (int64_t)((float)li * __builtin_amdgcn_rcpf((float)info.y));
-        int64_t r = (int64_t)li - q * (int64_t)info.y;
-        if (r < 0) {
-            --q;
-            r += info.y;
-        } else if (r >= (int64_t)info.y) {
-            ++q;
-            r -= info.y;
+    const bool off = *gu.flag != 0;  // of an earlier launch
+    const int seg = (per_view + SC_WAVES - 1) / SC_WAVES;
+    const int r0 = min(wave * seg, per_view), r1 = min(r0 + seg, per_view);
+    constexpr int KEEP = 16;
+    uint32_t c[KEEP];
+    int64_t col = 0, step = 0;  // this lane's column: its entry of row 0, the distance of the rows
+    // the column sums of group r by wavefront, in s_part; the first KEEP of
+    // the wavefront's entries stay in c
+    auto group_sums = [&](int r) {
+        const int64_t t = ((int64_t)b * rounds + r) * kWave + lane;
+        const bool in = !off && t < tiles;
+        if (in) {
+            const int v = view_of_tile(views, n_views, (int)t);
+            const gs_view& vw = views[v];
+            const int tiles_v = ceil_div(vw.width, tile) * ceil_div(vw.height, tile);
+            col = (table_row(vw, per_view, 0, tiles_v) + (t - vw.tile_offset)) * stride;
+            step = (int64_t)tiles_v * stride;
         }
-        const uint32_t yy = (info.x >> 16) + (uint32_t)q, xx = (info.x & 0xffffu) + (uint32_t)r;
-        const int64_t o = o_w + k;
-        if (o < capacity) {
-            keys[o] = info.z + yy * info.w + xx;
-            inst_gid[o] = s_gid[wave][lo];
-            depth_e[o] = s_depth[wave][lo];
+        uint32_t sum = 0;
+#pragma unroll
+        for (int k = 0; k < KEEP; ++k) {
+            c[k] = in && r0 + k < r1 ? table[col + (r0 + k) * step] : 0u;
+            sum += c[k];
+        }
+        if (in)
+            for (int q = r0 + KEEP; q < r1; ++q) sum += table[col + q * step];
+        s_part[wave][lane] = sum;
+        __syncthreads();
+    };
+    uint32_t total = 0;  // of the block (wavefront 0)
+    for (int r = 0; r < rounds; ++r) {
+        group_sums(r);
+        if (wave == 0) {
+            uint32_t x = 0;
+            for (int w = 0; w < SC_WAVES; ++w) x += s_part[w][lane];
+            total += wave_sum_u32(x, lane);
+        }
+        if (rounds > 1) __syncthreads();
+    }
+    uint32_t start = (uint32_t)lb_exchange(total, b, st->scan_status, &s_prefix, gu);
+    for (int r = 0; r < rounds; ++r) {
+        if (rounds > 1) group_sums(r);
+        const int64_t t = ((int64_t)b * rounds + r) * kWave + lane;
+        if (wave == 0) {
+            uint32_t x = 0;
+            for (int w = 0; w < SC_WAVES; ++w) x += s_part[w][lane];
+            const uint32_t incl = (uint32_t)wave_add_scan((int)x);
+            const uint32_t at = start + incl - x;
+            s_at[lane] = at;
+            if (lane == kWave - 1) s_sum = incl;
+            if (t < tiles) ranges[t] = x > 0 ? make_int2((int)at, (int)(at + x)) : make_int2(0, 0);
+        }
+        __syncthreads();
+        // with stride 2 the table is the ranges themselves (one chunk per
+        // view): an entry's first place is its range's start
+        if (!off && t < tiles && stride == 1) {
+            uint32_t at = s_at[lane];
+            for (int w = 0; w < wave; ++w) at += s_part[w][lane];
+#pragma unroll
+            for (int k = 0; k < KEEP; ++k) {
+                if (r0 + k < r1) table[col + (r0 + k) * step] = at;
+                at += c[k];
+            }
+            for (int q = r0 + KEEP; q < r1; ++q) {
+                const uint32_t x = table[col + q * step];
+                table[col + q * step] = at;
+                at += x;
+            }
+        }
+        start += s_sum;
+        __syncthreads();
+    }
+}
+
+// Every instance's sort key, (depth bits << 32 | emission index), to its
+// place in its tile's list.
+constexpr int PL_THREADS = 256, PL_ITEMS = 4;
+__global__ void __launch_bounds__(PL_THREADS) k_place(const uint32_t* __restrict__ cell_e,
+                                                      const uint32_t* __restrict__ rank_e,
+                                                      const uint32_t* __restrict__ depth_e,
+                                                      const uint32_t* __restrict__ table, int stride,
+                                                      const BinState* __restrict__ st, int64_t capacity,
+                                                      uint64_t* __restrict__ slab,
+                                                      const uint32_t* __restrict__ gave_up) {
+    const int64_t I = st->placed;
+    if (*gave_up) return;
+    // XCD x takes the x-th eighth of the instances: with several views the
+    // lists they go to are then few enough to be filled in its own L2 (eight
+    // 1200x680 views: 30 us, 46 with the instances dealt to all XCDs)
+    constexpr int64_t TILE = PL_THREADS * PL_ITEMS;
+    const int64_t share = (I + kXcds * TILE - 1) / (kXcds * TILE) * TILE;
+    const int64_t x0 = (int64_t)(blockIdx.x & (kXcds - 1)) * share, x1 = x0 + share < I ? x0 + share : I;
+    for (int64_t b0 = x0 + (int64_t)(blockIdx.x / kXcds) * TILE; b0 < x1; b0 += (int64_t)(gridDim.x / kXcds) * TILE) {
+        uint32_t ci[PL_ITEMS], rk[PL_ITEMS], d[PL_ITEMS];
+#pragma unroll
+        for (int k = 0; k < PL_ITEMS; ++k) {
+            const int64_t e = b0 + k * PL_THREADS + threadIdx.x;
+            const int64_t ec = e < x1 ? e : x1 - 1;
+            ci[k] = cell_e[ec];
+            rk[k] = rank_e[ec];
+            d[k] = depth_e[ec];
+        }
+#pragma unroll
+        for (int k = 0; k < PL_ITEMS; ++k) {
+            const int64_t e = b0 + k * PL_THREADS + threadIdx.x;
+            const int64_t p = (int64_t)table[(size_t)ci[k] * stride] + rk[k];
+            if (e < x1 && p < capacity) slab[p] = ((uint64_t)d[k] << 32) | (uint64_t)e;
         }
     }
 }
 
-// Per-tile [start, end) of the sorted instances; nothing (every range left
-// empty) when a look-back of the sort gave up.
-__global__ void k_ranges(const uint32_t* __restrict__ keys, const int64_t* n_inst, int2* __restrict__ ranges,
-                         const uint32_t* __restrict__ gave_up) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t I = *n_inst;
-    if (i >= I || *gave_up) return;
-    const uint32_t k = keys[i];
-    if (i == 0 || keys[i - 1] != k) ranges[k].x = (int)i;
-    if (i == I - 1 || keys[i + 1] != k) ranges[k].y = (int)(i + 1);
-}
-
-// Per-tile depth order.  The visible pairs are emitted in (view, index)
-// order and the tile sort is stable, so each tile's instances arrive in
-// Gaussian-index order; a stable sort of each tile's list by the binary32
-// bits of its pair's camera depth (positive, so the bits order like the
-// values) leaves them in (depth, index) order, the order the forward and
-// backward walk.  The sort key of the instance at list position i is
-// (depth bits << 32 | i): distinct keys, so any correct sort is the stable
-// one.  A list is cut into runs of 64 keys, one key per lane; each run is
-// sorted across the lanes of a wavefront by a bitonic network; the rank of
-// a key among up to eight runs (a chunk of 512) is its lane plus, for every
-// other run, the number of that run's keys below it (a 6-step binary search
-// in LDS); chunks of a longer list merge the same way (8- or 9-step
-// searches in the other sorted chunks).  k_tile_sort_short gives each list of up to
-// kTsShort one wavefront; k_tile_sort_long gives each longer list a
-// workgroup, in LDS up to kTsLong, and beyond that (rare) stable counting
-// passes over 8-bit digits in global memory (the tile's slices of the
-// sorted tile keys, whose values are all the tile's own id and are written
-// back, and of the tile sort's ping-pong arrays, unused by then).
+// ----------------------------------------------------------------------------
+// per-tile sort
+// ----------------------------------------------------------------------------
+// Each tile's keys (depth bits << 32 | emission index; depths are positive, so
+// the bits order like the values) in ascending order: distinct keys, so any
+// correct sort is the one.  A list is cut into runs of 64 keys, one key per
+// lane; each run is sorted across the lanes of a wavefront by a bitonic
+// network; the rank of a key among up to eight runs (a chunk of 512) is its
+// lane plus, for every other run, the number of that run's keys below it (a
+// 6-step binary search in LDS); chunks of a longer list merge the same way
+// (8- or 9-step searches in the other sorted chunks).  k_tile_sort_short
+// gives each list of up to kTsShort one wavefront and queues the longer ones
+// for k_tile_sort_long, which gives each up to kTsLong a workgroup; beyond
+// that, one workgroup sorts each kTsLong keys of it and, when all of them are
+// sorted, each finds the places of its keys by 12-step searches in the others.
 constexpr int kTsShort = 512, kTsLong = 4096;
 constexpr int kTsChunk = 512;  // keys a wavefront sorts at once (8 runs of 64)
 
-template <int NT>
-struct SegSortLds {
-    uint32_t next[256];             // next output position per digit
-    uint32_t wcnt[NT / kWave][256];  // per chunk: each wavefront's count per digit
-    uint32_t tmp[NT / kWave];
-};
-
-// One stable counting pass of the whole block over the digit at `shift`:
-// (kin, vin) -> (kout, vout), L items, every array in LDS or every array in
-// global memory.  Chunks of NT items: ranks within a wavefront from ballots,
-// wavefronts in order, chunks in order.  Thread tid keeps the digits
-// tid * DPT .. tid * DPT + DPT - 1 of the tables.
-template <int NT>
-__device__ void seg_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, int L, int shift,
-                         SegSortLds<NT>& S) {
-    constexpr int DPT = 256 / NT, NW = NT / kWave;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-#pragma unroll
-    for (int q = 0; q < DPT; ++q) S.next[tid * DPT + q] = 0;
-    __syncthreads();
-    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    for (int c0 = 0; c0 < L; c0 += NT) {
-        // one LDS atomic per run of equal digits in a wavefront (the keys of
-        // a tile share most of their high bits)
-        const int i = c0 + tid;
-        const bool valid = i < L;
-        const uint32_t d = valid ? (kin[i] >> shift) & 0xffu : 0u;
-        const uint64_t peers = match_digit(d, valid);
-        if (valid && (peers & lt) == 0) atomicAdd(&S.next[d], (uint32_t)__popcll(peers));
-    }
-    __syncthreads();
-    uint32_t c[DPT], sum = 0;
-#pragma unroll
-    for (int q = 0; q < DPT; ++q) {
-        c[q] = S.next[tid * DPT + q];
-        sum += c[q];
-    }
-    uint32_t tot;
-    uint32_t run = block_exclusive<NT>(sum, S.tmp, &tot);  // barriers inside
-#pragma unroll
-    for (int q = 0; q < DPT; ++q) {
-        S.next[tid * DPT + q] = run;
-        run += c[q];
-    }
-    for (int c0 = 0; c0 < L; c0 += NT) {
-#pragma unroll
-        for (int w = 0; w < NW; ++w)
-#pragma unroll
-            for (int q = 0; q < DPT; ++q) S.wcnt[w][tid * DPT + q] = 0;
-        __syncthreads();
-        const int i = c0 + tid;
-        const bool valid = i < L;
-        const uint32_t k = valid ? kin[i] : 0u, v = valid ? vin[i] : 0u;
-        const uint32_t d = (k >> shift) & 0xffu;
-        const uint64_t peers = match_digit(d, valid);
-        const uint32_t rank = (uint32_t)__popcll(peers & lt);
-        if (valid && rank == 0) S.wcnt[wave][d] = (uint32_t)__popcll(peers);
-        __syncthreads();
-        if (valid) {
-            uint32_t o = S.next[d] + rank;
-            for (int w = 0; w < wave; ++w) o += S.wcnt[w][d];
-            kout[o] = k;
-            vout[o] = v;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < DPT; ++q) {
-            uint32_t add = 0;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) add += S.wcnt[w][tid * DPT + q];
-            S.next[tid * DPT + q] += add;
-        }
-    }
-}
-
 constexpr int TSS_THREADS = kWave;  // short lists: one wavefront per tile
-constexpr int TSL_THREADS = 256;    // long lists: one workgroup per tile
+constexpr int TSL_THREADS = 256;    // long lists: one workgroup per kTsLong keys
 constexpr uint64_t kNoKey = ~0ull;  // padding, above every real key
 
 template <int J>
@@ -892,194 +727,234 @@ __device__ __forceinline__ void wave_sort_chunk_n(int n, uint64_t (&k)[8], int (
     }
 }
 
-// Sort key of list position i of the tile: (depth bits << 32) | i.
-__device__ __forceinline__ uint64_t depth_key(const uint32_t* __restrict__ depth_e, uint32_t e, int i) {
-    return ((uint64_t)depth_e[e] << 32) | (uint32_t)i;
-}
+// Work of k_tile_sort_long: a whole list, or part `part` of one of more than
+// kTsLong keys, first to sort and then to merge with the other parts.
+// Entries of one list are consecutive, the sorts before the merges.
+enum { kWhole = 0, kSortPart = 1, kMergePart = 2 };
+struct LongItem {
+    uint32_t tile, kind, part, first;  // first: index of the list's first entry (its done counter)
+};
 
 // Tiles in the XCD-aware order of the compositing launches (tile_of_block).
-__global__ void __launch_bounds__(TSS_THREADS) k_tile_sort_short(const int2* __restrict__ ranges, int total_tiles,
-                                                                  int run, const uint32_t* __restrict__ depth_e,
+// After a wait gave up, every list is left empty.
+__global__ void __launch_bounds__(TSS_THREADS) k_tile_sort_short(int2* __restrict__ ranges, int total_tiles,
+                                                                  int run_log2, const uint64_t* __restrict__ slab,
+                                                                  uint32_t* __restrict__ tile_keys,
                                                                   int32_t* __restrict__ inst,
-                                                                  uint32_t* __restrict__ long_list,
-                                                                  uint32_t* __restrict__ long_count,
+                                                                  LongItem* __restrict__ items,
+                                                                  uint32_t* __restrict__ done, BinState* st,
                                                                   const uint32_t* __restrict__ gave_up) {
     static_assert(kTsShort == kTsChunk && kTsChunk == 8 * kWave, "a short list is one chunk of eight runs");
     __shared__ uint64_t s_run[kTsChunk];
-    __shared__ uint32_t s_e[kTsShort];
-    const int t = tile_of_block(blockIdx.x, total_tiles, run);
-    if (t < 0 || *gave_up) return;  // after a look-back gave up the lists are not sorted (and none is long)
-    const int2 rg = ranges[t];
-    const int L = rg.y - rg.x;
-    if (L > kTsShort) {  // uniform across the wavefront: left to k_tile_sort_long
-        if (threadIdx.x == 0) long_list[atomicAdd(long_count, 1u)] = (uint32_t)t;
+    const int t = tile_of_block(blockIdx.x, total_tiles, run_log2);
+    if (t < 0) return;
+    const int lane = threadIdx.x;
+    if (*gave_up) {
+        if (lane == 0) ranges[t] = make_int2(0, 0);
         return;
     }
-    if (L <= 1) return;
-    const int lane = threadIdx.x;
-    uint32_t* einst = reinterpret_cast<uint32_t*>(inst) + rg.x;
+    const int2 rg = ranges[t];
+    const int L = rg.y - rg.x;
+    if (L <= 0) return;
+    if (L > kTsShort) {  // uniform across the wavefront: left to k_tile_sort_long
+        const uint32_t parts = (uint32_t)(L + kTsLong - 1) / kTsLong, ne = parts > 1 ? 2 * parts : 1;
+        uint32_t at = 0;
+        if (lane == 0) {
+            at = atomicAdd(&st->long_count, ne);
+            done[at] = 0;
+        }
+        at = (uint32_t)__builtin_amdgcn_readlane((int)at, 0);
+        for (uint32_t k = lane; k < ne; k += kWave)
+            items[at + k] = {(uint32_t)t, (uint32_t)(ne == 1 ? kWhole : (k < parts ? kSortPart : kMergePart)),
+                             k % parts, at};
+        return;
+    }
+    const uint64_t* in = slab + rg.x;
     uint64_t k[8];
     int rank[8];
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
         const int i = r * kWave + lane;
-        k[r] = kNoKey;
-        if (i < L) {
-            const uint32_t e = einst[i];
-            s_e[i] = e;
-            k[r] = depth_key(depth_e, e, i);
-        }
+        k[r] = i < L ? in[i] : kNoKey;
     }
     wave_sort_chunk_n(L, k, rank, s_run, lane);
-    // s_e was written by other lanes of this (only) wavefront
-    __syncthreads();
 #pragma unroll
-    for (int r = 0; r < 8; ++r)
-        if (r * kWave < L && k[r] != kNoKey) einst[rank[r]] = s_e[(uint32_t)k[r]];
-}
-
-// One long list (tile t, more than kTsShort instances), by the whole block.
-__device__ void sort_long_list(int t, const int2* __restrict__ ranges, const uint32_t* __restrict__ depth_e,
-                               uint32_t* __restrict__ tile_keys,
-                               int32_t* __restrict__ inst, uint32_t* __restrict__ gk, uint32_t* __restrict__ gv,
-                               uint64_t (&s_sorted)[kTsLong], uint64_t (&s_run)[TSL_THREADS / kWave][kTsChunk],
-                               uint32_t (&s_e)[kTsLong], SegSortLds<TSL_THREADS>& S) {
-    constexpr int NW = TSL_THREADS / kWave;
-    const int2 rg = ranges[t];
-    const int L = rg.y - rg.x;
-    uint32_t* einst = reinterpret_cast<uint32_t*>(inst) + rg.x;
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    if (L <= kTsLong) {
-        // chunks of 256 keys (four runs) up to 1024, so that all four
-        // wavefronts sort; of 512 beyond, where more chunks would make the
-        // final merge's searches the larger cost
-        const bool small = L <= 4 * (kTsChunk / 2);
-        const int CH = small ? kTsChunk / 2 : kTsChunk;
-        const int nchunk = (L + CH - 1) / CH;
-        for (int c = wave; c < nchunk; c += NW) {
-            const int c0 = c * CH;
-            const int nc = min(CH, L - c0);
-            uint64_t k[8];
-            int rank[8];
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                const int i = c0 + r * kWave + lane;
-                k[r] = kNoKey;
-                if (r * kWave < CH && i < L) {
-                    const uint32_t e = einst[i];
-                    s_e[i] = e;
-                    k[r] = depth_key(depth_e, e, i);
-                }
-            }
-            wave_sort_chunk_n(nc, k, rank, s_run[wave], lane);
-#pragma unroll
-            for (int r = 0; r < 8; ++r)
-                if (r * kWave + lane < nc) s_sorted[c0 + rank[r]] = k[r];
-            // pad the last chunk to a full CH for the searches
-            for (int i = nc + lane; i < CH; i += kWave) s_sorted[c0 + i] = kNoKey;
-            // s_run is rewritten by this wavefront's next chunk
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        }
-        __syncthreads();
-        for (int j = threadIdx.x; j < L; j += TSL_THREADS) {
-            const uint64_t key = s_sorted[j];
-            const int c = j / CH;
-            int pos = j - c * CH;
-            for (int c2 = 0; c2 < nchunk; ++c2) {
-                if (c2 == c) continue;
-                pos += small ? count_below<8>(s_sorted + c2 * CH, key) : count_below<9>(s_sorted + c2 * CH, key);
-            }
-            einst[pos] = s_e[(uint32_t)key];
-        }
-        return;
-    }
-    // in global memory: (depth bits, emission index) start in (tile_keys,
-    // inst) and ping-pong with the scratch slices; after four passes they
-    // are back
-    uint32_t* bk = tile_keys + rg.x;
-    uint32_t* ak = gk + rg.x;
-    uint32_t* av = gv + rg.x;
-    for (int i = threadIdx.x; i < L; i += TSL_THREADS)
-        bk[i] = depth_e[einst[i]];
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        // the previous pass's global writes are complete and visible to the
-        // whole block (and not stale in this CU's cache) before they are read
-        __threadfence();
-        __syncthreads();
-        if (p & 1) seg_pass<TSL_THREADS>(ak, av, bk, einst, L, 8 * p, S);
-        else seg_pass<TSL_THREADS>(bk, einst, ak, av, L, 8 * p, S);
-    }
-    __threadfence();
-    __syncthreads();
-    for (int i = threadIdx.x; i < L; i += TSL_THREADS) bk[i] = (uint32_t)t;
-}
-
-// The lists longer than kTsShort, which k_tile_sort_short listed in
-// long_list: a fixed grid of workgroups walks the list, one tile each at a
-// time.  Up to kTsLong: each wavefront sorts chunks (wave_sort_chunk) of 256
-// keys for lists up to 1024, else of 512, into s_sorted (the last chunk
-// padded with kNoKey), then every key's place
-// is its rank in its chunk plus, for each other chunk, the number of that
-// chunk's keys below it.  Beyond kTsLong: stable counting passes over the
-// four bytes of the depth bits in global memory.
-__global__ void __launch_bounds__(TSL_THREADS) k_tile_sort_long(const int2* __restrict__ ranges,
-                                                                 const uint32_t* __restrict__ long_list,
-                                                                 const uint32_t* __restrict__ long_count,
-                                                                 const uint32_t* __restrict__ depth_e,
-                                                                 uint32_t* __restrict__ tile_keys,
-                                                                 int32_t* __restrict__ inst,
-                                                                 uint32_t* __restrict__ gk,
-                                                                 uint32_t* __restrict__ gv) {
-    __shared__ uint64_t s_sorted[kTsLong];
-    __shared__ uint64_t s_run[TSL_THREADS / kWave][kTsChunk];
-    __shared__ uint32_t s_e[kTsLong];
-    __shared__ SegSortLds<TSL_THREADS> S;
-    const uint32_t count = *long_count;
-    for (uint32_t idx = blockIdx.x; idx < count; idx += gridDim.x) {
-        sort_long_list((int)long_list[idx], ranges, depth_e, tile_keys, inst, gk, gv, s_sorted, s_run, s_e, S);
-        __syncthreads();  // the LDS is reused by the next tile
+    for (int r = 0; r < 8; ++r) {
+        if (r * kWave < L && k[r] != kNoKey) inst[rg.x + rank[r]] = (int32_t)(uint32_t)k[r];
+        if (r * kWave + lane < L) tile_keys[rg.x + r * kWave + lane] = (uint32_t)t;
     }
 }
 
-
-struct WsLayout {
-    size_t vis_k0, vis_v0, inst_k2, inst_v2, depth_e, hist, sums, status, tickets, cnt, long_list, total;
-    int64_t spine_tiles, n_status;
+struct LongLds {
+    uint64_t sorted[kTsLong];
+    uint64_t run[TSL_THREADS / kWave][kTsChunk];
 };
 
-constexpr int kMaxPasses = 4;            // radix passes per sort (32-bit keys)
-constexpr int kTickets = kMaxPasses + 1; // one per radix pass of the tile sort, then the long-list count
+// The L (<= kTsLong) keys at `in`, sorted by the whole block: put(place, key)
+// is called for each.
+template <class Put>
+__device__ __forceinline__ void sort_long_chunk(const uint64_t* __restrict__ in, int L, LongLds& S, Put put) {
+    constexpr int NW = TSL_THREADS / kWave;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    // chunks of 256 keys (four runs) up to 1024, so that all four wavefronts
+    // sort; of 512 beyond, where more chunks would make the final merge's
+    // searches the larger cost
+    const bool small = L <= 4 * (kTsChunk / 2);
+    const int CH = small ? kTsChunk / 2 : kTsChunk;
+    const int nchunk = (L + CH - 1) / CH;
+    for (int c = wave; c < nchunk; c += NW) {
+        const int c0 = c * CH;
+        const int nc = min(CH, L - c0);
+        uint64_t k[8];
+        int rank[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const int i = c0 + r * kWave + lane;
+            k[r] = r * kWave < CH && i < L ? in[i] : kNoKey;
+        }
+        wave_sort_chunk_n(nc, k, rank, S.run[wave], lane);
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+            if (r * kWave + lane < nc) S.sorted[c0 + rank[r]] = k[r];
+        // pad the last chunk to a full CH for the searches
+        for (int i = nc + lane; i < CH; i += kWave) S.sorted[c0 + i] = kNoKey;
+        // S.run is rewritten by this wavefront's next chunk
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+    __syncthreads();
+    for (int j = threadIdx.x; j < L; j += TSL_THREADS) {
+        const uint64_t key = S.sorted[j];
+        const int c = j / CH;
+        int pos = j - c * CH;
+        for (int c2 = 0; c2 < nchunk; ++c2) {
+            if (c2 == c) continue;
+            pos += small ? count_below<8>(S.sorted + c2 * CH, key) : count_below<9>(S.sorted + c2 * CH, key);
+        }
+        put(pos, key);
+    }
+}
+
+// The queued lists.  A fixed grid of workgroups takes the entries by tickets;
+// a merge waits for the sorts of its own list, whose tickets are earlier.
+__global__ void __launch_bounds__(TSL_THREADS) k_tile_sort_long(int2* __restrict__ ranges,
+                                                                 const LongItem* __restrict__ items,
+                                                                 uint32_t* done, BinState* st, uint64_t* slab,
+                                                                 uint32_t* __restrict__ tile_keys,
+                                                                 int32_t* __restrict__ inst, LbGiveUp gu) {
+    __shared__ LongLds S;
+    __shared__ int s_item;
+    __shared__ int s_ok;
+    const int count = (int)st->long_count;
+    for (;;) {
+        __syncthreads();  // the LDS is reused by the next entry
+        if (count == 0) return;  // uniform
+        const int item = lb_ticket(&st->long_ticket, &s_item);
+        if (item >= count) return;
+        const LongItem it = items[item];
+        const int2 rg = ranges[it.tile];
+        const int L = rg.y - rg.x;
+        if (it.kind == kWhole) {
+            sort_long_chunk(slab + rg.x, L, S, [&](int pos, uint64_t key) {
+                inst[rg.x + pos] = (int32_t)(uint32_t)key;
+                tile_keys[rg.x + pos] = it.tile;
+            });
+            continue;
+        }
+        const int parts = (L + kTsLong - 1) / kTsLong;
+        const int p0 = (int)it.part * kTsLong, np = min(kTsLong, L - p0);
+        uint64_t* mine = slab + rg.x + p0;
+        if (it.kind == kSortPart) {
+            // in place: every key is in LDS before the first is written
+            sort_long_chunk(mine, np, S, [&](int pos, uint64_t key) { mine[pos] = key; });
+            __threadfence();  // the part is visible to the merges before it counts as done
+            __syncthreads();
+            if (threadIdx.x == 0) __hip_atomic_fetch_add(done + it.first, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            continue;
+        }
+        if (threadIdx.x == 0) {
+            const auto ready = [&] {
+                return (int)__hip_atomic_load(done + it.first, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) >= parts;
+            };
+            bool ok = ready();
+            for (int spin = 0; !ok && spin < gu.spin_limit; ++spin) ok = ready();
+            if (!ok) {  // the list is left empty; the caller discards the call's results
+                give_up(gu);
+                ranges[it.tile] = make_int2(0, 0);
+            }
+            s_ok = ok;
+        }
+        __syncthreads();
+        if (!s_ok) continue;
+        __threadfence();      // nothing of the other parts is read from before the wait
+        for (int j = threadIdx.x; j < np; j += TSL_THREADS) {
+            const uint64_t key = mine[j];
+            int pos = j;
+            for (int q = 0; q < parts; ++q) {
+                if (q == (int)it.part) continue;
+                const uint64_t* a = slab + rg.x + q * kTsLong;
+                int lo = 0, hi = min(kTsLong, L - q * kTsLong);  // first key above `key`
+                while (lo < hi) {
+                    const int m = (lo + hi) >> 1;
+                    if (a[m] < key) lo = m + 1;
+                    else hi = m;
+                }
+                pos += lo;
+            }
+            inst[rg.x + pos] = (int32_t)(uint32_t)key;
+            tile_keys[rg.x + pos] = it.tile;
+        }
+    }
+}
+
+struct WsLayout {
+    size_t slab, cell_e, rank_e, depth_e, inst_sums, vis_sums, state, items, done, table, total;
+    int64_t table_words;
+};
+
+// Chunks of a view of n pairs: of 1024 pairs while there are few (a workgroup
+// per CU), then 4096, then 16384 or whole multiples of them, so that there
+// are at most about a thousand and their table stays small.
+struct Chunks {
+    int64_t chunk;
+    int per_view, items;
+};
+Chunks chunks_of(int n, int n_views, int64_t total_tiles, int64_t table_words) {
+    auto per_view = [&](int64_t c) { return (int)((n + c - 1) / c); };
+    auto count = [&](int64_t c) { return (int64_t)n_views * per_view(c); };
+    int64_t c = count(1024) <= 256 ? 1024 : (count(4096) <= 512 ? 4096 : EM_PASS);
+    while (count(c) > 1024 && c < n) c *= 2;
+    // the table has to fit; at worst a chunk is a whole view
+    while (per_view(c) * total_tiles > table_words && per_view(c) > 1) c *= 2;
+    return {c, per_view(c), (int)(c < EM_PASS ? c : EM_PASS) / EM_THREADS};
+}
 
 WsLayout ws_layout(int n, int n_views, int64_t capacity) {
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
     const int64_t vn = (int64_t)n * n_views;
-    const int64_t cap = capacity > 0 ? capacity : 1;
-    const int64_t big = vn > cap ? vn : cap;
-    const int64_t nblk = rs_blocks(big);
+    const size_t cap = (size_t)(capacity > 0 ? capacity : 1);
+    const size_t chunks = (size_t)n_views * (size_t)((n + 1023) / 1024);  // at most
+    // entries of the long lists: a list of L keys has one up to kTsLong and
+    // 2 ceil(L / kTsLong) <= L / (kTsShort + 1) beyond
+    const size_t entries = cap / (kTsShort + 1) + 1;
     WsLayout L;
-    L.spine_tiles = lb_tiles(256 * nblk);
-    // run counts of the compaction, then tile totals of the instance-offset
-    // scan (runs are the shorter, so there are more of them)
-    const int64_t vt = (vn + CV_RUN - 1) / CV_RUN > 0 ? (vn + CV_RUN - 1) / CV_RUN : 1;
-    static_assert(CV_RUN <= LB_TILE, "the run counts need at least as many words as the tile totals");
-    // look-back status words: kMaxPasses radix spines
-    L.n_status = kMaxPasses * L.spine_tiles;
+    // the (chunk, tile) table: the tiles are not known here, so 4 MB, and
+    // four words per pair (at most 128 MB) where there are many; a call whose
+    // tiles need more takes larger chunks
+    const int64_t want = 4 * vn;
+    L.table_words = want < (1 << 20) ? (1 << 20) : (want > (32 << 20) ? (32 << 20) : want);
     size_t o = 0;
-    L.vis_k0 = o; o += al(4 * (size_t)(vn > 0 ? vn : 1));
-    L.vis_v0 = o; o += al(4 * (size_t)(vn > 0 ? vn : 1));
-    L.inst_k2 = o; o += al(4 * (size_t)cap);
-    L.inst_v2 = o; o += al(4 * (size_t)cap);
-    L.depth_e = o; o += al(4 * (size_t)cap);
-    L.hist = o; o += al(4 * (size_t)(256 * nblk + 1));
-    L.sums = o; o += al(4 * (size_t)vt);
-    L.status = o; o += al(8 * (size_t)L.n_status);
-    L.tickets = o; o += al(4 * (size_t)kTickets);
-    L.cnt = o; o += al(8 * 4);
-    // tiles with more than kTsShort instances: at most capacity / (kTsShort + 1)
-    L.long_list = o; o += al(4 * (size_t)(cap / (kTsShort + 1) + 1));
+    L.slab = o; o += al(8 * cap);
+    L.cell_e = o; o += al(4 * cap);
+    L.rank_e = o; o += al(4 * cap);
+    L.depth_e = o; o += al(4 * cap);
+    L.inst_sums = o; o += al(4 * chunks);
+    L.vis_sums = o; o += al(4 * chunks);
+    L.state = o; o += al(sizeof(BinState));
+    L.items = o; o += al(sizeof(LongItem) * entries);
+    L.done = o; o += al(4 * entries);
+    L.table = o; o += al(4 * (size_t)L.table_words);
     L.total = o;
     return L;
 }
@@ -1088,8 +963,8 @@ WsLayout ws_layout(int n, int n_views, int64_t capacity) {
 
 size_t binsort_workspace_bytes(int n, int n_views, int64_t capacity) { return ws_layout(n, n_views, capacity).total; }
 
-// Reads a look-back wait may take before it gives up (LB_SPIN_MAX, or the
-// value of SGS_LOOKBACK_SPIN, which tests set to force the give-up path).
+// Reads a wait may take before it gives up (LB_SPIN_MAX, or the value of
+// SGS_LOOKBACK_SPIN, which tests set to force the give-up path).
 int lookback_spin_limit() {
     const char* v = std::getenv("SGS_LOOKBACK_SPIN");
     if (v == nullptr || *v == 0) return LB_SPIN_MAX;
@@ -1098,82 +973,88 @@ int lookback_spin_limit() {
 }
 
 hipError_t launch_binsort(const uint32_t* rect, const int32_t* touched, int n,
-                          const gs_view* views_dev, int n_views, int total_tiles, int tile, void* ws,
+                          const gs_view* views_dev, int n_views, int total_tiles, int max_tiles, int tile, void* ws,
                           int64_t capacity, uint32_t* tile_keys, int32_t* inst, int32_t* inst_gid,
                           int32_t* pair_first, int32_t* ranges, int64_t* counts, hipStream_t s) {
+    if (n <= 0 || n_views <= 0 || total_tiles <= 0) return hipErrorInvalidValue;
     const WsLayout L = ws_layout(n, n_views, capacity);
+    const Chunks ck = chunks_of(n, n_views, total_tiles, L.table_words);
     char* w = static_cast<char*>(ws);
-    uint32_t* vis_k0 = reinterpret_cast<uint32_t*>(w + L.vis_k0);
-    uint32_t* vis_v0 = reinterpret_cast<uint32_t*>(w + L.vis_v0);
-    uint32_t* ik2 = reinterpret_cast<uint32_t*>(w + L.inst_k2);
-    uint32_t* iv2 = reinterpret_cast<uint32_t*>(w + L.inst_v2);
-    uint32_t* depth_e = reinterpret_cast<uint32_t*>(w + L.depth_e);
-    uint32_t* hist = reinterpret_cast<uint32_t*>(w + L.hist);
-    uint32_t* sums = reinterpret_cast<uint32_t*>(w + L.sums);
-    uint64_t* status = reinterpret_cast<uint64_t*>(w + L.status);
-    uint32_t* tickets = reinterpret_cast<uint32_t*>(w + L.tickets);
-    int64_t* cnt = reinterpret_cast<int64_t*>(w + L.cnt);  // [0] n_vis [1] n_inst [2] clamped
-    const int64_t vn = (int64_t)n * n_views;
-    hipError_t e;
+    auto words = [&](size_t off) { return reinterpret_cast<uint32_t*>(w + off); };
+    BinState* st = reinterpret_cast<BinState*>(w + L.state);
+    uint64_t* slab = reinterpret_cast<uint64_t*>(w + L.slab);
+    LongItem* items = reinterpret_cast<LongItem*>(w + L.items);
+    uint32_t* done = words(L.done);
+    int2* rg = reinterpret_cast<int2*>(ranges);
 
-    // 0. zero the scan state and the counts, and clear the per-tile ranges
-    hipLaunchKernelGGL(k_bin_reset, dim3(64), dim3(256), 0, s, status, L.n_status, tickets, kTickets,
-                       reinterpret_cast<uint32_t*>(ranges), 2 * (int64_t)total_tiles);
-    // 1. order-preserving compaction of the visible pairs: (tile count, pair)
-    if (vn > 0) {
-        const unsigned nrun = (unsigned)((vn + CV_RUN - 1) / CV_RUN);
-        hipLaunchKernelGGL(k_count_visible, dim3(nrun), dim3(CV_THREADS), 0, s, touched, vn, sums);
-        hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(TOP_THREADS), 0, s, sums, (int)nrun, &cnt[0]);
-        hipLaunchKernelGGL(k_compact_visible, dim3(nrun), dim3(CV_THREADS), 0, s, touched, sums, vn, vis_k0, vis_v0);
-    } else {
-        e = fill_u32(reinterpret_cast<uint32_t*>(cnt), 0u, 8, s);
-        if (e != hipSuccess) return e;
-    }
-    // 2. instance offsets in pair order (in place over the tile counts),
-    //    total instance count and the counts
-    e = exclusive_scan_long(LoadU32{vis_k0}, &cnt[0], vn, sums, vis_k0, &cnt[1], s,
-                            CountsOut{counts, &cnt[2], &cnt[0], capacity});
-    if (e != hipSuccess) return e;
-    // 3. emission, then stable sort by global tile id
-    int bits = 1;
-    while ((1ll << bits) < (int64_t)total_tiles) ++bits;
-    const int passes = (bits + 7) / 8;
-    if (passes > kMaxPasses) return hipErrorInvalidValue;
-    uint32_t* ek = (passes % 2 == 0) ? reinterpret_cast<uint32_t*>(tile_keys) : ik2;
-    uint32_t* ev = (passes % 2 == 0) ? reinterpret_cast<uint32_t*>(inst) : iv2;
-    uint32_t* ok = (passes % 2 == 0) ? ik2 : reinterpret_cast<uint32_t*>(tile_keys);
-    uint32_t* ov = (passes % 2 == 0) ? iv2 : reinterpret_cast<uint32_t*>(inst);
-    if (vn > 0) {
-        hipLaunchKernelGGL(k_emit, dim3((unsigned)((vn + 255) / 256)), dim3(256), 0, s, vis_v0, vis_k0, &cnt[0],
-                           reinterpret_cast<const uint4*>(rect), views_dev, n, tile, capacity, ek, inst_gid, depth_e,
-                           pair_first);
-    }
-    // a look-back that waits past the spin limit (SGS_LOOKBACK_SPIN overrides
-    // it, for tests) records the give-up in counts[3] and counts[4]
+    // a wait past the spin limit (SGS_LOOKBACK_SPIN overrides it, for tests)
+    // records the give-up in counts[3] and counts[4]
     LbGiveUp gu;
     gu.flag = reinterpret_cast<uint32_t*>(counts + 3);
     gu.sticky = reinterpret_cast<uint32_t*>(counts + 4);
     gu.spin_limit = lookback_spin_limit();
-    e = radix_sort(ek, ev, ok, ov, &cnt[2], capacity, passes, hist, status, L.spine_tiles, tickets, gu, s);
-    if (e != hipSuccess) return e;
-    // 4. per-tile [start, end) (the ranges were cleared in step 0), then each
-    //    tile's list in depth order
-    if (capacity > 0) {
-        hipLaunchKernelGGL(k_ranges, dim3((unsigned)((capacity + 255) / 256)), dim3(256), 0, s,
-                           reinterpret_cast<const uint32_t*>(tile_keys), &cnt[2], reinterpret_cast<int2*>(ranges),
-                           gu.flag);
-        if (total_tiles > 0) {
-            const int2* rg = reinterpret_cast<const int2*>(ranges);
-            const int run = tile_run_log2(tile, total_tiles);
-            uint32_t* long_list = reinterpret_cast<uint32_t*>(w + L.long_list);
-            uint32_t* long_count = tickets + kMaxPasses;
-            hipLaunchKernelGGL(k_tile_sort_short, dim3(tile_grid(total_tiles, run)), dim3(TSS_THREADS), 0, s, rg,
-                               total_tiles, run, depth_e, inst, long_list, long_count, gu.flag);
-            const int64_t max_long = capacity / (kTsShort + 1) + 1;
-            const unsigned lg = (unsigned)(max_long < 1024 ? max_long : 1024);
-            hipLaunchKernelGGL(k_tile_sort_long, dim3(lg), dim3(TSL_THREADS), 0, s, rg, long_list, long_count,
-                               depth_e, tile_keys, inst, ik2, iv2);
-        }
+
+    EmitArgs A;
+    A.touched = touched;
+    A.rect = reinterpret_cast<const uint4*>(rect);
+    A.views = views_dev;
+    A.n = n;
+    A.n_views = n_views;
+    A.tile = tile;
+    A.per_view = ck.per_view;
+    A.chunk = ck.chunk;
+    A.capacity = capacity;
+    A.items = ck.items;
+    A.inst_sums = words(L.inst_sums);
+    A.vis_sums = words(L.vis_sums);
+    A.st = st;
+    // a table that does not fit even with a chunk per view has one entry per
+    // tile: the first words of the tile ranges
+    const bool own = (int64_t)ck.per_view * total_tiles <= L.table_words;
+    A.table = own ? words(L.table) : reinterpret_cast<uint32_t*>(ranges);
+    A.stride = own ? 1 : 2;
+    A.cell_e = words(L.cell_e);
+    A.rank_e = words(L.rank_e);
+    A.depth_e = words(L.depth_e);
+    A.inst_gid = inst_gid;
+    A.pair_first = pair_first;
+    A.counts = counts;
+    A.gu = gu;
+    // 1. and 2.
+    const bool wide = ck.chunk > 65535;
+    const int holds = EM_LDS_BYTES / (wide ? 4 : 2);
+    A.window = max_tiles < holds ? max_tiles : holds;
+    const size_t lds = wide ? 4 * (size_t)A.window : 4 * (((size_t)A.window + 1) / 2);
+    const unsigned chunks = (unsigned)(n_views * ck.per_view);
+    const dim3 eb(EM_THREADS);
+    if (chunks <= EM_LOOKBACK) {
+        hipLaunchKernelGGL(k_bin_reset, dim3(8), dim3(256), 0, s, st, counts);
+        hipLaunchKernelGGL((wide ? k_emit<true, true> : k_emit<true, false>), dim3(chunks), eb, lds, s, A);
+    } else {
+        hipLaunchKernelGGL(k_chunk_sums, dim3(chunks), eb, 0, s, touched, n, ck.per_view, ck.chunk,
+                           words(L.inst_sums), words(L.vis_sums), st, counts);
+        hipLaunchKernelGGL((wide ? k_emit<false, true> : k_emit<false, false>),
+                           dim3(chunks), eb, lds, s, A);
+    }
+    // 3.
+    int rounds = 1;
+    while ((int64_t)SC_MAXBLK * kWave * rounds < (int64_t)total_tiles) ++rounds;
+    const int64_t per = (int64_t)rounds * kWave;
+    hipLaunchKernelGGL(k_tile_scan, dim3((unsigned)((total_tiles + per - 1) / per)), dim3(SC_THREADS), 0, s, A.table,
+                       A.stride, views_dev, n_views, tile, ck.per_view, total_tiles, rounds, rg, st, gu);
+    if (capacity <= 0) return hipGetLastError();
+    // 4.
+    const int64_t pb = (capacity + PL_THREADS * PL_ITEMS * kXcds - 1) / (PL_THREADS * PL_ITEMS * kXcds);
+    hipLaunchKernelGGL(k_place, dim3((unsigned)(pb < 1024 ? pb : 1024) * kXcds), dim3(PL_THREADS), 0, s, A.cell_e,
+                       A.rank_e, A.depth_e, A.table, A.stride, st, capacity, slab, gu.flag);
+    // 5. and 6. (no list is longer than the Gaussians)
+    const int run_log2 = tile_run_log2(tile, total_tiles);
+    hipLaunchKernelGGL(k_tile_sort_short, dim3(tile_grid(total_tiles, run_log2)), dim3(TSS_THREADS), 0, s, rg,
+                       total_tiles, run_log2, slab, tile_keys, inst, items, done, st, gu.flag);
+    if (n > kTsShort) {
+        const int64_t max_long = capacity / (kTsShort + 1) + 1;
+        hipLaunchKernelGGL(k_tile_sort_long, dim3((unsigned)(max_long < 768 ? max_long : 768)), dim3(TSL_THREADS), 0,
+                           s, rg, items, done, st, slab, tile_keys, inst, gu);
     }
     return hipGetLastError();
 }

@@ -256,7 +256,12 @@ int gs_bin_sort(const uint32_t* rect, const int32_t* tiles_touched, int32_t n,
     if (n < 1 || capacity < 0 || capacity >= (1ll << 31) || (int64_t)n * n_views >= (1ll << 31)) return GS_EINVAL;
     if (ws_bytes < binsort_workspace_bytes(n, n_views, capacity)) return GS_ECAPACITY;
     if (!aligned16(rect) || (reinterpret_cast<uintptr_t>(ws) & 255u) != 0) return GS_EINVAL;
-    return hip_status(launch_binsort(rect, tiles_touched, n, views_dev, n_views, total_tiles, cfg->tile, ws,
+    int max_tiles = 0;  // of one view
+    for (int v = 0; v < n_views; ++v) {
+        const int t = ceil_div(views[v].width, cfg->tile) * ceil_div(views[v].height, cfg->tile);
+        max_tiles = t > max_tiles ? t : max_tiles;
+    }
+    return hip_status(launch_binsort(rect, tiles_touched, n, views_dev, n_views, total_tiles, max_tiles, cfg->tile, ws,
                                      capacity, tile_keys, inst, inst_gid, pair_first, tile_ranges, counts,
                                      reinterpret_cast<hipStream_t>(stream)));
 }
@@ -496,7 +501,7 @@ int gs_render_bwd_records(const gs_gaussians* g, const float* rec, const float* 
     const size_t rec_bytes = (size_t)(capacity > 0 ? capacity : 1) * bwd_record_floats(g->n_feat, params) * sizeof(float);
     if (ws_bytes < rec_bytes) return GS_ECAPACITY;
     if (!aligned16(rec) || !aligned16(app) || !aligned16(ws)) return GS_EINVAL;
-    const int batch = bwd_batch(cfg->tile, g->n_feat, params, cfg->lds_batch, cfg->lds_batch_bwd);
+    const int batch = bwd_batch(cfg->tile, g->n_feat, params, total_tiles, cfg->lds_batch, cfg->lds_batch_bwd);
     return hip_status(launch_render_bwd(rec, app, g->n, g->n_feat, inst, inst_gid, tile_ranges, views_dev, n_views,
                                         total_tiles, P, make_const(cfg), batch, cfg->persistent, T_final, last,
                                         grad_out, params, static_cast<float*>(ws), queue,

@@ -164,7 +164,7 @@ hipError_t launch_project(const GaussPtrs& g, const gs_view* views_dev, int n_vi
 
 size_t binsort_workspace_bytes(int n, int n_views, int64_t capacity);
 hipError_t launch_binsort(const uint32_t* rect, const int32_t* touched, int n,
-                          const gs_view* views_dev, int n_views, int total_tiles, int tile, void* ws,
+                          const gs_view* views_dev, int n_views, int total_tiles, int max_tiles, int tile, void* ws,
                           int64_t capacity, uint32_t* tile_keys, int32_t* inst, int32_t* inst_gid,
                           int32_t* pair_first, int32_t* ranges, int64_t* counts, hipStream_t s);
 
@@ -178,16 +178,21 @@ inline int fwd_batch(int tile, int n_feat, int lds_batch) {
     return lds_batch < most ? lds_batch : most;
 }
 // Backward, which also holds an accumulator of 10 + F (6 for the pose alone)
-// floats per staged Gaussian: at tile 16, 128 from 16 feature channels on
-// with parameter gradients (1249 against 1827 us at eight views and F = 16,
-// 2106 against 4291 us at F = 32), at 16 alone without (799 against 857 us;
-// at F = 32 256 is faster, 1205 against 1282 us, its registers being the
-// limit); at tile 8 64 (255 against 387 us, one view, F = 16); at tile 32
-// the four times larger workgroups fit as they are (323 us with 256, 410
-// with 128).
-inline int bwd_batch(int tile, int n_feat, bool params, int lds_batch, int lds_batch_bwd) {
+// floats per staged Gaussian.  At tile 16 with parameter gradients 128 at
+// F = 16 (1249 against 1827 us with 256, eight views), and at F = 32, where
+// 128 leave three workgroups per CU, 64 once there are more tiles than
+// workgroups to go round (16 mixed views of 2M Gaussians 5149 us, 5529 with
+// 128, 10939 with 256; one 1200x680 view 354, 329 and 544 us); for the pose
+// alone 128 at F = 16 (799 against 857 us; at F = 32 256 is faster, 1205
+// against 1282 us, its registers being the limit).  At tile 8 64 (255 against
+// 387 us, one view, F = 16); at tile 32 the four times larger workgroups fit
+// as they are (323 us with 256, 410 with 128).
+inline int bwd_batch(int tile, int n_feat, bool params, int total_tiles, int lds_batch, int lds_batch_bwd) {
     if (lds_batch_bwd != 0) return lds_batch_bwd;
-    const int most = tile == 8 ? 64 : (tile == 16 && (params ? n_feat >= 16 : n_feat == 16) ? 128 : 256);
+    int most = 256;
+    if (tile == 8) most = 64;
+    else if (tile == 16 && n_feat == 16) most = 128;
+    else if (tile == 16 && n_feat > 16 && params) most = total_tiles > 4096 ? 64 : 128;
     return lds_batch < most ? lds_batch : most;
 }
 

@@ -1,0 +1,118 @@
+"""Binning, bit for bit against the oracle, where its kernels change their
+way: list lengths around the limits of the per-tile sort (one wavefront up to
+512 keys, one workgroup up to 4096, parts that are merged beyond), chunk
+counts on both sides of the look-back, chunks of 1024, 4096 and 16384 pairs
+and several passes, tiles counted in more than one window, a table that does
+not fit and falls back to larger chunks, 32-bit counters or the tile ranges,
+a capacity that cuts the lists, and replays of a captured call."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_common import oracle_cfg
+from paper_2603_27781_amd import workloads as wl
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _views(sizes, f=0.8, seed=0):
+    rng = np.random.default_rng(seed)
+    return [wl.make_view(w, h, f * max(w, h), wl.se3_exp(wl._random_twist(rng, 0.03, 0.03))) for w, h in sizes]
+
+
+def _scene(n, seed, log_scale=-3.5, spread=1.0):
+    sc = wl.box_scene(np.random.default_rng(seed), n, (-spread, -0.6 * spread, 1.5), (spread, 0.6 * spread, 4), log_scale,
+                      0.4, 0)
+    sc.mu[2, ::7] = sc.mu[2, 0]  # equal depths under the identity rotation: index order decides
+    return sc
+
+
+def _bin(sc, views, tile=16, capacity=None):
+    from paper_2603_27781_amd import raster
+    cfg = raster.Config(tile=tile)
+    g = raster.Gaussians.from_numpy(sc)
+    r = raster.Rasterizer(sc.n, 0, raster.Views(views, tile), cfg, capacity=capacity)
+    if capacity is None:
+        r.ensure_capacity(g)
+        r.clear_trouble()
+    r.project(g)
+    r.bin_sort()
+    return r, g, oracle.bin_instances(sc, views, oracle_cfg(cfg))
+
+
+def _check(r, ref, touched):
+    inst, nvis, over, gave_up = r.instance_counts()
+    assert not over and not gave_up and not r.trouble()
+    assert inst == ref["count"] and nvis == int((touched > 0).sum())
+    assert np.array_equal(r.ranges.view(-1, 2).cpu().numpy(), ref["ranges"])
+    assert np.array_equal(r.keys[:inst].cpu().numpy().view(np.uint32), ref["keys"])
+    assert np.array_equal(r.sorted_gids(inst).cpu().numpy(), ref["gids"])
+    first, t = r.pair_first.cpu().numpy().astype(np.int64), touched.reshape(-1).astype(np.int64)
+    vis = np.nonzero(t)[0]
+    assert np.array_equal(first[vis], (np.cumsum(t) - t)[vis])  # pairs in order, none skipped
+
+
+@pytest.mark.parametrize("n", [1, 63, 512, 513, 1100, 4096, 4097, 9000, 20000])
+def test_list_lengths(n):
+    """One tile that every Gaussian reaches (and three that most reach)."""
+    sc = _scene(n, n, log_scale=-1.0, spread=0.3)
+    sc.mu[2] = np.maximum(sc.mu[2], 1.0)
+    views = [wl.make_view(20, 20, 24.0, np.eye(4))]
+    r, g, ref = _bin(sc, views)
+    if n >= 512:
+        assert int((ref["ranges"][:, 1] - ref["ranges"][:, 0]).max()) > 0.9 * n
+    _check(r, ref, ref["dec"]["touched"])
+
+
+@pytest.mark.parametrize("sizes,n,tile", [
+    ([(120, 90)], 131072, 16),                              # 128 chunks: the last size by look-back
+    ([(120, 90)], 131073, 16),                              # 129
+    ([(200, 150)], 300001, 16),                             # 4096 pairs a chunk
+    ([(64, 48), (130, 70), (17, 200)] * 4, 200003, 16),     # 16384 a chunk, uneven views
+    ([(64, 48)] * 16, 1300001, 16),                         # several passes a chunk
+    ([(1300, 900)], 3000, 8),                               # 18,419 tiles in one window
+    ([(1500, 1500)], 3000, 8),                              # 35,344 tiles: two windows
+    ([(1, 1), (9, 8), (8, 9)], 700, 8),
+], ids=lambda x: str(x) if not isinstance(x, list) else "x".join(map(str, x[0])) + "*%d" % len(x))
+def test_chunks_and_windows(sizes, n, tile):
+    r, g, ref = _bin(_scene(n, 5), _views(sizes), tile)
+    _check(r, ref, ref["dec"]["touched"])
+
+
+@pytest.mark.parametrize("side,n", [(5000, 200000), (8200, 30000)], ids=["32-bit counters", "table in the ranges"])
+def test_more_tiles_than_the_table_holds(side, n):
+    r, g, ref = _bin(_scene(n, 6, log_scale=-5.0), [wl.make_view(side, side, 0.8 * side, np.eye(4))], 8)
+    _check(r, ref, ref["dec"]["touched"])
+
+
+def test_truncated_lists_hold_the_first_instances():
+    sc, views = _scene(5000, 7), _views([(160, 120)])
+    full, _, ref = _bin(sc, views)
+    cap = ref["count"] // 2 + 7
+    r, _, _ = _bin(sc, views, capacity=cap)
+    inst, _, over, _ = r.instance_counts()
+    assert inst == ref["count"] and over and r.trouble()
+    keys, e = full.keys[:inst].cpu().numpy(), full.inst[:inst].cpu().numpy()
+    keep = e < cap
+    assert np.array_equal(r.inst[:cap].cpu().numpy(), e[keep])
+    assert np.array_equal(r.keys[:cap].cpu().numpy(), keys[keep])
+    n = r.ranges.view(-1, 2).cpu().numpy()
+    assert np.array_equal(n[:, 1] - n[:, 0], np.bincount(keys[keep], minlength=len(n)))
+
+
+def test_replays_of_a_captured_call_follow_the_scene():
+    sc, views = _scene(9000, 8, log_scale=-2.0), _views([(90, 70), (40, 60)])
+    r, g, ref = _bin(sc, views, capacity=2_000_000)
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        r.project(g)
+        r.bin_sort()
+    for k in range(3):
+        sc.mu[2] += 0.2 * k
+        g.mu.copy_(torch.from_numpy(sc.mu))
+        graph.replay()
+        ref = oracle.bin_instances(sc, views, oracle_cfg(r.cfg))
+        _check(r, ref, ref["dec"]["touched"])
+        torch.ones(1000, device="cuda").sum().item()  # eager work between the replays
