@@ -23,10 +23,7 @@ constexpr int kLossThreads = 256;
 constexpr int kLossKC = 64;  // most classes whose logits are kept in registers (32 or 64 variants)
 
 __global__ void k_transpose_decoder(const float* __restrict__ W, int F, int K, float* __restrict__ Wt) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= F * K) return;
-    const int f = i / K, k = i - f * K;
-    Wt[k * F + f] = W[i];
+    transpose_decoder(W, F, K, Wt, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 __global__ void __launch_bounds__(kSumThreads) k_sum_stage(const double* __restrict__ src, int n, int terms,
@@ -118,28 +115,18 @@ __global__ void __launch_bounds__(kLossThreads) k_loss(const float* __restrict__
     }
 }
 
-// Last stage of the fixed-order sum: stage holds the first-stage sums,
-// term-major [3][nst]; loss = (colour, depth, semantic, total).  One block,
-// wavefront shuffles, every sum in a fixed order.
-__global__ void __launch_bounds__(kSumThreads) k_loss_final(const double* __restrict__ stage, int nst,
-                                                            double* __restrict__ loss) {
-    __shared__ double s[3][kSumThreads / kWave];
-    const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
-    double a[3] = {0.0, 0.0, 0.0};
-    for (int i = t; i < nst; i += kSumThreads)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) a[k] += stage[(size_t)k * nst + i];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        for (int d = kWave / 2; d > 0; d >>= 1) a[k] += __shfl_xor(a[k], d, kWave);
-        if (lane == 0) s[k][wave] = a[k];
-    }
+// Last stage of the fixed-order sum of the term-major partials [3][n]: loss =
+// (colour, depth, semantic, total).
+__global__ void __launch_bounds__(kSumLast) k_loss_final(const double* __restrict__ src, int n,
+                                                         double* __restrict__ loss) {
+    __shared__ double s[3][kSumLast / kWave];
+    sum_last<3>(src, n, s);
     __syncthreads();
-    if (t == 0) {
+    if (threadIdx.x == 0) {
         double r[3];
+#pragma unroll
         for (int k = 0; k < 3; ++k) {
-            r[k] = 0.0;
-            for (int w = 0; w < kSumThreads / kWave; ++w) r[k] += s[k][w];
+            r[k] = sum_last_total(s[k]);
             loss[k] = r[k];
         }
         loss[3] = (r[0] + r[1]) + r[2];
@@ -152,9 +139,13 @@ hipError_t launch_transpose_decoder(const float* W, int F, int K, float* Wt, hip
 }
 
 hipError_t launch_loss_sums(const double* partials, int n, double* stage, double* loss, hipStream_t s) {
-    const int nst = sum_stage_blocks(n);
-    hipLaunchKernelGGL(k_sum_stage, dim3((unsigned)nst), dim3(kSumThreads), 0, s, partials, n, 3, stage);
-    hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(kSumThreads), 0, s, stage, nst, loss);
+    if (n > kSumOne) {
+        const int nst = sum_stage_blocks(n);
+        hipLaunchKernelGGL(k_sum_stage, dim3((unsigned)nst), dim3(kSumThreads), 0, s, partials, n, 3, stage);
+        partials = stage;
+        n = nst;
+    }
+    hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(kSumLast), 0, s, partials, n, loss);
     return hipGetLastError();
 }
 
@@ -191,10 +182,7 @@ hipError_t launch_loss_t(const float* out, const float* rgb_t, const float* dept
         hipLaunchKernelGGL((k_loss<F, 32>), dim3((unsigned)nblk), dim3(kLossThreads), 0, s, out, P, rgb_t, depth_t,
                            labels, Wt, K, w[0], w[1], w[2], views, n_views, grad_out, partials);
     double* stage = partials + ((size_t)nblk * 3 * sizeof(double) + 255) / 256 * 256 / sizeof(double);
-    const int nst = sum_stage_blocks(nblk);
-    hipLaunchKernelGGL(k_sum_stage, dim3((unsigned)nst), dim3(kSumThreads), 0, s, partials, nblk, 3, stage);
-    hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(kSumThreads), 0, s, stage, nst, loss);
-    return hipGetLastError();
+    return launch_loss_sums(partials, nblk, stage, loss, s);
 }
 
 hipError_t launch_loss(const float* out, int n_feat, const float* rgb_t, const float* depth_t, const int32_t* labels,

@@ -8,6 +8,12 @@ namespace sgs {
 
 // Copies the decoder W [F][K] (row-major) transposed into Wt [K][F], so that
 // a class row is contiguous for the per-pixel kernels.
+__device__ __forceinline__ void transpose_decoder(const float* __restrict__ W, int F, int K, float* __restrict__ Wt,
+                                                  int i) {
+    if (i >= F * K) return;
+    const int f = i / K, k = i - f * K;
+    Wt[k * F + f] = W[i];
+}
 __global__ void k_transpose_decoder(const float* __restrict__ W, int F, int K, float* __restrict__ Wt);
 
 // Fixed-order sums of per-block partials, first stage over many workgroups:
@@ -18,6 +24,44 @@ __global__ void k_transpose_decoder(const float* __restrict__ W, int F, int K, f
 constexpr int kSumThreads = 256, kSumPer = 16, kSumChunk = kSumThreads * kSumPer;
 __global__ void k_sum_stage(const double* __restrict__ src, int n, int terms, double* __restrict__ dst);
 inline int sum_stage_blocks(int64_t n) { return (int)((n + kSumChunk - 1) / kSumChunk); }
+
+// Last stage: one block, `terms` term-major arrays src[term][n] in a fixed
+// order.  Up to kSumOne partials (a 1920x1080 frame at one per 256 pixels)
+// come here directly: one launch, 5 us, instead of two of 5.
+constexpr int kSumLast = 1024, kSumUnroll = 8, kSumOne = kSumLast * kSumUnroll;
+// Sum over i of src[term][i] for each term, in s[term][wavefront] partial
+// sums; the block's thread 0 adds them up (sum_last_total) after a barrier.
+template <int TERMS>
+__device__ __forceinline__ void sum_last(const double* __restrict__ src, int n, double (*s)[kSumLast / kWave]) {
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    double a[TERMS];
+#pragma unroll
+    for (int k = 0; k < TERMS; ++k) a[k] = 0.0;
+    for (int i0 = tid; i0 < n; i0 += kSumOne) {
+        double x[TERMS][kSumUnroll];
+#pragma unroll
+        for (int u = 0; u < kSumUnroll; ++u) {
+            const int i = i0 + u * kSumLast;
+#pragma unroll
+            for (int k = 0; k < TERMS; ++k) x[k][u] = src[(size_t)k * n + (i < n ? i : n - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < kSumUnroll; ++u)
+#pragma unroll
+            for (int k = 0; k < TERMS; ++k) a[k] += i0 + u * kSumLast < n ? x[k][u] : 0.0;
+    }
+#pragma unroll
+    for (int k = 0; k < TERMS; ++k) {
+        for (int d = kWave / 2; d > 0; d >>= 1) a[k] += __shfl_xor(a[k], d, kWave);
+        if (lane == 0) s[k][wave] = a[k];
+    }
+}
+__device__ __forceinline__ double sum_last_total(const double (&s)[kSumLast / kWave]) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < kSumLast / kWave; ++w) t += s[w];
+    return t;
+}
 
 // Cross-entropy of softmax(W^T f + b) (b optional) against `lab` for one pixel (the fixed
 // linear decoder standing in for F_cnn, Sec. 3.2.2, Eq. 8) and its gradient

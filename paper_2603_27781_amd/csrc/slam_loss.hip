@@ -4,10 +4,10 @@
 //   1. median depth error per view: the lower median of the binary32
 //      residuals r = |D - D*| over the pixels with D* > 0, found exactly by
 //      a radix select over the residual bits (non-negative floats order as
-//      their bit patterns): four passes of 8 bits, each a histogram of the
-//      digit among the residuals that match the prefix selected so far
-//      (k_median_hist), then one block per view that locates the bucket
-//      holding the wanted rank (k_median_select).  Integer counts only, so
+//      their bit patterns): three passes of 11, 10 and 10 bits, each a
+//      histogram of the digit among the residuals that match the prefix
+//      selected so far (k_median).  Every block of the next pass locates the
+//      bucket holding the wanted rank for itself.  Integer counts only, so
 //      the result is the same every run.
 //   2. one thread per pixel (k_slam_loss): the masks M_obs (Eq. 21) and
 //      M_unobs (Eq. 11) from binary32 tests, then the L1
@@ -62,29 +62,99 @@ __device__ __forceinline__ int view_of_pixel(const gs_view* views, int n_views, 
 // ---------------------------------------------------------------------------
 // 1. median depth error
 // ---------------------------------------------------------------------------
-// sel[4 v + 0..2]: selected prefix, rank still wanted within it, number of
-// valid pixels of the view.
+// Digits of the passes, from the top of the 31 bits of a residual.
 template <int PASS>
-__global__ void __launch_bounds__(kSlamThreads) k_median_hist(const float* __restrict__ depth,
-                                                              const float* __restrict__ depth_t,
-                                                              const gs_view* __restrict__ views,
-                                                              uint32_t* __restrict__ hist,
-                                                              const uint32_t* __restrict__ sel) {
-    constexpr int shift = 24 - 8 * PASS;
-    __shared__ uint32_t h[256];
+struct MedDigit {
+    static constexpr int bits = PASS == 0 ? 11 : 10;
+    static constexpr int shift = PASS == 0 ? 20 : (PASS == 1 ? 10 : 0);
+    static constexpr int bins = 1 << bits;
+    static constexpr int first = PASS == 0 ? 0 : (PASS == 1 ? 2048 : 3072);  // of the view's histogram words
+};
+constexpr int kMedWords = 2048 + 2 * 1024;
+
+// Per view, after the selection of a pass: the prefix selected so far, the
+// rank still wanted within it, the number of valid pixels.
+struct MedSel {
+    uint32_t prefix, rank, count, pad;
+};
+
+// Clears the histograms and transposes the decoder.
+__global__ void __launch_bounds__(256) k_slam_prep(uint32_t* __restrict__ words, int n, const float* __restrict__ W,
+                                                   int F, int K, float* __restrict__ Wt) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) words[i] = 0;
+    if (W != nullptr) transpose_decoder(W, F, K, Wt, i);
+}
+
+// Lanes of the wavefront with the same `bits`-bit digit among the valid ones.
+template <int BITS>
+__device__ __forceinline__ uint64_t match_bits(uint32_t d, bool valid) {
+    uint64_t m = __builtin_amdgcn_ballot_w64(valid);
+#pragma unroll
+    for (int b = 0; b < BITS; ++b) {
+        const bool bit = (d >> b) & 1u;
+        const uint64_t bb = __builtin_amdgcn_ballot_w64(bit);
+        m &= bit ? bb : ~bb;
+    }
+    return m;
+}
+
+// Selection after pass PASS, by a whole block: the bin of its histogram that
+// holds the wanted rank.  Returns the selection after it (all threads).
+template <int PASS>
+__device__ __forceinline__ MedSel median_select(const uint32_t* __restrict__ hist, const MedSel* __restrict__ sel,
+                                                int v, uint32_t* s_tmp, MedSel* s_sel) {
+    using D = MedDigit<PASS>;
+    constexpr int PER = D::bins / kSlamThreads;
+    const int tid = threadIdx.x;
+    const uint32_t* hv = hist + (size_t)v * kMedWords + D::first + tid * PER;
+    uint32_t c[PER], sum = 0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        c[q] = hv[q];
+        sum += c[q];
+    }
+    MedSel m = {0, 0, 0, 0};
+    if constexpr (PASS > 0) m = sel[2 * v + PASS - 1];
+    uint32_t total;
+    uint32_t excl = block_exclusive<kSlamThreads>(sum, s_tmp, &total);
+    if constexpr (PASS == 0) {
+        m.count = total;
+        m.rank = total > 0 ? (total - 1) / 2 : 0;
+    }
+    if (tid == 0) *s_sel = m;  // of a view without a valid depth
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        if (m.count > 0 && excl <= m.rank && m.rank < excl + c[q])  // exactly one thread and bin
+            *s_sel = {(m.prefix << D::bits) | (uint32_t)(tid * PER + q), m.rank - excl, m.count, 0};
+        excl += c[q];
+    }
+    __syncthreads();
+    return *s_sel;
+}
+
+// One pass over one view (blockIdx.y).  Bound by latency: a block streams
+// 32 KB and waits for it once, while it selects the previous pass's bucket.
+// (Four 8-bit passes with a selection launch after each were 9 launches,
+// 52 us for one 1200x680 view, 31 in 5 now; eight views 88 and 69.  The view's last block
+// doing the selection instead, behind a device-wide fence in every block,
+// made a pass 18 us there and 140 us at eight views: each fence writes an L2
+// back.)
+template <int PASS>
+__global__ void __launch_bounds__(kSlamThreads) k_median(const float* __restrict__ depth,
+                                                         const float* __restrict__ depth_t,
+                                                         const gs_view* __restrict__ views,
+                                                         uint32_t* __restrict__ hist, MedSel* __restrict__ sel) {
+    using D = MedDigit<PASS>;
+    __shared__ uint32_t h[D::bins];
+    __shared__ uint32_t s_tmp[kSlamThreads / kWave];
+    __shared__ MedSel s_sel;
     const int v = blockIdx.y, tid = threadIdx.x, lane = tid & (kWave - 1);
     const int64_t off = views[v].pixel_offset;
     const int64_t Pv = (int64_t)views[v].width * views[v].height;
     const int64_t b0 = (int64_t)blockIdx.x * kMedChunk;
     if (b0 >= Pv) return;  // uniform over the block
-    uint32_t prefix = 0;
-    if constexpr (PASS > 0) {
-        if (sel[4 * v + 2] == 0) return;  // no valid pixel in the view
-        prefix = sel[4 * v];
-    }
-    h[tid] = 0;
-    __syncthreads();
-    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
     // every load first (index clamped into the view), then the decisions
     float dtv[kMedItems], dv[kMedItems];
 #pragma unroll
@@ -94,56 +164,52 @@ __global__ void __launch_bounds__(kSlamThreads) k_median_hist(const float* __res
         dtv[k] = depth_t[off + jc];
         dv[k] = depth[off + jc];
     }
+    for (int i = tid; i < D::bins; i += kSlamThreads) h[i] = 0;
+    uint32_t prefix = 0;
+    if constexpr (PASS > 0) {
+        const MedSel m = median_select<PASS - 1>(hist, sel, v, s_tmp, &s_sel);
+        if (blockIdx.x == 0 && tid == 0) sel[2 * v + PASS - 1] = m;  // for the next launch
+        if (m.count == 0) return;  // uniform: no valid pixel in the view
+        prefix = m.prefix;
+    } else {
+        __syncthreads();
+    }
+    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
 #pragma unroll
     for (int k = 0; k < kMedItems; ++k) {
         const int64_t j = b0 + k * kSlamThreads + tid;
         const uint32_t u = __float_as_uint(fabsf(dv[k] - dtv[k]));
         bool ok = j < Pv && dtv[k] > 0.0f;
-        if constexpr (PASS > 0) ok = ok && (u >> (shift + 8)) == prefix;
-        const uint32_t d = (u >> shift) & 0xffu;
-        if (__builtin_amdgcn_ballot_w64(ok) == 0) continue;  // uniform
-        // one LDS add per distinct digit of the wavefront (the residuals of
-        // a view mostly share a few top digits)
-        const uint64_t peers = match_digit(d, ok);
-        if (ok && (peers & below) == 0) atomicAdd(&h[d], (uint32_t)__popcll(peers));
+        if constexpr (PASS > 0) ok = ok && (u >> (D::shift + D::bits)) == prefix;
+        const uint32_t d = (u >> D::shift) & (uint32_t)(D::bins - 1);
+        if constexpr (PASS == 0) {
+            // one LDS add per distinct digit of the wavefront (the residuals
+            // of a view mostly share a few top digits; the lower ones differ)
+            const uint64_t peers = match_bits<D::bits>(d, ok);
+            if (ok && (peers & below) == 0) atomicAdd(&h[d], (uint32_t)__popcll(peers));
+        } else {
+            if (ok) atomicAdd(&h[d], 1u);
+        }
     }
     __syncthreads();
-    if (h[tid] != 0) atomicAdd(&hist[256 * v + tid], h[tid]);
+    uint32_t* hv = hist + (size_t)v * kMedWords + D::first;
+    for (int i = tid; i < D::bins; i += kSlamThreads)
+        if (h[i] != 0) atomicAdd(&hv[i], h[i]);
 }
 
-template <int PASS>
-__global__ void __launch_bounds__(256) k_median_select(uint32_t* __restrict__ hist, uint32_t* __restrict__ sel,
-                                                      float* __restrict__ med_ws, float* __restrict__ med_out) {
-    __shared__ uint32_t s_tmp[256 / kWave];
-    const int v = blockIdx.x, tid = threadIdx.x;
-    const uint32_t c = hist[256 * v + tid];
-    hist[256 * v + tid] = 0;  // cleared for the next pass (or the next call)
-    uint32_t total;
-    const uint32_t excl = block_exclusive<256>(c, s_tmp, &total);
-    uint32_t prefix = 0, rank, count;
-    if constexpr (PASS == 0) {
-        count = total;
-        rank = count > 0 ? (count - 1) / 2 : 0;
-    } else {
-        prefix = sel[4 * v];
-        rank = sel[4 * v + 1];
-        count = sel[4 * v + 2];
-    }
-    __syncthreads();  // every thread has read sel before one of them rewrites it
-    const bool mine = count > 0 && excl <= rank && rank < excl + c;  // exactly one thread when count > 0
-    if (mine) {
-        sel[4 * v] = (prefix << 8) | (uint32_t)tid;
-        sel[4 * v + 1] = rank - excl;
-    }
-    if (PASS == 0 && tid == 0) sel[4 * v + 2] = count;
-    if constexpr (PASS == 3) {
-        // the selected residual (whatever its bits), or 0 for a view without
-        // a valid depth
-        if (mine || (count == 0 && tid == 0)) {
-            const float m = mine ? __uint_as_float((prefix << 8) | (uint32_t)tid) : 0.0f;
-            med_ws[v] = m;
-            if (med_out != nullptr) med_out[v] = m;
-        }
+__global__ void __launch_bounds__(kSlamThreads) k_median_final(const uint32_t* __restrict__ hist,
+                                                               const MedSel* __restrict__ sel,
+                                                               float* __restrict__ med_ws,
+                                                               float* __restrict__ med_out) {
+    __shared__ uint32_t s_tmp[kSlamThreads / kWave];
+    __shared__ MedSel s_sel;
+    const int v = blockIdx.x;
+    const MedSel m = median_select<2>(hist, sel, v, s_tmp, &s_sel);
+    if (threadIdx.x == 0) {
+        // the selected residual, whatever its bits; 0 without a valid depth
+        const float r = m.count > 0 ? __uint_as_float(m.prefix) : 0.0f;
+        med_ws[v] = r;
+        if (med_out != nullptr) med_out[v] = r;
     }
 }
 
@@ -792,34 +858,20 @@ __global__ void __launch_bounds__(kSlamThreads) k_ssim_bwd(const float* __restri
 // ---------------------------------------------------------------------------
 // 4. fixed-order sum: loss = (colour L1, SSIM, depth, semantic, total)
 // ---------------------------------------------------------------------------
-// stage: the first-stage sums of the pixel kernel's (colour, depth,
-// semantic) partials, term-major [3][nst]; ssim: the SSIM kernel's per-block
+// src: the pixel kernel's (colour, depth, semantic) partials, or their
+// first-stage sums, term-major [3][n]; ssim: the SSIM kernel's per-block
 // partials.  One block; every sum in a fixed order.
-__global__ void __launch_bounds__(kSumThreads) k_slam_loss_final(const double* __restrict__ stage, int nst,
-                                                                 const double* __restrict__ ssim, int nssim,
-                                                                 double* __restrict__ loss) {
-    __shared__ double s[4][kSumThreads / kWave];
-    const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
-    double a[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int i = t; i < nst; i += kSumThreads) {
-        a[0] += stage[i];
-        a[2] += stage[nst + i];
-        a[3] += stage[2 * (size_t)nst + i];
-    }
-    for (int i = t; i < nssim; i += kSumThreads) a[1] += ssim[i];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        for (int d = kWave / 2; d > 0; d >>= 1) a[k] += __shfl_xor(a[k], d, kWave);
-        if (lane == 0) s[k][wave] = a[k];
-    }
+__global__ void __launch_bounds__(kSumLast) k_slam_loss_final(const double* __restrict__ src, int n,
+                                                              const double* __restrict__ ssim, int nssim,
+                                                              double* __restrict__ loss) {
+    __shared__ double s[4][kSumLast / kWave];
+    sum_last<3>(src, n, s);
+    sum_last<1>(ssim, nssim, s + 3);
     __syncthreads();
-    if (t == 0) {
-        double r[4];
-        for (int k = 0; k < 4; ++k) {
-            r[k] = 0.0;
-            for (int w = 0; w < kSumThreads / kWave; ++w) r[k] += s[k][w];
-            loss[k] = r[k];
-        }
+    if (threadIdx.x == 0) {
+        const double r[4] = {sum_last_total(s[0]), sum_last_total(s[3]), sum_last_total(s[1]), sum_last_total(s[2])};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) loss[k] = r[k];
         loss[4] = ((r[0] + r[1]) + r[2]) + r[3];
     }
 }
@@ -860,9 +912,9 @@ SlamWs slam_layout(int64_t P, const gs_view* views, int n_views, bool ssim, int 
     SlamWs L;
     size_t o = 0;
     L.hist = o;
-    o += align256((size_t)n_views * 256 * 4);
+    o += (size_t)n_views * kMedWords * 4;  // a multiple of 256
     L.sel = o;
-    o += align256((size_t)n_views * 4 * 4);
+    o += align256((size_t)n_views * 2 * sizeof(MedSel));
     L.med = o;
     o += align256((size_t)n_views * 4);
     const int64_t nblk = slam_blocks(P);
@@ -989,7 +1041,7 @@ hipError_t launch_slam_t(const float* out, const float* rgb_t, const float* dept
     const int dterms = dec_terms_of(F, dec);
     const SlamWs L = slam_layout(P, views_host, n_views, ssim, dterms);
     uint32_t* hist = reinterpret_cast<uint32_t*>(ws + L.hist);
-    uint32_t* sel = reinterpret_cast<uint32_t*>(ws + L.sel);
+    MedSel* sel = reinterpret_cast<MedSel*>(ws + L.sel);
     float* med = reinterpret_cast<float*>(ws + L.med);
     double* part = reinterpret_cast<double*>(ws + L.part);
     double* spart = reinterpret_cast<double*>(ws + L.spart);
@@ -1000,8 +1052,12 @@ hipError_t launch_slam_t(const float* out, const float* rgb_t, const float* dept
     double* dstage = reinterpret_cast<double*>(ws + L.dstage);
 
     // 1. median depth error per view
-    hipError_t e = fill_u32(hist, 0u, (int64_t)n_views * (256 + 4), s);  // hist and sel are adjacent
-    if (e != hipSuccess) return e;
+    const int K = dec != nullptr ? dec->n_classes : 0;
+    const bool sem = F > 0 && K > 0 && o.w_sem != 0.0f;
+    const int words = n_views * kMedWords;
+    const int prep = sem && F * K > words ? F * K : words;
+    hipLaunchKernelGGL(k_slam_prep, dim3((unsigned)ceil_div(prep, 256)), dim3(256), 0, s, hist, words,
+                       sem ? dec->weight : nullptr, F, K, Wt);
     int64_t pmax = 0;
     for (int v = 0; v < n_views; ++v) {
         const int64_t pv = (int64_t)views_host[v].width * views_host[v].height;
@@ -1009,14 +1065,10 @@ hipError_t launch_slam_t(const float* out, const float* rgb_t, const float* dept
     }
     const dim3 hg((unsigned)((pmax + kMedChunk - 1) / kMedChunk), (unsigned)n_views);
     const float* dep = out + 3 * P;
-    hipLaunchKernelGGL(k_median_hist<0>, hg, dim3(kSlamThreads), 0, s, dep, depth_t, views_dev, hist, sel);
-    hipLaunchKernelGGL(k_median_select<0>, dim3(n_views), dim3(256), 0, s, hist, sel, med, median);
-    hipLaunchKernelGGL(k_median_hist<1>, hg, dim3(kSlamThreads), 0, s, dep, depth_t, views_dev, hist, sel);
-    hipLaunchKernelGGL(k_median_select<1>, dim3(n_views), dim3(256), 0, s, hist, sel, med, median);
-    hipLaunchKernelGGL(k_median_hist<2>, hg, dim3(kSlamThreads), 0, s, dep, depth_t, views_dev, hist, sel);
-    hipLaunchKernelGGL(k_median_select<2>, dim3(n_views), dim3(256), 0, s, hist, sel, med, median);
-    hipLaunchKernelGGL(k_median_hist<3>, hg, dim3(kSlamThreads), 0, s, dep, depth_t, views_dev, hist, sel);
-    hipLaunchKernelGGL(k_median_select<3>, dim3(n_views), dim3(256), 0, s, hist, sel, med, median);
+    hipLaunchKernelGGL(k_median<0>, hg, dim3(kSlamThreads), 0, s, dep, depth_t, views_dev, hist, sel);
+    hipLaunchKernelGGL(k_median<1>, hg, dim3(kSlamThreads), 0, s, dep, depth_t, views_dev, hist, sel);
+    hipLaunchKernelGGL(k_median<2>, hg, dim3(kSlamThreads), 0, s, dep, depth_t, views_dev, hist, sel);
+    hipLaunchKernelGGL(k_median_final, dim3(n_views), dim3(kSlamThreads), 0, s, hist, sel, med, median);
 
     // 2. masks, L1 and the semantic term (with the decoder gradients' block partials)
     SlamParams sp;
@@ -1030,11 +1082,6 @@ hipError_t launch_slam_t(const float* out, const float* rgb_t, const float* dept
     sp.unobs_factor = o.unobs_factor;
     sp.use_obs = (o.flags & GS_LOSS_OBS_MASK) != 0;
     sp.bce = (o.flags & GS_LOSS_BCE) != 0;
-    const int K = dec != nullptr ? dec->n_classes : 0;
-    const bool sem = F > 0 && K > 0 && sp.w2 != 0.0f;
-    if (sem)
-        hipLaunchKernelGGL(k_transpose_decoder, dim3((unsigned)ceil_div(F * K, 256)), dim3(256), 0, s, dec->weight,
-                           F, K, Wt);
     const unsigned nblk = slam_blocks(P);
     const int Ke = sem ? K : 0;
     const float* bias = sem ? dec->bias : nullptr;
@@ -1048,7 +1095,7 @@ hipError_t launch_slam_t(const float* out, const float* rgb_t, const float* dept
     if (dterms > 0) {
         // dL/dW and dL/db (zero when the semantic term is off)
         if (!sem) {
-            e = fill_u32(reinterpret_cast<uint32_t*>(dpart), 0u, (int64_t)nblk * dterms, s);
+            const hipError_t e = fill_u32(reinterpret_cast<uint32_t*>(dpart), 0u, (int64_t)nblk * dterms, s);
             if (e != hipSuccess) return e;
         }
         const int nch = row_chunks(nblk);
@@ -1085,11 +1132,17 @@ hipError_t launch_slam_t(const float* out, const float* rgb_t, const float* dept
         }
         nssim = nt > 0 ? (int)gf : 0;
     }
-    // 4. loss terms: the per-block partials summed in two fixed-order stages
-    double* stage = reinterpret_cast<double*>(ws + L.stage);
-    const int nst = sum_stage_blocks(nblk);
-    hipLaunchKernelGGL(k_sum_stage, dim3((unsigned)nst), dim3(kSumThreads), 0, s, part, (int)nblk, 3, stage);
-    hipLaunchKernelGGL(k_slam_loss_final, dim3(1), dim3(kSumThreads), 0, s, stage, nst, spart, nssim, loss);
+    // 4. loss terms: the per-block partials summed in a fixed order, in two
+    // stages where there are many
+    const double* src = part;
+    int nsrc = (int)nblk;
+    if (nsrc > kSumOne) {
+        double* stage = reinterpret_cast<double*>(ws + L.stage);
+        nsrc = sum_stage_blocks(nblk);
+        hipLaunchKernelGGL(k_sum_stage, dim3((unsigned)nsrc), dim3(kSumThreads), 0, s, part, (int)nblk, 3, stage);
+        src = stage;
+    }
+    hipLaunchKernelGGL(k_slam_loss_final, dim3(1), dim3(kSumLast), 0, s, src, nsrc, spart, nssim, loss);
     return hipGetLastError();
 }
 
