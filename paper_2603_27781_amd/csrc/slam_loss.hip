@@ -12,7 +12,8 @@
 //   2. one thread per pixel (k_slam_loss): the masks M_obs (Eq. 21) and
 //      M_unobs (Eq. 11) from binary32 tests, then the L1
 //      colour and depth terms and the semantic cross-entropy, each weighted
-//      by M_obs when the tracking mask is on, with their gradients.
+//      by M_obs when the tracking mask is on, with their gradients.  With the
+//      decoder's own gradients, k_slam_loss_dec.
 //   3. with lambda > 0, the SSIM part of Eq. (15)'s colour term: per colour
 //      channel and 64x16 output tile, k_ssim_fwd filters x, y, x^2, y^2 and
 //      xy with the separable 11-tap Gaussian (sigma 1.5) over the tile plus
@@ -53,9 +54,14 @@ struct SsimTiles {
     int n_views;
 };
 
-__device__ __forceinline__ int view_of_pixel(const gs_view* views, int n_views, int64_t p) {
+// View of pixel p of a workgroup whose pixels are consecutive, p0 (uniform) the
+// first of them: found once, with scalar loads, where they are all of one
+// view.
+__device__ __forceinline__ int view_of_pixel(const gs_view* views, int n_views, int64_t p0, int64_t p) {
     int v = 0;
-    while (v + 1 < n_views && views[v + 1].pixel_offset <= p) ++v;
+    while (v + 1 < n_views && views[v + 1].pixel_offset <= p0) ++v;
+    if (v + 1 < n_views && views[v + 1].pixel_offset < p0 + kSlamThreads)  // uniform
+        while (v + 1 < n_views && views[v + 1].pixel_offset <= p) ++v;
     return v;
 }
 
@@ -78,12 +84,38 @@ struct MedSel {
     uint32_t prefix, rank, count, pad;
 };
 
-// Clears the histograms and transposes the decoder.
+// The transposed decoder [K][F], at most 64 rows of 32, then its bias.
+constexpr int kWtBias = 32 * GS_SLAM_MAX_CLASSES, kWtFloats = kWtBias + GS_SLAM_MAX_CLASSES;
+
+// Weight of each term per pixel of a view, in the precision it is applied in
+// (a division each, eleven of binary32 and thirty of FP64 instructions, which
+// every pixel would repeat).
+struct ViewWeights {
+    float gc, gd, gs, pad;  // gradients of the colour L1, depth and semantic term
+    double d, s;            // values of the depth and semantic term
+};
+
+// Clears the histograms, transposes the decoder and forms the views' weights.
 __global__ void __launch_bounds__(256) k_slam_prep(uint32_t* __restrict__ words, int n, const float* __restrict__ W,
-                                                   int F, int K, float* __restrict__ Wt) {
+                                                   const float* __restrict__ bias, int F, int K,
+                                                   float* __restrict__ Wt, const gs_view* __restrict__ views,
+                                                   int n_views, SlamParams sp, ViewWeights* __restrict__ vw) {
     const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n_views) {
+        const float Pv = (float)((int64_t)views[i].width * views[i].height);
+        vw[i] = {(1.0f - sp.lam) * sp.w0 / (3.0f * Pv), sp.w1 / Pv, sp.w2 / Pv, 0.0f,
+                 (double)sp.w1 / (double)Pv, (double)sp.w2 / (double)Pv};
+    }
     if (i < n) words[i] = 0;
-    if (W != nullptr) transpose_decoder(W, F, K, Wt, i);
+    if (W != nullptr) {
+        transpose_decoder(W, F, K, Wt, i);
+        // k_slam_loss_dec takes the classes four at a time: zero rows and a
+        // bias of -infinity up to a multiple of four, so that the classes
+        // that are not there have logit -infinity and probability 0
+        const int K4 = (K + 3) / 4 * 4;
+        if (i >= F * K && i < F * K4) Wt[i] = 0.0f;
+        if (i < K4) Wt[kWtBias + i] = i < K ? (bias != nullptr ? bias[i] : 0.0f) : -INFINITY;
+    }
 }
 
 // Lanes of the wavefront with the same `bits`-bit digit among the valid ones.
@@ -218,15 +250,15 @@ __global__ void __launch_bounds__(kSlamThreads) k_median_final(const uint32_t* _
 // ---------------------------------------------------------------------------
 // Semantic term of one pixel through the decoder z = W^T f + b (a 1x1
 // convolution standing in for F_cnn, Eq. 8), K <= KC classes, logits in
-// registers.  Returns the term and leaves dz = dterm/dz in z:
-//   CE:  -log p_lab,  dz = p - y;
-//   BCE (Eq. 16): -sum_k [y_k log p_k + (1 - y_k) log(1 - p_k)], each log
-//   clamped at -100 (no gradient through a clamped log); dz_j = p_j (dp_j -
-//   sum_k p_k dp_k) with dp_k the derivative in p_k.
-// A class row of Wt is wavefront-uniform: scalar loads feeding the FMAs.
+// registers: the BCE of Eq. (16), -sum_k [y_k log p_k + (1 - y_k) log(1 -
+// p_k)], each log clamped at -100 (no gradient through a clamped log).
+// Returns the term and leaves dz = dterm/dz in z: dz_j = p_j (dp_j - sum_k
+// p_k dp_k) with dp_k the derivative in p_k.  (The cross-entropy -log p_lab,
+// dz = p - y, is semantic_ce.)  A class row of Wt is wavefront-uniform:
+// scalar loads feeding the FMAs.
 template <int F, int KC>
 __device__ __forceinline__ float sem_dz(const float (&fv)[F], const float* __restrict__ Wt,
-                                        const float* __restrict__ bias, int K, int lab, bool bce, float (&z)[KC]) {
+                                        const float* __restrict__ bias, int K, int lab, float (&z)[KC]) {
     // z = W^T f + b, then in place z - max (the only per-class state kept,
     // so that the logits cost one register per class)
     float m = -INFINITY;
@@ -250,16 +282,7 @@ __device__ __forceinline__ float sem_dz(const float (&fv)[F], const float* __res
         }
     const float inv = 1.0f / se, lse = __logf(se);
     float L = 0.0f;
-    if (!bce) {
-#pragma unroll
-        for (int k = 0; k < KC; ++k)
-            if (k < K) {
-                if (k == lab) L = lse - z[k];
-                z[k] = __expf(z[k]) * inv - (k == lab ? 1.0f : 0.0f);  // dz
-            }
-        return L;
-    }
-    // BCE: p_k, log p_k = z_k - lse, log(1 - p_k) = log(se - e_k) - lse;
+    // p_k, log p_k = z_k - lse, log(1 - p_k) = log(se - e_k) - lse;
     // z keeps p_k and one bit per class whether the log that class's
     // gradient uses is above the clamp, so dp_k = -1/p_k (label) or
     // 1/(1 - p_k) (other classes, hardware reciprocals) is rebuilt in the
@@ -292,191 +315,63 @@ __device__ __forceinline__ float sem_dz(const float (&fv)[F], const float* __res
     return L;
 }
 
-// Decoder-gradient staging (dynamic LDS, only when the decoder gradients
-// are wanted): one slot per wavefront of 32 pixel rows, f [32][F] then the
-// scaled dz [32][K]; a wavefront stages and contracts its 64 pixels in two
-// halves, so the area is 4 * 32 * (F + K) floats (at most 48 KiB).
-constexpr int kDecRows = kWave / 2;
-inline size_t dec_lds_bytes(int F, int K) { return (size_t)4 * kDecRows * (F + K) * sizeof(float); }
+// The per-pixel terms without the semantic one: masks, L1 colour and depth
+// and their gradients.  Returns whether the pixel counts; terms not yet
+// divided by the pixels.
+struct PixelTerms {
+    double c, d;     // sums of |C - C*| and |D - D*|
+    ViewWeights w;
+};
+// The pixel is p0 + i, p0 uniform over the workgroup: the planes' addresses
+// are then scalar work.
+__device__ __forceinline__ bool pixel_terms(const float* __restrict__ out, int64_t P, int64_t p0, int i,
+                                            const float* __restrict__ rgb_t, const float* __restrict__ depth_t,
+                                            const SlamParams& sp, const float* __restrict__ med,
+                                            const ViewWeights* __restrict__ vws,
+                                            const gs_view* __restrict__ views, int n_views,
+                                            float* __restrict__ grad_out, uint8_t* __restrict__ masks,
+                                            PixelTerms& t) {
+    // every load first: one round trip to memory
+    float x[3], y[3];
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) {
+        x[ch] = (out + ch * P + p0)[i];
+        y[ch] = (rgb_t + ch * P + p0)[i];
+    }
+    const float d = (out + 3 * P + p0)[i], dt = (depth_t + p0)[i], o = (out + 4 * P + p0)[i];
+    const int v = view_of_pixel(views, n_views, p0, p0 + i);
+    t.w = vws[v];
+    t.c = t.d = 0.0;
+    // Eq. (21) / Eq. (11), binary32 tests
+    const float r = fabsf(d - dt), m = med[v];
+    const float lim_obs = sp.obs_factor * m, lim_unobs = sp.unobs_factor * m;
+    const bool obs = (o > sp.tau_obs) && (r < lim_obs);
+    const bool unobs = (o < sp.tau_unobs) || ((d > dt) && (r > lim_unobs));
+    (masks + p0)[i] = (uint8_t)((obs ? 1 : 0) | (unobs ? 2 : 0));
+    const bool on = !sp.use_obs || obs;
+    if (on) {
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) {
+            const float rc = x[ch] - y[ch];
+            t.c += (double)fabsf(rc);
+            (grad_out + ch * P + p0)[i] = rc > 0.0f ? t.w.gc : (rc < 0.0f ? -t.w.gc : 0.0f);
+        }
+        const float rd = d - dt;
+        t.d += (double)fabsf(rd);
+        (grad_out + 3 * P + p0)[i] = rd > 0.0f ? t.w.gd : (rd < 0.0f ? -t.w.gd : 0.0f);
+    } else {
+#pragma unroll
+        for (int ch = 0; ch < 4; ++ch) (grad_out + ch * P + p0)[i] = 0.0f;
+    }
+    (grad_out + 4 * P + p0)[i] = 0.0f;
+    return on;
+}
 
-// MODE: kSemCE the fused cross-entropy (no decoder gradients; fewest
-// registers), kSemDz the semantic term through dz (BCE), kSemDzDec the same
-// plus the decoder gradients.
-constexpr int kSemCE = 0, kSemDz = 1, kSemDzDec = 2;
-
-template <int F, int KC, int MODE>
-__global__ void __launch_bounds__(kSlamThreads) k_slam_loss(const float* __restrict__ out, int64_t P,
-                                                            const float* __restrict__ rgb_t,
-                                                            const float* __restrict__ depth_t,
-                                                            const int32_t* __restrict__ labels,
-                                                            const float* __restrict__ Wt,
-                                                            const float* __restrict__ bias, int K, SlamParams sp,
-                                                            const float* __restrict__ med,
-                                                            const gs_view* __restrict__ views, int n_views,
-                                                            float* __restrict__ grad_out,
-                                                            uint8_t* __restrict__ masks,
-                                                            double* __restrict__ partials,
-                                                            float* __restrict__ dec_partials) {
-    extern __shared__ float s_dyn[];
-    __shared__ double s_red[3][kSlamThreads / kWave];
-    __shared__ float s_db[kSlamThreads / kWave][KC > 0 ? KC : 1];  // per-wavefront bias sums
+// The workgroup's sums of the three terms into its partials (term-major).
+__device__ __forceinline__ void store_partials(double lc, double ld, double ls,
+                                               double (&s_red)[3][kSlamThreads / kWave],
+                                               double* __restrict__ partials) {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int64_t p = (int64_t)blockIdx.x * kSlamThreads + tid;
-    double lc = 0.0, ld = 0.0, ls = 0.0;
-    float fv[F > 0 ? F : 1], dz[KC > 0 ? KC : 1];
-    float dscale = 0.0f;  // w_sem / P_v * M(p) for the decoder gradients (0: no contribution)
-    if (p < P) {
-        double pc = 0.0, pd = 0.0, ps = 0.0;
-        const int v = view_of_pixel(views, n_views, p);
-        const float Pv = (float)((int64_t)views[v].width * views[v].height);
-        const float d = out[3 * P + p], dt = depth_t[p], o = out[4 * P + p];
-        // Eq. (21) / Eq. (11), binary32 tests
-        const float r = fabsf(d - dt), m = med[v];
-        const float lim_obs = sp.obs_factor * m, lim_unobs = sp.unobs_factor * m;
-        const bool obs = (o > sp.tau_obs) && (r < lim_obs);
-        const bool unobs = (o < sp.tau_unobs) || ((d > dt) && (r > lim_unobs));
-        masks[p] = (uint8_t)((obs ? 1 : 0) | (unobs ? 2 : 0));
-        const bool on = !sp.use_obs || obs;
-        const float gc = (1.0f - sp.lam) * sp.w0 / (3.0f * Pv), gd = sp.w1 / Pv, gs = sp.w2 / Pv;
-        if (on) {
-#pragma unroll
-            for (int ch = 0; ch < 3; ++ch) {
-                const float rc = out[ch * P + p] - rgb_t[ch * P + p];
-                pc += (double)fabsf(rc);
-                grad_out[ch * P + p] = rc > 0.0f ? gc : (rc < 0.0f ? -gc : 0.0f);
-            }
-            const float rd = d - dt;
-            pd += (double)fabsf(rd);
-            grad_out[3 * P + p] = rd > 0.0f ? gd : (rd < 0.0f ? -gd : 0.0f);
-        } else {
-#pragma unroll
-            for (int ch = 0; ch < 4; ++ch) grad_out[ch * P + p] = 0.0f;
-        }
-        grad_out[4 * P + p] = 0.0f;
-        if constexpr (F > 0) {
-            float gf[F];
-#pragma unroll
-            for (int f = 0; f < F; ++f) gf[f] = 0.0f;
-#pragma unroll
-            for (int f = 0; f < F; ++f) fv[f] = 0.0f;
-            if (on && K > 0 && sp.w2 != 0.0f) {
-#pragma unroll
-                for (int f = 0; f < F; ++f) fv[f] = out[(5 + f) * P + p];
-                if constexpr (MODE == kSemCE) {
-                    ps = (double)semantic_ce<F, KC>(fv, Wt, K, labels[p], gf, bias);
-                } else {
-                    ps = (double)sem_dz<F, KC>(fv, Wt, bias, K, labels[p], sp.bce != 0, dz);
-                    // dL/df = W dz
-#pragma unroll
-                    for (int k = 0; k < KC; ++k)
-                        if (k < K) {
-                            const float* wr = Wt + k * F;
-#pragma unroll
-                            for (int f = 0; f < F; ++f) gf[f] = fmaf(wr[f], dz[k], gf[f]);
-                        }
-                    dscale = gs;
-                }
-            }
-#pragma unroll
-            for (int f = 0; f < F; ++f) grad_out[(5 + f) * P + p] = gs * gf[f];
-        }
-        lc = pc * (double)gc;
-        ld = pd * ((double)sp.w1 / (double)Pv);
-        ls = ps * ((double)sp.w2 / (double)Pv);
-    }
-    // decoder gradients of the workgroup: dW = sum_p dscale_p f_p dz_p^T and
-    // db = sum_p dscale_p dz_p.  The contraction over a wavefront's 64
-    // pixels runs on MFMA (16x16x4 f32: four pixels per step; A[m][k] = f of
-    // pixel k at row m, B[k][n] = scaled dz of pixel k at class n), the four
-    // wavefronts' tiles and bias sums are then added in a fixed order.
-    if constexpr (MODE == kSemDzDec && F > 0 && KC > 0) {
-        constexpr int MT = (F + 15) / 16, NT = KC / 16;
-        float* sF = s_dyn + wave * kDecRows * (F + K);  // [32][F]
-        float* sZ = sF + kDecRows * F;                  // [32][K]
-        using f4 = __attribute__((__vector_size__(4 * sizeof(float)))) float;
-        f4 acc[MT][NT];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-        const int col = lane & 15, kk = lane >> 4, row = lane & (kDecRows - 1);
-        const bool c = dscale != 0.0f;
-        float db = 0.0f;  // lane n < K: bias sum of this wavefront, rows in a fixed order
-        for (int half = 0; half < 2; ++half) {
-            if ((lane >> 5) == half) {
-#pragma unroll
-                for (int f = 0; f < F; ++f) sF[row * F + f] = c ? fv[f] : 0.0f;
-#pragma unroll
-                for (int k = 0; k < KC; ++k)
-                    if (k < K) sZ[row * K + k] = c ? dscale * dz[k] : 0.0f;
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            // 8 steps of four pixels: A[m][k] = f of pixel k at row m, B[k][n]
-            // = scaled dz of pixel k at class n (zero past F and K)
-#pragma unroll 2
-            for (int st = 0; st < kDecRows / 4; ++st) {
-                const int pr = 4 * st + kk;
-                float a[MT];
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    const int m = col + 16 * mt;
-                    a[mt] = m < F ? sF[pr * F + m] : 0.0f;
-                }
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    const int n = col + 16 * nt;
-                    const float bv = n < K ? sZ[pr * K + n] : 0.0f;
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt)
-                        acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mt], bv, acc[mt][nt], 0, 0, 0);
-                }
-            }
-            if (lane < K) {
-                float t0 = 0.0f, t1 = 0.0f, t2 = 0.0f, t3 = 0.0f;  // four chains
-                for (int r = 0; r < kDecRows; r += 4) {
-                    t0 += sZ[r * K + lane];
-                    t1 += sZ[(r + 1) * K + lane];
-                    t2 += sZ[(r + 2) * K + lane];
-                    t3 += sZ[(r + 3) * K + lane];
-                }
-                db += (t0 + t1) + (t2 + t3);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        }
-        if (lane < KC) s_db[wave][lane] = db;
-        __syncthreads();  // every wavefront is done with its slot
-        // D[m][n] with m = 4 (lane / 16) + i, n = lane % 16 per tile, into the
-        // freed slots as [wave][F][K]
-        float* sD = s_dyn + wave * F * K;
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int mm = 16 * mt + 4 * kk + i, nn = 16 * nt + col;
-                    if (mm < F && nn < K) sD[mm * K + nn] = acc[mt][nt][i];
-                }
-        __syncthreads();
-        const int T = F * K + K;  // this workgroup's partial: dW [F][K], then db [K]
-        float* dst = dec_partials + (size_t)blockIdx.x * T;
-        for (int e = tid; e < F * K; e += kSlamThreads) {
-            float t = 0.0f;
-#pragma unroll
-            for (int w = 0; w < kSlamThreads / kWave; ++w) t += s_dyn[w * F * K + e];
-            dst[e] = t;
-        }
-        if (tid < K) {
-            float t = 0.0f;
-#pragma unroll
-            for (int w = 0; w < kSlamThreads / kWave; ++w) t += s_db[w][tid];
-            dst[F * K + tid] = t;
-        }
-    }
     for (int dd = kWave / 2; dd > 0; dd >>= 1) {
         lc += __shfl_xor(lc, dd, kWave);
         ld += __shfl_xor(ld, dd, kWave);
@@ -491,8 +386,326 @@ __global__ void __launch_bounds__(kSlamThreads) k_slam_loss(const float* __restr
     if (tid < 3) {
         double a = 0;
         for (int w = 0; w < kSlamThreads / kWave; ++w) a += s_red[tid][w];
-        partials[(size_t)tid * gridDim.x + blockIdx.x] = a;  // term-major
+        partials[(size_t)tid * gridDim.x + blockIdx.x] = a;
     }
+}
+
+// BCE: the semantic term through dz (sem_dz), otherwise the fused
+// cross-entropy (fewer registers).
+template <int F, int KC, bool BCE>
+__global__ void __launch_bounds__(kSlamThreads) k_slam_loss(const float* __restrict__ out, int64_t P,
+                                                            const float* __restrict__ rgb_t,
+                                                            const float* __restrict__ depth_t,
+                                                            const int32_t* __restrict__ labels,
+                                                            const float* __restrict__ Wt,
+                                                            const float* __restrict__ bias, int K, SlamParams sp,
+                                                            const float* __restrict__ med,
+                                                            const ViewWeights* __restrict__ vws,
+                                                            const gs_view* __restrict__ views, int n_views,
+                                                            float* __restrict__ grad_out,
+                                                            uint8_t* __restrict__ masks,
+                                                            double* __restrict__ partials) {
+    __shared__ double s_red[3][kSlamThreads / kWave];
+    const int64_t p0 = (int64_t)blockIdx.x * kSlamThreads;
+    const int i = threadIdx.x;
+    double lc = 0.0, ld = 0.0, ls = 0.0;
+    if (p0 + i < P) {
+        PixelTerms t;
+        const bool on = pixel_terms(out, P, p0, i, rgb_t, depth_t, sp, med, vws, views, n_views, grad_out, masks, t);
+        double ps = 0.0;
+        if constexpr (F > 0) {
+            float fv[F], gf[F];
+#pragma unroll
+            for (int f = 0; f < F; ++f) gf[f] = 0.0f;
+            if (on && K > 0 && sp.w2 != 0.0f) {
+#pragma unroll
+                for (int f = 0; f < F; ++f) fv[f] = (out + (5 + f) * P + p0)[i];
+                if constexpr (!BCE) {
+                    ps = (double)semantic_ce<F, KC>(fv, Wt, K, (labels + p0)[i], gf, bias);
+                } else {
+                    float dz[KC];
+                    ps = (double)sem_dz<F, KC>(fv, Wt, bias, K, (labels + p0)[i], dz);
+                    // dL/df = W dz
+#pragma unroll
+                    for (int k = 0; k < KC; ++k)
+                        if (k < K) {
+                            const float* wr = Wt + k * F;
+#pragma unroll
+                            for (int f = 0; f < F; ++f) gf[f] = fmaf(wr[f], dz[k], gf[f]);
+                        }
+                }
+            }
+#pragma unroll
+            for (int f = 0; f < F; ++f) (grad_out + (5 + f) * P + p0)[i] = t.w.gs * gf[f];
+        }
+        lc = t.c * (double)t.w.gc;
+        ld = t.d * t.w.d;
+        ls = ps * t.w.s;
+    }
+    store_partials(lc, ld, ls, s_red, partials);
+}
+
+// The same with the decoder gradients dW = sum_p s_p f_p dz_p^T and db =
+// sum_p s_p dz_p (s = w_sem M(p) / P_v).  Workgroups stay and take 256
+// pixels in turn; the wavefronts share nothing until the end, so no barrier
+// holds one between its pixels.
+//
+// A lane's logits live in a row of LDS and not in registers: the classes run
+// in a loop of four at a time (four independent chains of F FMAs, the four
+// rows of W in scalar registers), the passes over the classes -- logits and
+// maximum, exponentials and sum, dz and W dz -- read and write the row, and
+// what it holds at the end is the operand B of the contraction.  That runs on
+// MFMA (16x16x4 f32, four pixels per step: A[m][k] = f of pixel k at row m,
+// staged 32 pixels at a time, B[k][n] = scaled dz of pixel k at class n); B is
+// also what the bias sums add up.  Rows are an odd number of floats apart, so
+// that neither the lanes' accesses nor the operand loads share banks.  Each
+// 64 pixels are summed in binary32 by the MFMAs, and those sums in FP64.
+//
+// Bound by vector issue (4 F K flops per pixel, 2 F K more in the MFMAs, which
+// share the issue slots, and an exponential per class) and, at F = 16 and
+// K = 20, nearly as much by the 189 bytes per pixel.  With the logits in
+// registers, one pixel per thread and the workgroup's reduction after every
+// 256 pixels it was held by latency at three or four wavefronts per SIMD:
+// 549 us for eight 1200x680 views at F = 16, K = 20, 400 us now; a fifth
+// wavefront per SIMD spills 26 registers and is slower.
+__host__ __device__ constexpr int odd_stride(int n) { return n | 1; }
+// Floats of a wavefront's slot: its rows, and room for the operand loads of
+// the last ones, which run past them (rows m >= F of A and classes n >= K of
+// B: what they hold only reaches entries of D that nobody reads).
+__host__ __device__ constexpr int dec_slot(int F, int K) {
+    return kWave * odd_stride((K + 3) / 4 * 4) + kWave / 2 * odd_stride(F) + 16;
+}
+inline size_t dec_lds_bytes(int F, int K) {
+    const size_t slot = (size_t)dec_slot(F, K), tile = (size_t)F * K;
+    return (kSlamThreads / kWave) * sizeof(float) * (slot > tile ? slot : tile);
+}
+
+template <int F, int NT, bool BCE>
+__global__ void __launch_bounds__(kSlamThreads)
+    __attribute__((amdgpu_waves_per_eu(F <= 16 && NT <= 2 ? 4 : 2, 8))) k_slam_loss_dec(const float* __restrict__ out, int64_t P,
+                                                                const float* __restrict__ rgb_t,
+                                                                const float* __restrict__ depth_t,
+                                                                const int32_t* __restrict__ labels,
+                                                                const float* __restrict__ Wt, int K, SlamParams sp,
+                                                                const float* __restrict__ med,
+                                                                const ViewWeights* __restrict__ vws,
+                                                                const gs_view* __restrict__ views, int n_views,
+                                                                float* __restrict__ grad_out,
+                                                                uint8_t* __restrict__ masks,
+                                                                double* __restrict__ partials,
+                                                                float* __restrict__ dec_partials) {
+    constexpr int NW = kSlamThreads / kWave, MT = (F + 15) / 16, ROWS = kWave / 2;
+    constexpr int FS = odd_stride(F), U = F > 16 ? 2 : 4;  // rows of W at a time, 64 scalar registers
+    constexpr int U2 = F > 8 ? 2 : 4;                 // half in the last pass, whose loop holds more
+    extern __shared__ float s_dyn[];
+    __shared__ double s_red[3][NW];
+    __shared__ float s_db[NW][16 * NT];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int K4 = (K + 3) / 4 * 4, ZS = odd_stride(K4);
+    const float* bias = Wt + kWtBias;
+    float* const sZ = s_dyn + wave * dec_slot(F, K);  // [64][ZS]
+    float* const sF = sZ + kWave * ZS;                          // [32][FS]
+    float* const z = sZ + lane * ZS;
+    const int col = lane & 15, kk = lane >> 4;
+    // entry i of tile (mt, nt) is row 16 mt + 4 kk + i, class 16 nt + col; the
+    // bias sums are of class 16 nt + col over the pixel rows kk, kk + 4, ...
+    double lc = 0.0, ld = 0.0, ls = 0.0;
+    using f4 = __attribute__((__vector_size__(4 * sizeof(float)))) float;
+    double dws[MT][NT][4], dbs[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        dbs[nt] = 0.0;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) dws[mt][nt][i] = 0.0;
+    }
+    for (int64_t p0 = (int64_t)blockIdx.x * kSlamThreads; p0 < P; p0 += (int64_t)gridDim.x * kSlamThreads) {
+        bool on = false;
+        float scale = 0.0f, fv[F];
+        if (p0 + tid < P) {
+            // with every other load of the pixel, before anything waits
+            const int lab = (labels + p0)[tid];
+#pragma unroll
+            for (int f = 0; f < F; ++f) fv[f] = (out + (5 + f) * P + p0)[tid];
+            PixelTerms t;
+            on = pixel_terms(out, P, p0, tid, rgb_t, depth_t, sp, med, vws, views, n_views, grad_out, masks, t);
+            float gf[F];
+#pragma unroll
+            for (int f = 0; f < F; ++f) gf[f] = 0.0f;
+            if (on) {
+                scale = t.w.gs;
+                // logits, their maximum, the label's
+                float m = -INFINITY, zl = 0.0f;
+                for (int k0 = 0; k0 < K4; k0 += U) {
+                    float a[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) a[u] = bias[k0 + u];
+#pragma unroll
+                    for (int f = 0; f < F; ++f)
+#pragma unroll
+                        for (int u = 0; u < U; ++u) a[u] = fmaf(Wt[(k0 + u) * F + f], fv[f], a[u]);
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        z[k0 + u] = a[u];
+                        m = fmaxf(m, a[u]);
+                        zl = k0 + u == lab ? a[u] : zl;
+                    }
+                }
+                const bool has = lab >= 0 && lab < K;
+                float se = 0.0f, term = 0.0f, sdp = 0.0f, inv;
+                uint64_t live = 0;
+                if constexpr (!BCE) {
+#pragma unroll 4
+                    for (int k = 0; k < K4; ++k) {
+                        const float e = __expf(z[k] - m);
+                        z[k] = e;
+                        se += e;
+                    }
+                    inv = 1.0f / se;
+                    term = has ? __logf(se) - (zl - m) : 0.0f;
+                } else {
+                    // p_k, log p_k = z_k - lse, log(1 - p_k) = log(se - e_k) -
+                    // lse; the row keeps p_k and `live` whether the log that
+                    // the class's gradient uses is above the clamp, so that
+                    // dp_k = -1/p_k (label) or 1/(1 - p_k) (other classes,
+                    // hardware reciprocals) is rebuilt in the last pass
+#pragma unroll 4
+                    for (int k = 0; k < K4; ++k) {
+                        const float zk = z[k] - m;
+                        z[k] = zk;
+                        se += __expf(zk);
+                    }
+                    inv = 1.0f / se;
+                    const float lse = __logf(se);
+#pragma unroll 4
+                    for (int k = 0; k < K4; ++k) {
+                        const bool y = k == lab;
+                        const float zk = z[k], e = __expf(zk), pk = e * inv;
+                        const float lp = zk - lse, lq = __logf(se - e) - lse;
+                        term -= y ? fmaxf(lp, -100.0f) : fmaxf(lq, -100.0f);
+                        const bool w = y ? lp > -100.0f : lq > -100.0f;
+                        const float dp =
+                            w ? (y ? -__builtin_amdgcn_rcpf(pk) : __builtin_amdgcn_rcpf(1.0f - pk)) : 0.0f;
+                        sdp = fmaf(pk, dp, sdp);
+                        z[k] = pk;
+                        live |= (uint64_t)w << k;
+                    }
+                }
+                // dz and dL/df = W dz; the row ends as the scaled dz
+                for (int k0 = 0; k0 < K4; k0 += U2) {
+                    float dz[U2];
+#pragma unroll
+                    for (int u = 0; u < U2; ++u) {
+                        const int k = k0 + u;
+                        if constexpr (!BCE) {
+                            dz[u] = z[k] * inv - (k == lab ? 1.0f : 0.0f);
+                        } else {
+                            const float pk = z[k];
+                            const float dp = ((live >> k) & 1)
+                                                 ? (k == lab ? -__builtin_amdgcn_rcpf(pk) : __builtin_amdgcn_rcpf(1.0f - pk))
+                                                 : 0.0f;
+                            dz[u] = pk * (dp - sdp);
+                        }
+                        z[k] = scale * dz[u];
+                    }
+#pragma unroll
+                    for (int u = 0; u < U2; ++u)
+#pragma unroll
+                        for (int f = 0; f < F; ++f) gf[f] = fmaf(Wt[(k0 + u) * F + f], dz[u], gf[f]);
+                }
+                ls += (double)term * t.w.s;
+            }
+#pragma unroll
+            for (int f = 0; f < F; ++f) (grad_out + (5 + f) * P + p0)[tid] = t.w.gs * gf[f];
+            lc += t.c * (double)t.w.gc;
+            ld += t.d * t.w.d;
+        }
+        if (__builtin_amdgcn_ballot_w64(!on) != 0 && !on) {  // no contribution
+            for (int k = 0; k < K4; ++k) z[k] = 0.0f;
+#pragma unroll
+            for (int f = 0; f < F; ++f) fv[f] = 0.0f;
+        }
+        f4 acc[MT][NT];
+        float db[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            db[nt] = 0.0f;
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+        for (int half = 0; half < 2; ++half) {
+            if ((lane >> 5) == half) {
+#pragma unroll
+                for (int f = 0; f < F; ++f) sF[(lane & (ROWS - 1)) * FS + f] = fv[f];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll 2
+            for (int st = 0; st < ROWS / 4; ++st) {
+                const int pr = 4 * st + kk;
+                float a[MT];
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    a[mt] = sF[pr * FS + col + 16 * mt];
+                }
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    if (16 * nt >= K) continue;  // uniform
+                    const float b = sZ[(half * ROWS + pr) * ZS + col + 16 * nt];
+                    db[nt] += b;
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt)
+                        acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mt], b, acc[mt][nt], 0, 0, 0);
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            dbs[nt] += (double)db[nt];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) dws[mt][nt][i] += (double)acc[mt][nt][i];
+        }
+    }
+    // the wavefronts' tiles and bias sums added in a fixed order: this
+    // workgroup's partial, dW [F][K], then db [K]
+    __syncthreads();  // every wavefront is done with its slot
+    float* sD = s_dyn + wave * F * K;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int mm = 16 * mt + 4 * kk + i, nn = 16 * nt + col;
+                if (mm < F && nn < K) sD[mm * K + nn] = (float)dws[mt][nt][i];
+            }
+        double t = dbs[nt];
+        t += __shfl_xor(t, 16, kWave);
+        t += __shfl_xor(t, 32, kWave);
+        if (kk == 0) s_db[wave][16 * nt + col] = (float)t;
+    }
+    __syncthreads();
+    float* dst = dec_partials + (size_t)blockIdx.x * (F * K + K);
+    for (int e = tid; e < F * K; e += kSlamThreads) {
+        float t = 0.0f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) t += s_dyn[w * F * K + e];
+        dst[e] = t;
+    }
+    if (tid < K) {
+        float t = 0.0f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) t += s_db[w][tid];
+        dst[F * K + tid] = t;
+    }
+    store_partials(lc, ld, ls, s_red, partials);
 }
 
 // ---------------------------------------------------------------------------
@@ -885,7 +1098,7 @@ size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 unsigned slam_blocks(int64_t P) { return (unsigned)((P + kSlamThreads - 1) / kSlamThreads); }
 
 struct SlamWs {
-    size_t hist, sel, med, part, spart, stage, wt, mask, maps, dpart, dstage, total;
+    size_t hist, sel, med, vws, part, spart, stage, wt, mask, maps, dpart, dstage, total;
 };
 
 int ssim_tiles(const gs_view* views, int n_views, SsimTiles* st) {
@@ -917,6 +1130,8 @@ SlamWs slam_layout(int64_t P, const gs_view* views, int n_views, bool ssim, int 
     o += align256((size_t)n_views * 2 * sizeof(MedSel));
     L.med = o;
     o += align256((size_t)n_views * 4);
+    L.vws = o;
+    o += align256((size_t)n_views * sizeof(ViewWeights));
     const int64_t nblk = slam_blocks(P);
     L.part = o;
     o += align256((size_t)nblk * 3 * 8);
@@ -926,7 +1141,7 @@ SlamWs slam_layout(int64_t P, const gs_view* views, int n_views, bool ssim, int 
     L.stage = o;
     o += align256((size_t)sum_stage_blocks(nblk) * 3 * 8);
     L.wt = o;
-    o += align256((size_t)32 * GS_MAX_CLASSES * 4);
+    o += align256((size_t)kWtFloats * 4);
     L.mask = o;
     o += align256((size_t)P);
     L.maps = o;
@@ -990,17 +1205,20 @@ __global__ void __launch_bounds__(256) k_rows_final(const double* __restrict__ s
     }
 }
 
-// Workgroups of a persistent SSIM launch: as many as are resident on the
-// device at once, rounded down to a multiple of the 8 XCDs (ItemWalk), at
-// least 8, at most the items rounded up to 8.
-unsigned ssim_grid(const void* kern, int nitems) {
+// Workgroups of kSlamThreads that are resident on the device at once.
+unsigned resident_blocks(const void* kern, size_t lds) {
     int dev = 0, cus = 0, per_cu = 0;
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kSlamThreads, 0);
-    if (cus < 1) cus = 1;
-    if (per_cu < 1) per_cu = 1;
-    int g = cus * per_cu / 8 * 8;
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kSlamThreads, lds);
+    return (unsigned)((cus > 1 ? cus : 1) * (per_cu > 1 ? per_cu : 1));
+}
+
+// Workgroups of a persistent SSIM launch: the resident ones, rounded down to
+// a multiple of the 8 XCDs (ItemWalk), at least 8, at most the items rounded
+// up to 8.
+unsigned ssim_grid(const void* kern, int nitems) {
+    int g = (int)resident_blocks(kern, 0) / 8 * 8;
     const int cap = (nitems + 7) / 8 * 8;
     if (g > cap) g = cap;
     return (unsigned)(g >= 8 ? g : 8);
@@ -1009,21 +1227,27 @@ unsigned ssim_grid(const void* kern, int nitems) {
 template <int F, int KC>
 void launch_slam_pixels(unsigned nblk, hipStream_t s, const float* out, int64_t P, const float* rgb_t,
                         const float* depth_t, const int32_t* labels, const float* Wt, const float* bias, int K,
-                        const SlamParams& sp, const float* med, const gs_view* views, int n_views, float* grad_out,
-                        uint8_t* masks, double* partials, float* dec_partials) {
-    // the decoder-gradient path is its own instantiation, so that the plain
-    // loss keeps its register budget
+                        const SlamParams& sp, const float* med, const ViewWeights* vws, const gs_view* views, int n_views,
+                        float* grad_out, uint8_t* masks, double* partials) {
+    auto kern = sp.bce ? k_slam_loss<F, KC, true> : k_slam_loss<F, KC, false>;
+    hipLaunchKernelGGL(kern, dim3(nblk), dim3(kSlamThreads), 0, s, out, P, rgb_t, depth_t, labels, Wt, bias, K, sp,
+                       med, vws, views, n_views, grad_out, masks, partials);
+}
+
+// With the decoder gradients: as many workgroups as are resident at once (at
+// most one per 256 pixels, for which the partials have room).
+template <int F, int NT>
+unsigned launch_slam_pixels_dec(hipStream_t s, const float* out, int64_t P, const float* rgb_t, const float* depth_t,
+                                const int32_t* labels, const float* Wt, int K, const SlamParams& sp, const float* med,
+                                const ViewWeights* vws, const gs_view* views, int n_views, float* grad_out, uint8_t* masks, double* partials,
+                                float* dec_partials) {
+    auto kern = sp.bce ? k_slam_loss_dec<F, NT, true> : k_slam_loss_dec<F, NT, false>;
     const size_t lds = dec_lds_bytes(F, K);
-    if (dec_partials != nullptr && F > 0)
-        hipLaunchKernelGGL((k_slam_loss<F, KC, kSemDzDec>), dim3(nblk), dim3(kSlamThreads), lds, s, out, P, rgb_t,
-                           depth_t, labels, Wt, bias, K, sp, med, views, n_views, grad_out, masks, partials,
-                           dec_partials);
-    else if (sp.bce)
-        hipLaunchKernelGGL((k_slam_loss<F, KC, kSemDz>), dim3(nblk), dim3(kSlamThreads), 0, s, out, P, rgb_t, depth_t,
-                           labels, Wt, bias, K, sp, med, views, n_views, grad_out, masks, partials, nullptr);
-    else
-        hipLaunchKernelGGL((k_slam_loss<F, KC, kSemCE>), dim3(nblk), dim3(kSlamThreads), 0, s, out, P, rgb_t, depth_t,
-                           labels, Wt, bias, K, sp, med, views, n_views, grad_out, masks, partials, nullptr);
+    const unsigned fit = resident_blocks(reinterpret_cast<const void*>(kern), lds), most = slam_blocks(P);
+    const unsigned nblk = fit < most ? fit : most;
+    hipLaunchKernelGGL(kern, dim3(nblk), dim3(kSlamThreads), lds, s, out, P, rgb_t, depth_t, labels, Wt, K, sp,
+                       med, vws, views, n_views, grad_out, masks, partials, dec_partials);
+    return nblk;
 }
 
 int dec_terms_of(int F, const gs_decoder* dec) {
@@ -1046,18 +1270,30 @@ hipError_t launch_slam_t(const float* out, const float* rgb_t, const float* dept
     double* part = reinterpret_cast<double*>(ws + L.part);
     double* spart = reinterpret_cast<double*>(ws + L.spart);
     float* Wt = reinterpret_cast<float*>(ws + L.wt);
+    ViewWeights* vws = reinterpret_cast<ViewWeights*>(ws + L.vws);
     uint8_t* mk = masks != nullptr ? masks : reinterpret_cast<uint8_t*>(ws + L.mask);
     float* maps = reinterpret_cast<float*>(ws + L.maps);
     float* dpart = dterms > 0 ? reinterpret_cast<float*>(ws + L.dpart) : nullptr;
     double* dstage = reinterpret_cast<double*>(ws + L.dstage);
 
     // 1. median depth error per view
+    SlamParams sp;
+    sp.w0 = o.w_color;
+    sp.w1 = o.w_depth;
+    sp.w2 = o.w_sem;
+    sp.lam = o.ssim_lambda;
+    sp.tau_obs = o.tau_obs;
+    sp.tau_unobs = o.tau_unobs;
+    sp.obs_factor = o.obs_factor;
+    sp.unobs_factor = o.unobs_factor;
+    sp.use_obs = (o.flags & GS_LOSS_OBS_MASK) != 0;
+    sp.bce = (o.flags & GS_LOSS_BCE) != 0;
     const int K = dec != nullptr ? dec->n_classes : 0;
     const bool sem = F > 0 && K > 0 && o.w_sem != 0.0f;
     const int words = n_views * kMedWords;
-    const int prep = sem && F * K > words ? F * K : words;
+    const int wt = F * ((K + 3) / 4 * 4), prep = sem && wt > words ? wt : words;
     hipLaunchKernelGGL(k_slam_prep, dim3((unsigned)ceil_div(prep, 256)), dim3(256), 0, s, hist, words,
-                       sem ? dec->weight : nullptr, F, K, Wt);
+                       sem ? dec->weight : nullptr, sem ? dec->bias : nullptr, F, K, Wt, views_dev, n_views, sp, vws);
     int64_t pmax = 0;
     for (int v = 0; v < n_views; ++v) {
         const int64_t pv = (int64_t)views_host[v].width * views_host[v].height;
@@ -1071,27 +1307,21 @@ hipError_t launch_slam_t(const float* out, const float* rgb_t, const float* dept
     hipLaunchKernelGGL(k_median_final, dim3(n_views), dim3(kSlamThreads), 0, s, hist, sel, med, median);
 
     // 2. masks, L1 and the semantic term (with the decoder gradients' block partials)
-    SlamParams sp;
-    sp.w0 = o.w_color;
-    sp.w1 = o.w_depth;
-    sp.w2 = o.w_sem;
-    sp.lam = o.ssim_lambda;
-    sp.tau_obs = o.tau_obs;
-    sp.tau_unobs = o.tau_unobs;
-    sp.obs_factor = o.obs_factor;
-    sp.unobs_factor = o.unobs_factor;
-    sp.use_obs = (o.flags & GS_LOSS_OBS_MASK) != 0;
-    sp.bce = (o.flags & GS_LOSS_BCE) != 0;
-    const unsigned nblk = slam_blocks(P);
+    unsigned nblk = slam_blocks(P);
     const int Ke = sem ? K : 0;
     const float* bias = sem ? dec->bias : nullptr;
-    float* dp = sem ? dpart : nullptr;
-    if (Ke > 32)
-        launch_slam_pixels<F, 64>(nblk, s, out, P, rgb_t, depth_t, labels, Wt, bias, Ke, sp, med, views_dev, n_views,
-                                  grad_out, mk, part, dp);
-    else
-        launch_slam_pixels<F, 32>(nblk, s, out, P, rgb_t, depth_t, labels, Wt, bias, Ke, sp, med, views_dev, n_views,
-                                  grad_out, mk, part, dp);
+    if constexpr (F > 0) {
+        if (sem && dterms > 0) {
+            auto go = Ke > 32 ? launch_slam_pixels_dec<F, 4>
+                              : (Ke > 16 ? launch_slam_pixels_dec<F, 2> : launch_slam_pixels_dec<F, 1>);
+            nblk = go(s, out, P, rgb_t, depth_t, labels, Wt, Ke, sp, med, vws, views_dev, n_views, grad_out, mk, part,
+                      dpart);
+        }
+    }
+    if (!(sem && dterms > 0)) {
+        auto go = Ke > 32 ? launch_slam_pixels<F, 64> : launch_slam_pixels<F, 32>;
+        go(nblk, s, out, P, rgb_t, depth_t, labels, Wt, bias, Ke, sp, med, vws, views_dev, n_views, grad_out, mk, part);
+    }
     if (dterms > 0) {
         // dL/dW and dL/db (zero when the semantic term is off)
         if (!sem) {
