@@ -141,116 +141,190 @@ __global__ void __launch_bounds__(kGrowThreads) k_expand_write(const uint8_t* __
 // ---------------------------------------------------------------------------
 // DSR
 // ---------------------------------------------------------------------------
-constexpr int kDsrItems = 16;
+constexpr int kDsrItems = 8;
 constexpr int kDsrChunk = kGrowThreads * kDsrItems;
+constexpr int kDsrBlocks = 1024;  // most blocks: each reads every block's numbers in the merges below
 
-// stats[0..7] (double): sum s, sum (s - mu)^2, sum over the big set of s,
-// its count, sum over the small set of -log s, its count, mu, sigma.
-__device__ __forceinline__ double block_sum_d(double v, double* s_red) {
+// Sums of N values over the block, to every thread, in a fixed order.
+template <int N>
+__device__ __forceinline__ void block_sums_d(double (&v)[N], double (*s_red)[kGrowThreads / kWave]) {
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    for (int d = kWave / 2; d > 0; d >>= 1) v += __shfl_xor(v, d, kWave);
-    if (lane == 0) s_red[wave] = v;
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        for (int d = kWave / 2; d > 0; d >>= 1) v[k] += __shfl_xor(v[k], d, kWave);
+        if (lane == 0) s_red[k][wave] = v[k];
+    }
     __syncthreads();
-    double t = 0.0;
-    for (int w = 0; w < kGrowThreads / kWave; ++w) t += s_red[w];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        v[k] = 0.0;
+        for (int w = 0; w < kGrowThreads / kWave; ++w) v[k] += s_red[k][w];
+    }
     __syncthreads();
-    return t;
 }
 
-// PASS 0: partial sums of s; PASS 1: of (s - mu)^2; PASS 2: the two sets
-__global__ void __launch_bounds__(kGrowThreads) k_dsr_partial(const float* __restrict__ ls, int64_t m, int pass,
-                                                              const double* __restrict__ stats,
-                                                              double* __restrict__ partials) {
-    __shared__ double s_red[kGrowThreads / kWave];
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-    const double mu = pass > 0 ? stats[6] : 0.0, sd = pass > 1 ? stats[7] : 0.0;
-    const double big = mu + 2.0 * sd, small = mu - 2.0 * sd;
-    float x[kDsrItems];
+__host__ __device__ __forceinline__ int64_t dsr_chunks(int64_t m) { return (m + kDsrChunk - 1) / kDsrChunk; }
+
+// Log scales of chunk c: item k of the thread is c * kDsrChunk +
+// k * kGrowThreads + threadIdx.x (the last one where there is none).
+__device__ __forceinline__ void dsr_load(const float* __restrict__ ls, int64_t m, int64_t c, float (&x)[kDsrItems]) {
+    const int64_t j0 = c * kDsrChunk + threadIdx.x;
 #pragma unroll
     for (int k = 0; k < kDsrItems; ++k) {
-        const int64_t j = (int64_t)blockIdx.x * kDsrChunk + k * kGrowThreads + threadIdx.x;
+        const int64_t j = j0 + k * kGrowThreads;
         x[k] = ls[j < m ? j : m - 1];
     }
+}
+
+// The block's chunks in turn: body(k-th scales, which of them are there,
+// chunk).  x holds the first chunk; the next one is under way during a body.
+template <typename Body>
+__device__ __forceinline__ void dsr_each(const float* __restrict__ ls, int64_t m, float (&x)[kDsrItems], Body body) {
+    for (int64_t c = blockIdx.x; c < dsr_chunks(m); c += gridDim.x) {
+        double s[kDsrItems];
+        bool live[kDsrItems];
+        float y[kDsrItems];
+        if (c + gridDim.x < dsr_chunks(m)) dsr_load(ls, m, c + gridDim.x, y);
 #pragma unroll
-    for (int k = 0; k < kDsrItems; ++k) {
-        const int64_t j = (int64_t)blockIdx.x * kDsrChunk + k * kGrowThreads + threadIdx.x;
-        if (j >= m) continue;
-        const double s = (double)dec_exp(x[k]);
-        if (pass == 0) {
-            a0 += s;
-        } else if (pass == 1) {
-            a0 += (s - mu) * (s - mu);
-        } else {
-            if (s > big) {
-                a0 += s;
-                a1 += 1.0;
-            }
-            if (s < small) {
-                a2 += -log(s);
-                a3 += 1.0;
-            }
+        for (int k = 0; k < kDsrItems; ++k) {
+            s[k] = (double)dec_exp(x[k]);
+            live[k] = c * kDsrChunk + k * kGrowThreads + threadIdx.x < m;
         }
-    }
-    const int nb = gridDim.x;
-    const double t0 = block_sum_d(a0, s_red);
-    if (pass < 2) {
-        if (threadIdx.x == 0) partials[blockIdx.x] = t0;
-        return;
-    }
-    const double t1 = block_sum_d(a1, s_red), t2 = block_sum_d(a2, s_red), t3 = block_sum_d(a3, s_red);
-    if (threadIdx.x == 0) {
-        partials[blockIdx.x] = t0;
-        partials[nb + blockIdx.x] = t1;
-        partials[2 * nb + blockIdx.x] = t2;
-        partials[3 * nb + blockIdx.x] = t3;
+        body(s, live, c);
+#pragma unroll
+        for (int k = 0; k < kDsrItems; ++k) x[k] = y[k];
     }
 }
 
-// One block: the pass's sums in a fixed order, into stats (and, after the
-// last pass, the outputs).
-__global__ void __launch_bounds__(kGrowThreads) k_dsr_reduce(const double* __restrict__ partials, int nb, int pass,
-                                                             int64_t m, float w_big, float w_small,
-                                                             double* __restrict__ stats, double* __restrict__ out) {
-    __shared__ double s_red[kGrowThreads / kWave];
-    const int terms = pass < 2 ? 1 : 4;
-    double r[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int k = 0; k < terms; ++k) {
-        double a = 0.0;
-        for (int b = threadIdx.x; b < nb; b += kGrowThreads) a += partials[k * nb + b];
-        r[k] = block_sum_d(a, s_red);
+// Three launches: the moments of every block's chunks, their two sets, the
+// gradient.  The blocks of the second and third merge what the one before
+// left for themselves (at most kDsrBlocks numbers of each kind), instead of a
+// one-block launch after every pass: seven launches took 47 us for 1 M
+// Gaussians and 35 us for 77 k, three take 30 and 17.
+
+// Count, sum and squared deviations from the mean of the block's scales, chunks merged pairwise (no sum of squares, whose difference from
+// the squared mean would cancel): mom[3 b ..].
+__global__ void __launch_bounds__(kGrowThreads) k_dsr_moments(const float* __restrict__ ls, int64_t m,
+                                                              double* __restrict__ mom) {
+    __shared__ double s_red[1][kGrowThreads / kWave];
+    float x[kDsrItems];
+    dsr_load(ls, m, blockIdx.x, x);
+    double n = 0.0, sum = 0.0, q = 0.0;
+    dsr_each(ls, m, x, [&](const double(&s)[kDsrItems], const bool(&live)[kDsrItems], int64_t c) {
+        double a[1] = {0.0}, e[1] = {0.0};
+#pragma unroll
+        for (int k = 0; k < kDsrItems; ++k) a[0] += live[k] ? s[k] : 0.0;
+        block_sums_d(a, s_red);
+        const int64_t left = m - c * kDsrChunk;
+        const double nc = (double)(left < kDsrChunk ? left : kDsrChunk), mc = a[0] / nc;
+#pragma unroll
+        for (int k = 0; k < kDsrItems; ++k) e[0] += live[k] ? (s[k] - mc) * (s[k] - mc) : 0.0;
+        block_sums_d(e, s_red);
+        q += e[0];
+        if (n > 0.0) {
+            const double d = mc - sum / n;
+            q += d * d * (n * nc / (n + nc));
+        }
+        n += nc;
+        sum += a[0];
+    });
+    if (threadIdx.x == 0) {
+        mom[3 * blockIdx.x] = n;
+        mom[3 * blockIdx.x + 1] = sum;
+        mom[3 * blockIdx.x + 2] = q;
     }
-    if (threadIdx.x != 0) return;
-    if (pass == 0) {
-        stats[0] = r[0];
-        stats[6] = m > 0 ? r[0] / (double)m : 0.0;
-    } else if (pass == 1) {
-        stats[1] = r[0];
-        stats[7] = m > 0 ? sqrt(r[0] / (double)m) : 0.0;
-    } else {
-        for (int k = 0; k < 4; ++k) stats[2 + k] = r[k];
+}
+
+// Mean and population standard deviation from the blocks' moments, by the
+// whole block, in a fixed order.
+__device__ __forceinline__ void dsr_stats(const double* __restrict__ mom, int64_t m,
+                                          double (*s_red)[kGrowThreads / kWave], double& mu, double& sd) {
+    double a[1] = {0.0}, q[1] = {0.0};
+    for (int b = threadIdx.x; b < (int)gridDim.x; b += kGrowThreads) a[0] += mom[3 * b + 1];
+    block_sums_d(a, s_red);
+    mu = a[0] / (double)m;
+    for (int b = threadIdx.x; b < (int)gridDim.x; b += kGrowThreads) {
+        const double d = mom[3 * b + 1] / mom[3 * b] - mu;
+        q[0] += mom[3 * b + 2] + mom[3 * b] * d * d;
+    }
+    block_sums_d(q, s_red);
+    sd = sqrt(q[0] / (double)m);
+}
+
+// Sums over the block's part of the big set (s > mu + 2 sigma) of s, its
+// count, over that of the small set (s < mu - 2 sigma) of -log s, its count:
+// sets[4 b ..].
+__global__ void __launch_bounds__(kGrowThreads) k_dsr_sets(const float* __restrict__ ls, int64_t m,
+                                                           const double* __restrict__ mom,
+                                                           double* __restrict__ sets, double* __restrict__ out) {
+    __shared__ double s_red[4][kGrowThreads / kWave];
+    float x[kDsrItems];
+    dsr_load(ls, m, blockIdx.x, x);
+    double mu, sd, a[4] = {0.0, 0.0, 0.0, 0.0};
+    dsr_stats(mom, m, s_red, mu, sd);
+    const double big = mu + 2.0 * sd, small = mu - 2.0 * sd;
+    dsr_each(ls, m, x, [&](const double(&s)[kDsrItems], const bool(&live)[kDsrItems], int64_t) {
+#pragma unroll
+        for (int k0 = 0; k0 < kDsrItems; k0 += 4) {
+            // one logarithm for four scales: the product of four floats stays
+            // far inside the doubles (2^-149 to the fourth is 2^-596)
+            double prod = 1.0;
+#pragma unroll
+            for (int k = k0; k < k0 + 4; ++k) {
+                const bool in_big = live[k] && s[k] > big, in_small = live[k] && s[k] < small;
+                a[0] += in_big ? s[k] : 0.0;
+                a[1] += in_big ? 1.0 : 0.0;
+                prod *= in_small ? s[k] : 1.0;
+                a[3] += in_small ? 1.0 : 0.0;
+            }
+            if (prod != 1.0) a[2] -= log(prod);
+        }
+    });
+    block_sums_d(a, s_red);
+    if (threadIdx.x == 0)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) sets[4 * blockIdx.x + k] = a[k];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        out[3] = mu;
+        out[4] = sd;
+    }
+}
+
+// grad_ls[j] += w_big s / n_big (big set), -w_small / n_small (small set);
+// block 0 also writes the values.  nb: the blocks of k_dsr_sets.
+__global__ void __launch_bounds__(kGrowThreads) k_dsr_grad(const float* __restrict__ ls, int64_t m,
+                                                           const double* __restrict__ sets, int nb, float w_big,
+                                                           float w_small, float* __restrict__ grad, double* out) {
+    __shared__ double s_red[4][kGrowThreads / kWave];
+    float x[kDsrItems];
+    dsr_load(ls, m, blockIdx.x, x);
+    double r[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int b = threadIdx.x; b < nb; b += kGrowThreads)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) r[k] += sets[4 * b + k];
+    block_sums_d(r, s_red);
+    const double mu = out[3], sd = out[4];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
         const double Lb = r[1] > 0.0 ? r[0] / r[1] : 0.0, Ls = r[3] > 0.0 ? r[2] / r[3] : 0.0;
         out[0] = Lb;
         out[1] = Ls;
         out[2] = (double)w_big * Lb + (double)w_small * Ls;
-        out[3] = stats[6];
-        out[4] = stats[7];
         out[5] = r[1];
         out[6] = r[3];
     }
-}
-
-// grad_ls[j] += w_big s / n_big (big set), -w_small / n_small (small set)
-__global__ void __launch_bounds__(kGrowThreads) k_dsr_grad(const float* __restrict__ ls, int64_t m,
-                                                           const double* __restrict__ stats, float w_big,
-                                                           float w_small, float* __restrict__ grad) {
-    const int64_t j = (int64_t)blockIdx.x * kGrowThreads + threadIdx.x;
-    if (j >= m) return;
-    const double mu = stats[6], sd = stats[7], nb = stats[3], ns = stats[5];
-    const double s = (double)dec_exp(ls[j]);
-    double g = 0.0;
-    if (s > mu + 2.0 * sd) g += (double)w_big * s / nb;
-    if (s < mu - 2.0 * sd) g += -(double)w_small / ns;
-    if (g != 0.0) grad[j] += (float)g;
+    if (grad == nullptr) return;
+    const double big = mu + 2.0 * sd, small = mu - 2.0 * sd;
+    const double g_big = (double)w_big / r[1], g_small = -(double)w_small / r[3];
+    dsr_each(ls, m, x, [&](const double(&s)[kDsrItems], const bool(&live)[kDsrItems], int64_t c) {
+#pragma unroll
+        for (int k = 0; k < kDsrItems; ++k) {
+            if (!live[k]) continue;
+            double g = 0.0;
+            if (s[k] > big) g += g_big * s[k];
+            if (s[k] < small) g += g_small;
+            if (g != 0.0) grad[c * kDsrChunk + k * kGrowThreads + threadIdx.x] += (float)g;
+        }
+    });
 }
 
 }  // namespace
@@ -289,25 +363,26 @@ hipError_t launch_expand(const uint8_t* masks, const float* rgb_t, const float* 
     return hipGetLastError();
 }
 
+static int dsr_blocks(int64_t m) {
+    const int64_t chunks = dsr_chunks(m), per = (chunks + kDsrBlocks - 1) / kDsrBlocks;
+    return (int)((chunks + per - 1) / per);
+}
+
 size_t dsr_workspace_bytes(int64_t n) {
-    const int64_t m = 3 * n, nb = (m + kDsrChunk - 1) / kDsrChunk;
-    return ((size_t)nb * 4 * 8 + 255) / 256 * 256 + 256;  // partials, then stats[8]
+    if (n <= 0) return 0;
+    return ((size_t)dsr_blocks(3 * n) * 7 * 8 + 255) / 256 * 256;  // moments [nb][3], sets [nb][4]
 }
 
 hipError_t launch_dsr(const float* log_scale, int64_t n, float w_big, float w_small, float* grad_ls, double* out,
                       void* ws, hipStream_t s) {
     const int64_t m = 3 * n;
-    const int nb = (int)((m + kDsrChunk - 1) / kDsrChunk);
-    double* partials = static_cast<double*>(ws);
-    double* stats = reinterpret_cast<double*>(static_cast<char*>(ws) + ((size_t)nb * 4 * 8 + 255) / 256 * 256);
-    for (int pass = 0; pass < 3; ++pass) {
-        hipLaunchKernelGGL(k_dsr_partial, dim3(nb), dim3(kGrowThreads), 0, s, log_scale, m, pass, stats, partials);
-        hipLaunchKernelGGL(k_dsr_reduce, dim3(1), dim3(kGrowThreads), 0, s, partials, nb, pass, m, w_big, w_small,
-                           stats, out);
-    }
-    if (grad_ls != nullptr)
-        hipLaunchKernelGGL(k_dsr_grad, dim3((unsigned)((m + kGrowThreads - 1) / kGrowThreads)), dim3(kGrowThreads), 0,
-                           s, log_scale, m, stats, w_big, w_small, grad_ls);
+    const int nb = dsr_blocks(m);
+    double* mom = static_cast<double*>(ws);
+    double* sets = mom + 3 * (size_t)nb;
+    hipLaunchKernelGGL(k_dsr_moments, dim3(nb), dim3(kGrowThreads), 0, s, log_scale, m, mom);
+    hipLaunchKernelGGL(k_dsr_sets, dim3(nb), dim3(kGrowThreads), 0, s, log_scale, m, mom, sets, out);
+    hipLaunchKernelGGL(k_dsr_grad, dim3(grad_ls != nullptr ? nb : 1), dim3(kGrowThreads), 0, s, log_scale, m, sets, nb,
+                       w_big, w_small, grad_ls, out);
     return hipGetLastError();
 }
 
