@@ -23,7 +23,9 @@
 //      filters the maps again (the window is symmetric, so the adjoint is the
 //      same filter) and adds G*m_mu + 2 x G*m_xx + y G*m_xy to the colour
 //      gradient.  Both walk the tiles persistently, loading the next tile
-//      while the current one is filtered.
+//      while the current one is filtered.  Where there are enough pixels to
+//      fill the device, k_ssim does both in one pass down strips of columns,
+//      and the maps never leave the chip.
 //   4. a fixed-order sum of the per-block partial losses (deterministic).
 #include "loss_common.h"
 
@@ -52,6 +54,20 @@ struct SsimConst {
 struct SsimTiles {
     int first[GS_MAX_VIEWS + 1];
     int n_views;
+};
+
+// Strips of k_ssim: first workgroup of each view (x strip fastest, then
+// channel, then y strip), output rows of a strip.
+constexpr int kStripBW = 256, kStripR = 4;  // columns of a strip with its 10 on either side, rows of a step
+constexpr int kSsimPad = 8;                 // columns of zeros left and right of a strip in LDS
+// k_ssim filters x - 1/2 and y - 1/2 (-1/2 outside the view): variances and
+// the covariance do not change with it, and the squares that round are at most
+// a quarter instead of one.  Against 64 bits the colour gradient of the
+// mapping loss is 1.9e-7 off instead of 1.0e-6 (eight 1200x680 views).
+constexpr float kSsimMid = 0.5f;
+struct SsimStrips {
+    int first[GS_MAX_VIEWS + 1];
+    int n_views, rows;
 };
 
 // View of pixel p of a workgroup whose pixels are consecutive, p0 (uniform) the
@@ -1068,6 +1084,250 @@ __global__ void __launch_bounds__(kSlamThreads) k_ssim_bwd(const float* __restri
     }
 }
 
+// One row more of a vertical window: returns the window that ends with h,
+// part[k] the sum of the one that ends k + 1 rows later.  (The shift is the
+// FMA's own, no ring and no moves.)
+__device__ __forceinline__ float window_row(const SsimConst& sc, float h, float (&part)[2 * kSsimR]) {
+    const float done = fmaf(sc.g[2 * kSsimR], h, part[0]);
+#pragma unroll
+    for (int k = 0; k < 2 * kSsimR - 1; ++k) part[k] = fmaf(sc.g[2 * kSsimR - 1 - k], h, part[k + 1]);
+    part[2 * kSsimR - 1] = sc.g[0] * h;
+    return done;
+}
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kSsimK = 7;  // steps of four inputs that hold the 26 of 16 outputs
+
+// Horizontal windows of Q planes, R rows and the wavefront's 64 columns:
+// o[q][i] that of plane q, row i and the lane's column.  Per plane and four
+// rows one 16x16 product with the banded matrix of the weights (`band`: tap
+// 4 s + lane / 16 - lane % 16), whose 16 rows are the four of each 16 columns,
+// so that a lane's four results are its own column's.  With rows 4 times an
+// odd number of words apart the 64 lanes of a read are on the 64 banks.
+// The zeros of the band would turn an infinity or a NaN into NaNs outside
+// its window: with `finite` false the windows are summed tap by tap.
+template <int Q, int R, int LD>
+__device__ __forceinline__ void window_cols(const SsimConst& sc, const float (*s_f)[R][LD],
+                                            const float (&band)[kSsimK], bool finite, float (&o)[Q][R]) {
+    static_assert(LD % 8 == 4, "no bank conflicts");
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const float* src = &s_f[0][0][kSsimPad - kSsimR];
+    if (finite) {
+        const float* a = src + (lane & 3) * LD + wave * kWave + (lane & 12) * 4 + (lane >> 4);
+        f32x4 d[Q][R / 4];
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+#pragma unroll
+            for (int g = 0; g < R / 4; ++g) d[q][g] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int s = 0; s < kSsimK; ++s)
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+#pragma unroll
+                for (int g = 0; g < R / 4; ++g)
+                    d[q][g] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[(q * R + 4 * g) * LD + 4 * s], band[s], d[q][g], 0,
+                                                                   0, 0);
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+#pragma unroll
+            for (int i = 0; i < R; ++i) o[q][i] = d[q][i / 4][i % 4];
+    } else {
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+#pragma unroll
+            for (int i = 0; i < R; ++i) o[q][i] = 0.0f;
+#pragma unroll 1
+        for (int tp = 0; tp <= 2 * kSsimR; ++tp)
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+#pragma unroll
+                for (int i = 0; i < R; ++i)
+                    o[q][i] = fmaf(sc.g[tp], src[(q * R + i) * LD + threadIdx.x + tp], o[q][i]);
+    }
+}
+
+// SSIM of one strip of one channel: the loss and its gradient, added to
+// grad_out.  A workgroup of BW threads takes BW columns, one a thread, of which
+// the middle BW - 20 are its own, and walks down pl.rows output rows in steps
+// of R input rows:
+//   1. x, y, x^2 + y^2 and xy of the new rows, x and y less 1/2, through the
+//      vertical window (partial sums in registers), to LDS;
+//   2. their horizontal windows (MFMA), SSIM and its derivatives with respect
+//      to the windowed sums x, x^2 + y^2 and xy, scaled by coef M(p) (coef =
+//      -lambda w0 / (3 P_v)), to LDS;
+//   3. the horizontal windows of those three maps, their vertical windows, and
+//      grad += B_mu + 2 x B_xx + y B_xy (the window is symmetric, so the
+//      adjoint is the same filter).
+// Step t's new rows complete windows 5 rows up and gradients 10 rows up.
+// Bound by instruction issue: 160 vector instructions and 12 MFMA a column and
+// row, of which the four vertical and three adjoint windows are 77; with the
+// horizontal windows on the vector unit too it took 325 us for eight 1200x680
+// views (register and LDS use left two wavefronts a SIMD), now 245, and the
+// two tile kernels, which move 9 maps of every pixel through memory, 354.
+template <int BW, int R>
+__global__ void __launch_bounds__(BW) __attribute__((amdgpu_waves_per_eu(3)))
+k_ssim(const float* __restrict__ out, const float* __restrict__ rgb_t, int64_t P, const gs_view* __restrict__ views,
+       SsimStrips pl, SsimConst sc, const uint8_t* __restrict__ masks, int use_obs, float* __restrict__ grad_out,
+       double* __restrict__ partials) {
+    constexpr int LD = BW + 2 * kSsimPad + 4;  // column c at kSsimPad + c
+    __shared__ float s_f[7][R][LD];
+    __shared__ double s_red[BW / kWave];
+    __shared__ int s_bad[2][2];  // [step's parity]: a sum, a map of the step is not finite
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    int v = 0;
+    while (v + 1 < pl.n_views && pl.first[v + 1] <= (int)blockIdx.x) ++v;
+    const int W = views[v].width, H = views[v].height;
+    const int64_t base = views[v].pixel_offset;
+    const int nx = ceil_div(W, BW - 4 * kSsimR);
+    int lt = blockIdx.x - pl.first[v];
+    const int x0 = lt % nx * (BW - 4 * kSsimR);
+    lt /= nx;
+    const int c = lt % 3, y0 = lt / 3 * pl.rows, y1 = min(y0 + pl.rows, H);
+    const float* X = out + c * P + base;
+    const float* Y = rgb_t + c * P + base;
+    float* G = grad_out + c * P + base;
+    const uint8_t* M = masks + base;
+    const int gx = x0 - 2 * kSsimR + tid;
+    const bool col_in = gx >= 0 && gx < W, col_own = col_in && tid >= 2 * kSsimR && tid < BW - 2 * kSsimR;
+    const int gxc = col_in ? gx : 0;
+    float band[kSsimK];
+#pragma unroll
+    for (int s = 0; s < kSsimK; ++s) {
+        const int tp = 4 * s + (lane >> 4) - (lane & 15);
+        band[s] = 0.0f;
+#pragma unroll
+        for (int k = 0; k <= 2 * kSsimR; ++k) band[s] = tp == k ? sc.g[k] : band[s];
+    }
+    for (int k = tid; k < 7 * R * 2 * kSsimPad; k += BW) {  // the columns outside the block: zeros
+        const int e = k % (2 * kSsimPad);
+        s_f[k / (2 * kSsimPad) / R][k / (2 * kSsimPad) % R][e < kSsimPad ? e : BW + e] = 0.0f;
+    }
+    if (tid < 4) s_bad[tid >> 1][tid & 1] = 0;
+    __syncthreads();
+    const float Pv = (float)((int64_t)W * H);
+    const float coef = -sc.lam_w0 / (3.0f * Pv);
+    const int steps = ceil_div(y1 - y0 + 4 * kSsimR, R);
+
+    // the row's offset, rows outside the view at its edge (loaded, not used)
+    auto row = [&](int r) { return (int64_t)(r < 0 ? 0 : (r < H ? r : H - 1)) * W; };
+    float xn[R], yn[R];
+    auto load_rows = [&](int t) {
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const int64_t o = row(y0 - 2 * kSsimR + t * R + i);
+            xn[i] = (X + o)[gxc];
+            yn[i] = (Y + o)[gxc];
+        }
+    };
+    load_rows(0);
+    float va[4][2 * kSsimR], vb[3][2 * kSsimR];
+#pragma unroll
+    for (int k = 0; k < 2 * kSsimR; ++k) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) va[q][k] = 0.0f;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) vb[q][k] = 0.0f;
+    }
+    double acc = 0.0;  // sum of M(p) (1 - s(p)) over the block's own pixels
+    for (int t = 0; t < steps; ++t) {
+        const int r0 = y0 - 2 * kSsimR + t * R;  // first of the new rows
+        bool bad = false;
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const bool in = col_in && r0 + i >= 0 && r0 + i < H;
+            const float x = in ? xn[i] - kSsimMid : -kSsimMid, y = in ? yn[i] - kSsimMid : -kSsimMid;
+            const float sq = window_row(sc, fmaf(x, x, y * y), va[2]);
+            s_f[0][i][kSsimPad + tid] = window_row(sc, x, va[0]);
+            s_f[1][i][kSsimPad + tid] = window_row(sc, y, va[1]);
+            s_f[2][i][kSsimPad + tid] = sq;
+            s_f[3][i][kSsimPad + tid] = window_row(sc, x * y, va[3]);
+            bad |= !(sq < INFINITY);
+        }
+        if (t + 1 < steps) load_rows(t + 1);  // in flight while this step is filtered
+        if ((t + 1) * R <= 2 * kSsimR) continue;  // windows that no gradient of the strip needs
+        // x, y and the gradient so far at the rows that this step completes
+        const bool done = (t + 1) * R > 4 * kSsimR;
+        float xo[R], yo[R], go[R];
+        if (done) {
+#pragma unroll
+            for (int i = 0; i < R; ++i) {
+                const int64_t o = row(r0 - 2 * kSsimR + i);
+                xo[i] = (X + o)[gxc];
+                yo[i] = (Y + o)[gxc];
+                go[i] = (G + o)[gxc];
+            }
+        }
+        int mn[R];
+        if (use_obs) {
+#pragma unroll
+            for (int i = 0; i < R; ++i) mn[i] = (M + row(r0 - kSsimR + i))[gxc];
+        }
+        if (__any(bad)) s_bad[t & 1][0] = 1;
+        __syncthreads();
+        if (tid < 2) s_bad[(t + 1) & 1][tid] = 0;  // read before this barrier, written after the next one
+        {
+            const bool finite = s_bad[t & 1][0] == 0;
+            float f[4][R], part = 0.0f;
+            window_cols(sc, s_f, band, finite, f);
+            bad = false;
+#pragma unroll
+            for (int i = 0; i < R; ++i) {
+                const int m = r0 - kSsimR + i;
+                const float ux = f[0][i], uy = f[1][i], mx = ux + kSsimMid, my = uy + kSsimMid;
+                // differences of nearly equal numbers: the products unrounded
+                const float vs = fmaf(-uy, uy, fmaf(-ux, ux, f[2][i])), cxy = fmaf(-ux, uy, f[3][i]);
+                const float N1 = 2.0f * (mx * my) + sc.c1, N2 = 2.0f * cxy + sc.c2;
+                const float D1 = (mx * mx + my * my) + sc.c1, D2 = vs + sc.c2;
+                // hardware reciprocals: ~1 ulp, far inside the loss tolerance
+                const float iD1 = __builtin_amdgcn_rcpf(D1), iD2 = __builtin_amdgcn_rcpf(D2);
+                const float iD12 = iD1 * iD2;
+                const float s = N1 * N2 * iD12;
+                const float mk = !use_obs || (mn[i] & 1) ? 1.0f : 0.0f, k1 = coef * mk;
+                const bool in = col_in && m >= 0 && m < H;
+                // partials of s with the other windowed sums fixed
+                const float d_mu = 2.0f * (my * N2 - uy * N1) * iD12 + 2.0f * s * (ux * iD2 - mx * iD1);
+                const float d_xx = -s * iD2;
+                const float d_xy = 2.0f * N1 * iD12;
+                part += col_own && m >= y0 && m < y1 ? mk * (1.0f - s) : 0.0f;
+                const float m0 = in ? k1 * d_mu : 0.0f, m1 = in ? k1 * d_xx : 0.0f, m2 = in ? k1 * d_xy : 0.0f;
+                bad |= !(fabsf(m0) + fabsf(m1) + fabsf(m2) < INFINITY);
+                s_f[4][i][kSsimPad + tid] = m0;
+                s_f[5][i][kSsimPad + tid] = m1;
+                s_f[6][i][kSsimPad + tid] = m2;
+            }
+            acc += (double)part;
+            if (__any(bad)) s_bad[t & 1][1] = 1;
+        }
+        __syncthreads();
+        {
+            const bool finite = s_bad[t & 1][1] == 0;
+            float b[3][R];
+            window_cols(sc, s_f + 4, band, finite, b);
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+#pragma unroll
+                for (int i = 0; i < R; ++i) b[k][i] = window_row(sc, b[k][i], vb[k]);
+            if (done && col_own) {
+#pragma unroll
+                for (int i = 0; i < R; ++i) {
+                    const int r = r0 - 2 * kSsimR + i;
+                    if (r >= y0 && r < y1)
+                        (G + (int64_t)r * W)[gx] = go[i] + (b[0][i] + 2.0f * (xo[i] - kSsimMid) * b[1][i] + (yo[i] - kSsimMid) * b[2][i]);
+                }
+            }
+        }
+    }
+    acc *= (double)sc.lam_w0 / (3.0 * (double)Pv);
+    for (int d = kWave / 2; d > 0; d >>= 1) acc += __shfl_xor(acc, d, kWave);
+    if (lane == 0) s_red[wave] = acc;
+    __syncthreads();
+    if (tid == 0) {
+        double a = 0;
+        for (int w = 0; w < BW / kWave; ++w) a += s_red[w];
+        partials[blockIdx.x] = a;
+    }
+}
+
 // ---------------------------------------------------------------------------
 // 4. fixed-order sum: loss = (colour L1, SSIM, depth, semantic, total)
 // ---------------------------------------------------------------------------
@@ -1114,6 +1374,35 @@ int ssim_tiles(const gs_view* views, int n_views, SsimTiles* st) {
     return t;
 }
 
+int strip_blocks(const gs_view* views, int n_views, int rows, SsimStrips* pl) {
+    int t = 0;
+    for (int v = 0; v < n_views; ++v) {
+        if (pl) pl->first[v] = t;
+        t += 3 * ceil_div(views[v].width, kStripBW - 4 * kSsimR) * ceil_div(views[v].height, rows);
+    }
+    if (pl) {
+        pl->first[n_views] = t;
+        pl->n_views = n_views;
+        pl->rows = rows;
+    }
+    return t;
+}
+
+// Output rows of a strip, or 0: the tiles (k_ssim_fwd, k_ssim_bwd).  A strip
+// filters 20 rows more than it owns and a workgroup alone on its CU takes
+// 2.7 us for four rows, so strips pay where there are two for every CU
+// (tiles/strips, SSIM of both directions in us: 320x240 11/17, 640x480 25/31,
+// eight 320x240 28/45, 1200x680 54/49, four 640x480 76/63, two, four and eight
+// 1200x680 92/83, 180/136 and 354/245), and have as few rows as leave all
+// workgroups resident (three a CU), at most 72 (eight 1200x680: 24 rows 278,
+// 40 238, 72 233, 96 259).
+int strip_rows(const gs_view* views, int n_views) {
+    int rows = 24;
+    if (strip_blocks(views, n_views, rows, nullptr) < 2 * 256) return 0;
+    while (rows < 72 && strip_blocks(views, n_views, rows, nullptr) > 3 * 256) rows += 16;
+    return rows;
+}
+
 // Decoder-gradient reduction: the pixel kernel's block partials, block-major
 // [nblk][T] floats (T = F K + K), are summed in fixed order by chunks of
 // kRowChunk rows (k_rows_stage, doubles [nchunk][T]), then over the chunks
@@ -1135,9 +1424,12 @@ SlamWs slam_layout(int64_t P, const gs_view* views, int n_views, bool ssim, int 
     const int64_t nblk = slam_blocks(P);
     L.part = o;
     o += align256((size_t)nblk * 3 * 8);
-    const int nt = ssim ? ssim_tiles(views, n_views, nullptr) : 0;
+    // one partial per SSIM workgroup (of tiles: at most three times their number, rounded up to 8)
+    const int rows = ssim ? strip_rows(views, n_views) : 0;
+    const int nssim = rows > 0 ? strip_blocks(views, n_views, rows, nullptr)
+                               : 3 * (ssim ? ssim_tiles(views, n_views, nullptr) : 0) + 8;
     L.spart = o;
-    o += align256((size_t)(3 * nt + 8) * 8);  // one partial per SSIM workgroup (at most 3 nt rounded up to 8)
+    o += align256((size_t)nssim * 8);
     L.stage = o;
     o += align256((size_t)sum_stage_blocks(nblk) * 3 * 8);
     L.wt = o;
@@ -1145,7 +1437,7 @@ SlamWs slam_layout(int64_t P, const gs_view* views, int n_views, bool ssim, int 
     L.mask = o;
     o += align256((size_t)P);
     L.maps = o;
-    if (ssim) o += align256((size_t)9 * P * 4);
+    if (ssim && rows == 0) o += align256((size_t)9 * P * 4);
     L.dpart = o;
     o += align256((size_t)nblk * dec_terms * 4);
     L.dstage = o;
@@ -1338,8 +1630,6 @@ hipError_t launch_slam_t(const float* out, const float* rgb_t, const float* dept
     // 3. SSIM
     int nssim = 0;
     if (ssim) {
-        SsimTiles st;
-        const int nt = ssim_tiles(views_host, n_views, &st);
         SsimConst sc;
         double g[2 * kSsimR + 1], tot = 0.0;
         for (int t = 0; t <= 2 * kSsimR; ++t) {
@@ -1351,16 +1641,26 @@ hipError_t launch_slam_t(const float* out, const float* rgb_t, const float* dept
         sc.c1 = (float)(0.01 * 0.01);
         sc.c2 = (float)(0.03 * 0.03);
         sc.lam_w0 = o.ssim_lambda * o.w_color;
-        // persistent grids walking the (channel, tile) items
-        const unsigned gf = ssim_grid(reinterpret_cast<const void*>(&k_ssim_fwd), 3 * nt);
-        const unsigned gb = ssim_grid(reinterpret_cast<const void*>(&k_ssim_bwd), 3 * nt);
-        if (nt > 0) {
-            hipLaunchKernelGGL(k_ssim_fwd, dim3(gf), dim3(kSlamThreads), 0, s, out, rgb_t, P, views_dev, st, sc, mk,
-                               sp.use_obs, maps, spart);
-            hipLaunchKernelGGL(k_ssim_bwd, dim3(gb), dim3(kSlamThreads), 0, s, out, rgb_t, P, views_dev, st, sc, maps,
-                               grad_out);
+        const int rows = strip_rows(views_host, n_views);
+        if (rows > 0) {
+            SsimStrips pl;
+            nssim = strip_blocks(views_host, n_views, rows, &pl);
+            hipLaunchKernelGGL((k_ssim<kStripBW, kStripR>), dim3((unsigned)nssim), dim3(kStripBW), 0, s, out, rgb_t, P,
+                               views_dev, pl, sc, mk, sp.use_obs, grad_out, spart);
+        } else {
+            SsimTiles st;
+            const int nt = ssim_tiles(views_host, n_views, &st);
+            // persistent grids walking the (channel, tile) items
+            const unsigned gf = ssim_grid(reinterpret_cast<const void*>(&k_ssim_fwd), 3 * nt);
+            const unsigned gb = ssim_grid(reinterpret_cast<const void*>(&k_ssim_bwd), 3 * nt);
+            if (nt > 0) {
+                hipLaunchKernelGGL(k_ssim_fwd, dim3(gf), dim3(kSlamThreads), 0, s, out, rgb_t, P, views_dev, st, sc,
+                                   mk, sp.use_obs, maps, spart);
+                hipLaunchKernelGGL(k_ssim_bwd, dim3(gb), dim3(kSlamThreads), 0, s, out, rgb_t, P, views_dev, st, sc,
+                                   maps, grad_out);
+            }
+            nssim = nt > 0 ? (int)gf : 0;
         }
-        nssim = nt > 0 ? (int)gf : 0;
     }
     // 4. loss terms: the per-block partials summed in a fixed order, in two
     // stages where there are many
