@@ -1390,15 +1390,15 @@ int strip_blocks(const gs_view* views, int n_views, int rows, SsimStrips* pl) {
 
 // Output rows of a strip, or 0: the tiles (k_ssim_fwd, k_ssim_bwd).  A strip
 // filters 20 rows more than it owns and a workgroup alone on its CU takes
-// 2.7 us for four rows, so strips pay where there are two for every CU
-// (tiles/strips, SSIM of both directions in us: 320x240 11/17, 640x480 25/31,
-// eight 320x240 28/45, 1200x680 54/49, four 640x480 76/63, two, four and eight
-// 1200x680 92/83, 180/136 and 354/245), and have as few rows as leave all
-// workgroups resident (three a CU), at most 72 (eight 1200x680: 24 rows 278,
-// 40 238, 72 233, 96 259).
+// 2.7 us for four rows, so strips pay where short ones (24 rows) would be more
+// than the three for every CU that are resident (tiles/strips, SSIM of both
+// directions in us: 320x240 11/17, 640x480 25/31, eight 320x240 28/45,
+// 1200x680 54/49, two, four and eight 1200x680 92/83, 180/136 and 354/245), and
+// have as few rows as leave all workgroups resident, at most 72 (eight
+// 1200x680: 24 rows 278, 40 238, 72 233, 96 259).
 int strip_rows(const gs_view* views, int n_views) {
-    int rows = 24;
-    if (strip_blocks(views, n_views, rows, nullptr) < 2 * 256) return 0;
+    if (strip_blocks(views, n_views, 24, nullptr) <= 3 * 256) return 0;
+    int rows = 40;
     while (rows < 72 && strip_blocks(views, n_views, rows, nullptr) > 3 * 256) rows += 16;
     return rows;
 }

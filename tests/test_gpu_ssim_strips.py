@@ -49,17 +49,19 @@ def _loss(sizes, out, rgb, dep, o):
     return r.grad_out.cpu().numpy(), r.slam_terms.cpu().numpy()
 
 
-def _images(copies):
-    sizes = SIZES * copies
+TALL = [(473, 145), (237, 73), (1, 1)]
+
+
+def _images(sizes):
     rng = np.random.default_rng(5)
     li = wl.loss_images(rng, sizes, 0, 0)
     return sizes, li.out, li.rgb_t, li.depth_t
 
 
 @pytest.mark.parametrize("use_obs", [False, True])
-@pytest.mark.parametrize("copies", [3, 5])  # strips of 24 and of 40 rows
-def test_strips_against_tiles(copies, use_obs):
-    sizes, out, rgb, dep = _images(copies)
+@pytest.mark.parametrize("sizes", [SIZES * 4, TALL * 18, [(1200, 680)] * 8], ids=["40", "56", "72"])  # rows of a strip
+def test_strips_against_tiles(sizes, use_obs):
+    sizes, out, rgb, dep = _images(sizes)
     o = _opts(use_obs)
     g, terms = _loss(sizes, out, rgb, dep, o)
     total, off = 0.0, 0
@@ -74,7 +76,7 @@ def test_strips_against_tiles(copies, use_obs):
 
 
 def test_strips_against_oracle():
-    sizes, out, rgb, dep = _images(3)
+    sizes, out, rgb, dep = _images(SIZES * 4)
     o = _opts(False)
     g, terms = _loss(sizes, out, rgb, dep, o)
     oo = oracle.SlamLossOpts(w_color=o.w_color, w_depth=o.w_depth, w_sem=0.0, ssim_lambda=o.ssim_lambda,
@@ -87,7 +89,7 @@ def test_strips_against_oracle():
 
 @pytest.mark.parametrize("value", [np.nan, np.inf])
 def test_not_finite(value):
-    sizes, out, rgb, dep = _images(3)
+    sizes, out, rgb, dep = _images(SIZES * 4)
     o = _opts(False)
     off = sum(W * H for W, H in sizes[:9])  # the 1200x73 view
     W, H = sizes[9]
