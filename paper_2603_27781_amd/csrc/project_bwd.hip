@@ -255,7 +255,7 @@ __global__ void __launch_bounds__(kPbThreads) k_project_bwd(GaussPtrs g, const g
 }
 
 // Twist contributions per (view, Gaussian), reduced per block in FP64.  A
-// block takes kPoseChunk consecutive Gaussians of one view.  Few pairs are
+// block takes kPoseThreads * GPT consecutive Gaussians of one view.  Few pairs are
 // visible (under a tenth at the mapping workloads), so the block first lists
 // the pairs with a nonzero 2D gradient in LDS, in index order (thread t
 // screens Gaussians t, t + 256, ..., each round coalesced, ranked with
@@ -264,32 +264,60 @@ __global__ void __launch_bounds__(kPbThreads) k_project_bwd(GaussPtrs g, const g
 // works on a visible pair instead of one in ten.  Each thread sums its
 // entries in list order and the block sums the threads in a fixed order.
 constexpr int kPoseThreads = 256;
-constexpr int kPoseGPT = 8;  // Gaussians screened per thread
-constexpr int kPoseChunk = kPoseThreads * kPoseGPT;
+// Gaussians screened per thread: 4 (16 views of 2 M Gaussians: 267 us, 282 with
+// 8), 2 where 8 would leave fewer than four workgroups for every CU (1200x680
+// with 1 M Gaussians 19 -> 14 us, 320x240 with 60 k 12 -> 6, 2 k Gaussians, one
+// workgroup of 2048 before, 15 -> 6), and 8 where the partials of 4 would come
+// near the fixed scratch array's 8 MB: what fitted there still does.
+int pose_gpt(int n, int n_views) {
+    const int64_t blocks = (int64_t)ceil_div(n > 0 ? n : 1, 8 * kPoseThreads) * n_views;
+    return blocks < 4 * 256 ? 2 : (blocks <= 65536 ? 4 : 8);
+}
+template <int GPT>
 __global__ void __launch_bounds__(kPoseThreads) k_pose_partial(GaussPtrs g, const gs_view* __restrict__ views,
                                                                float blur, const int32_t* __restrict__ touched,
                                                                const float4* __restrict__ grad_geo,
                                                                double* __restrict__ partials, int nblk) {
-    __shared__ int s_list[kPoseChunk];
-    __shared__ uint32_t s_tmp[kPoseThreads / kWave];
-    __shared__ double s_red[6][kPoseThreads / kWave];
+    constexpr int kChunk = kPoseThreads * GPT, kWaves = kPoseThreads / kWave;
+    __shared__ int s_list[kChunk];
+    __shared__ uint32_t s_count[GPT][kWaves];
+    __shared__ double s_red[6][kWaves];
     const int n = g.n;
     const int v = blockIdx.y;
-    const int tid = threadIdx.x;
-    const int base = blockIdx.x * kPoseChunk;
-    uint32_t count = 0;
-    for (int k = 0; k < kPoseGPT; ++k) {
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int base = blockIdx.x * kChunk;
+    // all loads of a kind in flight together: two round trips for the block
+    bool keep[GPT];
+#pragma unroll
+    for (int k = 0; k < GPT; ++k) {
         const int i = base + k * kPoseThreads + tid;
-        bool keep = false;
-        if (i < n && touched[(size_t)v * n + i] > 0) {
-            const size_t o = (size_t)v * n + i;
-            keep = nonzero(grad_geo[2 * o], grad_geo[2 * o + 1]);
-        }
-        uint32_t tot;
-        const uint32_t rank = block_exclusive<kPoseThreads>(keep ? 1u : 0u, s_tmp, &tot);
-        if (keep) s_list[count + rank] = i;
-        count += tot;
+        keep[k] = touched[(size_t)v * n + (i < n ? i : n - 1)] > 0 && i < n;
     }
+    float4 a[GPT], b[GPT];
+#pragma unroll
+    for (int k = 0; k < GPT; ++k)
+        if (keep[k]) {
+            const size_t o = (size_t)v * n + base + k * kPoseThreads + tid;
+            a[k] = grad_geo[2 * o];
+            b[k] = grad_geo[2 * o + 1];
+        }
+    uint64_t set[GPT];
+#pragma unroll
+    for (int k = 0; k < GPT; ++k) {
+        keep[k] = keep[k] && nonzero(a[k], b[k]);
+        set[k] = __ballot(keep[k]);
+        if (lane == 0) s_count[k][wave] = (uint32_t)__popcll(set[k]);
+    }
+    __syncthreads();
+    uint32_t count = 0;
+#pragma unroll
+    for (int k = 0; k < GPT; ++k)
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            if (w == wave && keep[k])
+                s_list[count + __popcll(set[k] & ((1ull << lane) - 1))] = base + k * kPoseThreads + tid;
+            count += s_count[k][w];
+        }
     __syncthreads();
     double tw[6] = {0, 0, 0, 0, 0, 0};
     const gs_view& vw = views[v];
@@ -332,7 +360,6 @@ __global__ void __launch_bounds__(kPoseThreads) k_pose_partial(GaussPtrs g, cons
         tw[4] += (double)(p[2] * dp[0] - p[0] * dp[2]) + 2.0 * (double)(SG(2, 0) - GS(2, 0));
         tw[5] += (double)(p[0] * dp[1] - p[1] * dp[0]) + 2.0 * (double)(SG(0, 1) - GS(0, 1));
     }
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     for (int k = 0; k < 6; ++k) {
         double x = tw[k];
         for (int d = kWave / 2; d > 0; d >>= 1) x += __shfl_xor(x, d, kWave);
@@ -383,16 +410,22 @@ hipError_t launch_project_bwd(const GaussPtrs& g, const gs_view* views_dev, int 
 }
 
 size_t pose_workspace_bytes(int n, int n_views) {
-    const size_t nblk = (size_t)ceil_div(n > 0 ? n : 1, kPoseChunk);
-    return nblk * (size_t)n_views * 6 * sizeof(double);
+    const int gpt = pose_gpt(n, n_views);
+    size_t nblk = (size_t)ceil_div(n > 0 ? n : 1, kPoseThreads * gpt) * (size_t)n_views;
+    // never less than fewer Gaussians or views take: a workspace sized for a
+    // map's capacity serves the map while it grows
+    const size_t least = gpt == 2 ? 0 : (gpt == 4 ? 4 * 4 * 256 : 2 * 65536);
+    if (nblk < least) nblk = least;
+    return nblk * 6 * sizeof(double);
 }
 
 hipError_t launch_pose_grad(const GaussPtrs& g, const gs_view* views_dev, int n_views, const RasterConst& c,
                             const int32_t* touched, const float* grad_geo, void* ws, float* twist, hipStream_t s) {
-    const int nblk = ceil_div(g.n > 0 ? g.n : 1, kPoseChunk);
+    const int gpt = pose_gpt(g.n, n_views), nblk = ceil_div(g.n > 0 ? g.n : 1, kPoseThreads * gpt);
     double* partials = static_cast<double*>(ws);
-    hipLaunchKernelGGL(k_pose_partial, dim3((unsigned)nblk, (unsigned)n_views), dim3(kPoseThreads), 0, s, g, views_dev,
-                       c.blur, touched, reinterpret_cast<const float4*>(grad_geo), partials, nblk);
+    auto kern = gpt == 8 ? k_pose_partial<8> : (gpt == 4 ? k_pose_partial<4> : k_pose_partial<2>);
+    hipLaunchKernelGGL(kern, dim3((unsigned)nblk, (unsigned)n_views), dim3(kPoseThreads), 0, s, g, views_dev, c.blur,
+                       touched, reinterpret_cast<const float4*>(grad_geo), partials, nblk);
     hipLaunchKernelGGL(k_pose_final, dim3((unsigned)n_views), dim3(256), 0, s, partials, nblk, twist);
     return hipGetLastError();
 }
