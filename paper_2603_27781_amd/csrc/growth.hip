@@ -370,7 +370,10 @@ static int dsr_blocks(int64_t m) {
 
 size_t dsr_workspace_bytes(int64_t n) {
     if (n <= 0) return 0;
-    return ((size_t)dsr_blocks(3 * n) * 7 * 8 + 255) / 256 * 256;  // moments [nb][3], sets [nb][4]
+    // moments [nb][3], sets [nb][4]; all kDsrBlocks from there on, so that a
+    // workspace sized for more Gaussians serves fewer
+    const int64_t chunks = dsr_chunks(3 * n);
+    return ((size_t)(chunks < kDsrBlocks ? chunks : kDsrBlocks) * 7 * 8 + 255) / 256 * 256;
 }
 
 hipError_t launch_dsr(const float* log_scale, int64_t n, float w_big, float w_small, float* grad_ls, double* out,

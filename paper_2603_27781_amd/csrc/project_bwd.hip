@@ -255,49 +255,46 @@ __global__ void __launch_bounds__(kPbThreads) k_project_bwd(GaussPtrs g, const g
 }
 
 // Twist contributions per (view, Gaussian), reduced per block in FP64.  A
-// block takes kPoseThreads * GPT consecutive Gaussians of one view.  Few pairs are
+// block takes kPoseChunk consecutive Gaussians of one view.  Few pairs are
 // visible (under a tenth at the mapping workloads), so the block first lists
 // the pairs with a nonzero 2D gradient in LDS, in index order (thread t
-// screens Gaussians t, t + 256, ..., each round coalesced, ranked with
+// screens Gaussians t, t + THREADS, ..., each round coalesced, ranked with
 // ballots and per-wavefront counts), and then its threads take the listed
-// pairs, entry e by thread e mod 256: every lane of the projection backward
+// pairs, entry e by thread e mod THREADS: every lane of the projection backward
 // works on a visible pair instead of one in ten.  Each thread sums its
 // entries in list order and the block sums the threads in a fixed order.
-constexpr int kPoseThreads = 256;
-// Gaussians screened per thread: 4 (16 views of 2 M Gaussians: 267 us, 282 with
-// 8), 2 where 8 would leave fewer than four workgroups for every CU (1200x680
-// with 1 M Gaussians 19 -> 14 us, 320x240 with 60 k 12 -> 6, 2 k Gaussians, one
-// workgroup of 2048 before, 15 -> 6), and 8 where the partials of 4 would come
-// near the fixed scratch array's 8 MB: what fitted there still does.
-int pose_gpt(int n, int n_views) {
-    const int64_t blocks = (int64_t)ceil_div(n > 0 ? n : 1, 8 * kPoseThreads) * n_views;
-    return blocks < 4 * 256 ? 2 : (blocks <= 65536 ? 4 : 8);
-}
-template <int GPT>
-__global__ void __launch_bounds__(kPoseThreads) k_pose_partial(GaussPtrs g, const gs_view* __restrict__ views,
-                                                               float blur, const int32_t* __restrict__ touched,
-                                                               const float4* __restrict__ grad_geo,
-                                                               double* __restrict__ partials, int nblk) {
-    constexpr int kChunk = kPoseThreads * GPT, kWaves = kPoseThreads / kWave;
-    __shared__ int s_list[kChunk];
+constexpr int kPoseChunk = 2048;
+// Threads that share a chunk: 512 (16 views of 2 M Gaussians: 276 us with 256
+// and eight dependent rounds of screening, now 271), 1024 where there are fewer
+// than four chunks for every CU (1200x680 with 1 M Gaussians 19 -> 16 us,
+// 320x240 with 60 k 12 -> 9, 2 k Gaussians, which are one chunk, 15 -> 11;
+// smaller chunks, 6 us there, would take a larger workspace).
+int pose_threads(int nblk, int n_views) { return (int64_t)nblk * n_views < 4 * 256 ? 1024 : 512; }
+template <int THREADS>
+__global__ void __launch_bounds__(THREADS) k_pose_partial(GaussPtrs g, const gs_view* __restrict__ views, float blur,
+                                                          const int32_t* __restrict__ touched,
+                                                          const float4* __restrict__ grad_geo,
+                                                          double* __restrict__ partials, int nblk) {
+    constexpr int GPT = kPoseChunk / THREADS, kWaves = THREADS / kWave;
+    __shared__ int s_list[kPoseChunk];
     __shared__ uint32_t s_count[GPT][kWaves];
     __shared__ double s_red[6][kWaves];
     const int n = g.n;
     const int v = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int base = blockIdx.x * kChunk;
+    const int base = blockIdx.x * kPoseChunk;
     // all loads of a kind in flight together: two round trips for the block
     bool keep[GPT];
 #pragma unroll
     for (int k = 0; k < GPT; ++k) {
-        const int i = base + k * kPoseThreads + tid;
+        const int i = base + k * THREADS + tid;
         keep[k] = touched[(size_t)v * n + (i < n ? i : n - 1)] > 0 && i < n;
     }
     float4 a[GPT], b[GPT];
 #pragma unroll
     for (int k = 0; k < GPT; ++k)
         if (keep[k]) {
-            const size_t o = (size_t)v * n + base + k * kPoseThreads + tid;
+            const size_t o = (size_t)v * n + base + k * THREADS + tid;
             a[k] = grad_geo[2 * o];
             b[k] = grad_geo[2 * o + 1];
         }
@@ -315,13 +312,13 @@ __global__ void __launch_bounds__(kPoseThreads) k_pose_partial(GaussPtrs g, cons
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) {
             if (w == wave && keep[k])
-                s_list[count + __popcll(set[k] & ((1ull << lane) - 1))] = base + k * kPoseThreads + tid;
+                s_list[count + __popcll(set[k] & ((1ull << lane) - 1))] = base + k * THREADS + tid;
             count += s_count[k][w];
         }
     __syncthreads();
     double tw[6] = {0, 0, 0, 0, 0, 0};
     const gs_view& vw = views[v];
-    for (uint32_t e = tid; e < count; e += kPoseThreads) {
+    for (uint32_t e = tid; e < count; e += THREADS) {
         const int i = s_list[e];
         const size_t o = (size_t)v * n + i;
         const float4 g0 = grad_geo[2 * o], g1 = grad_geo[2 * o + 1];
@@ -410,22 +407,17 @@ hipError_t launch_project_bwd(const GaussPtrs& g, const gs_view* views_dev, int 
 }
 
 size_t pose_workspace_bytes(int n, int n_views) {
-    const int gpt = pose_gpt(n, n_views);
-    size_t nblk = (size_t)ceil_div(n > 0 ? n : 1, kPoseThreads * gpt) * (size_t)n_views;
-    // never less than fewer Gaussians or views take: a workspace sized for a
-    // map's capacity serves the map while it grows
-    const size_t least = gpt == 2 ? 0 : (gpt == 4 ? 4 * 4 * 256 : 2 * 65536);
-    if (nblk < least) nblk = least;
-    return nblk * 6 * sizeof(double);
+    const size_t nblk = (size_t)ceil_div(n > 0 ? n : 1, kPoseChunk);
+    return nblk * (size_t)n_views * 6 * sizeof(double);
 }
 
 hipError_t launch_pose_grad(const GaussPtrs& g, const gs_view* views_dev, int n_views, const RasterConst& c,
                             const int32_t* touched, const float* grad_geo, void* ws, float* twist, hipStream_t s) {
-    const int gpt = pose_gpt(g.n, n_views), nblk = ceil_div(g.n > 0 ? g.n : 1, kPoseThreads * gpt);
+    const int nblk = ceil_div(g.n > 0 ? g.n : 1, kPoseChunk), threads = pose_threads(nblk, n_views);
     double* partials = static_cast<double*>(ws);
-    auto kern = gpt == 8 ? k_pose_partial<8> : (gpt == 4 ? k_pose_partial<4> : k_pose_partial<2>);
-    hipLaunchKernelGGL(kern, dim3((unsigned)nblk, (unsigned)n_views), dim3(kPoseThreads), 0, s, g, views_dev, c.blur,
-                       touched, reinterpret_cast<const float4*>(grad_geo), partials, nblk);
+    auto kern = threads == 1024 ? k_pose_partial<1024> : k_pose_partial<512>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)nblk, (unsigned)n_views), dim3((unsigned)threads), 0, s, g, views_dev,
+                       c.blur, touched, reinterpret_cast<const float4*>(grad_geo), partials, nblk);
     hipLaunchKernelGGL(k_pose_final, dim3((unsigned)n_views), dim3(256), 0, s, partials, nblk, twist);
     return hipGetLastError();
 }

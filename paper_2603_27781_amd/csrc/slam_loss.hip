@@ -1424,12 +1424,13 @@ SlamWs slam_layout(int64_t P, const gs_view* views, int n_views, bool ssim, int 
     const int64_t nblk = slam_blocks(P);
     L.part = o;
     o += align256((size_t)nblk * 3 * 8);
-    // one partial per SSIM workgroup (of tiles: at most three times their number, rounded up to 8)
-    const int rows = ssim ? strip_rows(views, n_views) : 0;
-    const int nssim = rows > 0 ? strip_blocks(views, n_views, rows, nullptr)
-                               : 3 * (ssim ? ssim_tiles(views, n_views, nullptr) : 0) + 8;
+    // one partial per SSIM workgroup: of tiles at most three times their number
+    // rounded up to 8, of strips (larger than a tile either way) fewer; the
+    // maps of the tiles also where a call takes strips, so that a workspace
+    // sized for many views serves fewer
+    const int nt = ssim ? ssim_tiles(views, n_views, nullptr) : 0;
     L.spart = o;
-    o += align256((size_t)nssim * 8);
+    o += align256((size_t)(3 * nt + 8) * 8);
     L.stage = o;
     o += align256((size_t)sum_stage_blocks(nblk) * 3 * 8);
     L.wt = o;
@@ -1437,7 +1438,7 @@ SlamWs slam_layout(int64_t P, const gs_view* views, int n_views, bool ssim, int 
     L.mask = o;
     o += align256((size_t)P);
     L.maps = o;
-    if (ssim && rows == 0) o += align256((size_t)9 * P * 4);
+    if (ssim) o += align256((size_t)9 * P * 4);
     L.dpart = o;
     o += align256((size_t)nblk * dec_terms * 4);
     L.dstage = o;

@@ -1,5 +1,5 @@
-"""gs_pose_grad over its ways to split the Gaussians into workgroups (512, 1024
-or 2048 a workgroup, by Gaussians times views): the same visible Gaussians
+"""gs_pose_grad over its two widths of a workgroup (1024 or 512 threads for 2048
+Gaussians, by Gaussians times views): the same visible Gaussians
 among more and more invisible ones, at the first and last index, around the
 workgroups' edges and at random.
 
