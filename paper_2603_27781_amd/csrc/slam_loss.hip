@@ -540,8 +540,11 @@ __global__ void __launch_bounds__(kSlamThreads)
         bool on = false;
         float scale = 0.0f, fv[F];
         if (p0 + tid < P) {
-            // with every other load of the pixel, before anything waits
-            const int lab = (labels + p0)[tid];
+            // with every other load of the pixel, before anything waits; no
+            // class at all for a label outside [0, K), as without the decoder
+            // gradients (the rows up to K4 are no classes either)
+            int lab = (labels + p0)[tid];
+            lab = lab < K ? lab : -1;
 #pragma unroll
             for (int f = 0; f < F; ++f) fv[f] = (out + (5 + f) * P + p0)[tid];
             PixelTerms t;
@@ -568,7 +571,7 @@ __global__ void __launch_bounds__(kSlamThreads)
                         zl = k0 + u == lab ? a[u] : zl;
                     }
                 }
-                const bool has = lab >= 0 && lab < K;
+                const bool has = lab >= 0;
                 float se = 0.0f, term = 0.0f, sdp = 0.0f, inv;
                 uint64_t live = 0;
                 if constexpr (!BCE) {

@@ -74,3 +74,46 @@ def test_decoder_gradients(F, K, bce):
         got, top = got.cpu().double(), float(want.abs().max())
         # one class: every gradient is exactly 0 up to rounding of the softmax
         assert float((got - want).abs().max()) <= tol * max(top, 1e-9), (float((got - want).abs().max()), top)
+
+
+@pytest.mark.parametrize("bce", [False, True])
+@pytest.mark.parametrize("K", [5, 6, 7, 8, 50])
+def test_labels_outside_the_classes_are_no_class(K, bce):
+    """Labels -1 and K .. K + 3 (void pixels) are no class: a BCE term has the
+    other classes' logarithms only, a cross-entropy none, and the gradients
+    are those of a softmax no class of which is the label; the features' equal
+    those of the call without decoder gradients.  1e-5 relative between the two
+    variants (the same binary32 formulas, summed differently), against FP64 the
+    tolerances above."""
+    from paper_2603_27781_amd import _lib, raster
+    F, P = 16, 300
+    g = torch.Generator().manual_seed(K)
+    r = raster.Rasterizer(1, F, raster.Views([wl.make_view(P, 1, 50.0, np.eye(4))], 16), raster.Config(), capacity=64)
+    r.out.copy_(torch.randn(5 + F, P, generator=g))
+    rgb, dep = torch.rand(3, P, generator=g).cuda(), torch.rand(P, generator=g).cuda()
+    labels = torch.arange(P, dtype=torch.int32) % (K + 5) - 1
+    W, b = torch.randn(F, K, generator=g) / 4, 0.1 * torch.randn(K, generator=g)
+    o = _lib.GsSlamLossOpts()
+    _lib.check(_lib.load().gs_default_slam_loss_opts(ctypes.byref(o)), "opts")
+    o.ssim_lambda, o.flags = 0.0, _lib.GS_LOSS_BCE if bce else 0
+    grads, terms = [], []
+    for dec in (False, True):
+        r.slam_loss(rgb, dep, labels.cuda(), W.cuda(), o, bias=b.cuda(), decoder_grads=dec)
+        torch.cuda.synchronize()
+        grads.append(r.grad_out.cpu().clone())
+        terms.append(float(r.slam_terms[3]))
+    assert float((grads[0] - grads[1]).abs().max()) <= 1e-5 * float(grads[0].abs().max())
+    z = r.out[5:].cpu().double().T @ W.double() + b.double()
+    p = torch.softmax(z, 1)
+    y = torch.zeros(P, K).double()
+    has = (labels >= 0) & (labels < K)
+    y[has] = torch.nn.functional.one_hot(labels[has].long(), K).double()
+    S = -(y * p.log() + ((1 - y) * (1 - p).log() if bce else 0)).sum()
+    dp = -y / p + (1 - y) / (1 - p)
+    dz = p * (dp - (p * dp).sum(1, keepdim=True)) if bce else p - y
+    w, tol = float(np.float32(o.w_sem)) / P, 2e-4 if bce else 2e-5
+    assert terms[1] == pytest.approx(w * float(S), rel=tol)
+    if bce:
+        assert terms[0] == pytest.approx(terms[1], rel=1e-5)
+    gW = w * r.out[5:].cpu().double() @ dz
+    assert float((r.grad_decoder_w.cpu().double() - gW).abs().max()) <= tol * float(gW.abs().max())
