@@ -186,7 +186,8 @@ constexpr int EM_ITEMS = 16;                         // pairs per lane and pass 
 constexpr int EM_PASS = EM_THREADS * EM_ITEMS;       // pairs per workgroup and pass at most
 constexpr int EM_RING = 2 * kWave;                   // queued visible pairs per wavefront
 constexpr int EM_LOOKBACK = 128;                     // up to this many chunks, offsets by look-back
-constexpr int EM_LDS_BYTES = 65536;                  // tile counters per workgroup at most (of 160 KB a CU)
+constexpr int EM_LDS_TILES = 32768;                  // 16-bit tile counters per workgroup at most (64 of 160 KB a CU)
+constexpr int64_t EM_CHUNK = 32768;                  // pairs of a chunk at most, so that they count to 16 bits
 constexpr int SC_WAVES = 16, SC_THREADS = SC_WAVES * kWave;
 constexpr int SC_MAXBLK = 4096;                      // blocks of k_tile_scan at most
 
@@ -199,24 +200,28 @@ struct BinState {
 };
 static_assert(sizeof(BinState) % 4 == 0, "cleared as words");
 
-// Clears the call's state and the give-up flag (with a kernel, not a memset,
-// so that graph replays stay correct).
-__device__ __forceinline__ void bin_reset(BinState* st, int64_t* counts) {
-    const int stride = (int)(gridDim.x * blockDim.x), i0 = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+// Clears the call's state, the give-up flag and the tiles' counters in memory,
+// if k_emit counts there (with a kernel, not a memset, so that graph replays
+// stay correct).
+__device__ __forceinline__ void bin_reset(BinState* st, int64_t* counts, uint32_t* tiles, int64_t n_tiles) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x, i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     uint32_t* w = reinterpret_cast<uint32_t*>(st);
-    for (int i = i0; i < (int)(sizeof(BinState) / 4); i += stride) w[i] = 0;
+    for (int64_t i = i0; i < (int64_t)(sizeof(BinState) / 4); i += stride) w[i] = 0;
+    for (int64_t i = i0; i < n_tiles; i += stride) tiles[i] = 0;
     if (i0 == 0) counts[3] = 0;
 }
 
-__global__ void __launch_bounds__(256) k_bin_reset(BinState* st, int64_t* counts) { bin_reset(st, counts); }
+__global__ void __launch_bounds__(256) k_bin_reset(BinState* st, int64_t* counts, uint32_t* tiles, int64_t n_tiles) {
+    bin_reset(st, counts, tiles, n_tiles);
+}
 
 // Instances and visible pairs of every chunk of pairs.
 __global__ void __launch_bounds__(EM_THREADS) k_chunk_sums(const int32_t* __restrict__ touched, int n, int per_view,
                                                            int64_t chunk, uint32_t* __restrict__ inst_sums,
                                                            uint32_t* __restrict__ vis_sums, BinState* st,
-                                                           int64_t* counts) {
+                                                           int64_t* counts, uint32_t* tiles, int64_t n_tiles) {
     __shared__ uint32_t s_w[2][EM_WAVES];
-    bin_reset(st, counts);
+    bin_reset(st, counts, tiles, n_tiles);
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const int v = (int)blockIdx.x / per_view;
     const int64_t i0 = (int64_t)((int)blockIdx.x - v * per_view) * chunk, i1 = min(i0 + chunk, (int64_t)n);
@@ -256,7 +261,6 @@ struct EmitArgs {
     int n, n_views, tile, per_view;  // per_view: chunks of each view
     int64_t chunk, capacity;
     int items;       // pairs per lane and pass
-    int window;      // tiles counted at once
     const uint32_t *inst_sums, *vis_sums;  // not read with the look-back
     BinState* st;
     uint32_t* table;
@@ -294,14 +298,16 @@ __device__ __forceinline__ int64_t table_row(const gs_view& vw, int per_view, in
 // max-scan over the wavefront (DPP) carries the latest mark to every later
 // slot.
 //
-// Counting in LDS and not in memory: a returning atomic per instance on
+// Counting in LDS where it can be: a returning atomic per instance on
 // counters in memory (eight sets, one per XCD) made this kernel 128 us at
 // eight 1200x680 views, 26 G atomics/s, against 57 us now.  The counters
 // are 16 bits wide (a pair is in a tile once, so a count is at most the
-// chunk's pairs), two to a word; WIDE, 32 bits, where a chunk has more pairs
-// than that.  A view of more tiles than the counters hold is counted in
-// several windows of tiles, the walk repeated for each.
-template <bool LOOKBACK, bool WIDE>
+// chunk's pairs), two to a word.  LDS false, for views of more tiles than that
+// holds (and where the table would not fit): one counter per tile in memory,
+// cleared by the launch before, for all chunks.  (Walking the pairs again for
+// every 32,768 tiles took 43 ms for a 3840x2160 view of 300 k Gaussians at
+// tile 8, 52.6 M instances, and 900 ms at 7680x4320; now 3.3 and 4.3.)
+template <bool LOOKBACK, bool LDS>
 __global__ void __launch_bounds__(EM_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) k_emit(EmitArgs A) {
     extern __shared__ uint32_t s_cnt[];
     __shared__ uint32_t s_tmp[EM_WAVES];
@@ -319,7 +325,7 @@ __global__ void __launch_bounds__(EM_THREADS) __attribute__((amdgpu_waves_per_eu
     const int v = ch / A.per_view, cb = ch - v * A.per_view;
     const gs_view& vw = A.views[v];
     const int tiles_x = ceil_div(vw.width, A.tile), tiles_v = tiles_x * ceil_div(vw.height, A.tile);
-    const int64_t row = table_row(vw, A.per_view, cb, tiles_v);
+    const int64_t row = LDS ? table_row(vw, A.per_view, cb, tiles_v) : vw.tile_offset;
     const int64_t c0 = (int64_t)cb * A.chunk, c1 = min(c0 + A.chunk, (int64_t)A.n);
     const int64_t vbase = (int64_t)v * A.n;
     const int pass = EM_THREADS * A.items;
@@ -345,7 +351,6 @@ __global__ void __launch_bounds__(EM_THREADS) __attribute__((amdgpu_waves_per_eu
     };
     // 1. the chunk's offset
     uint64_t prefix;
-    const bool one_pass = c1 - c0 <= pass;
     uint32_t off = 0, tot_i = 0, tot_v = 0;
     pass_offsets(c0, off, tot_i, tot_v);
     if constexpr (LOOKBACK) {
@@ -380,121 +385,114 @@ __global__ void __launch_bounds__(EM_THREADS) __attribute__((amdgpu_waves_per_eu
     }
     const int64_t first = (int64_t)(uint32_t)prefix;
 
-    // 2. the walk, once per window of tiles
-    for (int w0 = 0; w0 < tiles_v; w0 += A.window) {
-        const int wn = min(A.window, tiles_v - w0);
-        const int words = WIDE ? wn : (wn + 1) / 2;
+    // 2. the walk
+    if constexpr (LDS) {
+        for (int i = tid; i < (tiles_v + 1) / 2; i += EM_THREADS) s_cnt[i] = 0;
         __syncthreads();
-        for (int i = tid; i < words; i += EM_THREADS) s_cnt[i] = 0;
-        __syncthreads();
-        int64_t done = 0;  // instances of the passes before
-        for (int64_t j = c0; j < c1; j += pass) {
-            if (!(j == c0 && (w0 == 0 || one_pass))) pass_offsets(j, off, tot_i, tot_v);
-            uint32_t run = off;  // first instance of the next pair, within the pass
-            int head = 0, tail = 0;
-            const uint32_t wpair = (uint32_t)(j + (int64_t)wave * (kWave * A.items));
-            // emits the queued pairs [head, head + ng), one per lane
-            auto emit = [&](int ng) {
-                uint32_t my_start = 0, my_end = 0;
-                const int q0 = head & (EM_RING - 1);
-                const uint32_t gstart = s_qfirst[wave][q0];
-                if (lane < ng) {
-                    const int q = (head + lane) & (EM_RING - 1);
-                    const uint32_t i = wpair + s_qpair[wave][q], f = s_qfirst[wave][q];
-                    const uint4 r = A.rect[vbase + i];
-                    const uint32_t x0 = r.x & 0xffffu, y0 = r.x >> 16, x1 = r.y & 0xffffu, y1 = r.y >> 16;
-                    const uint32_t wr = x1 - x0 + 1, hr = y1 - y0 + 1;
-                    my_start = f - gstart;
-                    my_end = my_start + wr * hr;
-                    if (w0 == 0) A.pair_first[vbase + i] = (int32_t)(first + done + f);
-                    s_info[wave][lane] = make_uint2(x0 | (y0 << 16), wr);
-                    s_who[wave][lane] = make_uint2(i, r.z);
-                }
-                const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)my_end, ng - 1);
-                const int64_t o_g = first + done + gstart;
-                int carry = 0;  // the pair of the last instance before the current 64
-                for (uint32_t b0 = 0; b0 < total; b0 += kWave) {
-                    s_mark[wave][lane] = -1;
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                    // starts strictly increase (a visible pair has an
-                    // instance), so a slot is marked at most once
-                    if (lane < ng && my_start >= b0 && my_start < b0 + kWave) s_mark[wave][my_start - b0] = lane;
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                    const int lo = max(wave_max_scan(s_mark[wave][lane]), carry);
-                    carry = __builtin_amdgcn_readlane(lo, kWave - 1);
-                    const uint32_t k = b0 + lane;
-                    const int64_t o = o_g + k;
-                    const uint2 info = s_info[wave][lo], who = s_who[wave][lo];
-                    // row and column of the instance in the rectangle (width
-                    // info.y): the quotient is below 2^16, so a float estimate
-                    // is within one of it and one correction step makes it exact
-                    const uint32_t li = k - (s_qfirst[wave][(head + lo) & (EM_RING - 1)] - gstart);
-                    uint32_t q = (uint32_t)((float)li * __builtin_amdgcn_rcpf((float)info.y));
-                    int32_t r = (int32_t)(li - q * info.y);
-                    if (r < 0) {
-                        --q;
-                        r += (int32_t)info.y;
-                    } else if (r >= (int32_t)info.y) {
-                        ++q;
-                        r -= (int32_t)info.y;
-                    }
-                    const int t = (int)((info.x >> 16) + q) * tiles_x + (int)(info.x & 0xffffu) + r;
-                    if (k < total && o < A.capacity) {
-                        if (w0 == 0) {
-                            A.inst_gid[o] = (int32_t)who.x;
-                            A.depth_e[o] = who.y;
-                        }
-                        if (t >= w0 && t < w0 + wn) {
-                            uint32_t rank;
-                            if constexpr (WIDE) {
-                                rank = atomicAdd(&s_cnt[t - w0], 1u);
-                            } else {
-                                const int sh = ((t - w0) & 1) * 16;
-                                rank = (atomicAdd(&s_cnt[(t - w0) >> 1], 1u << sh) >> sh) & 0xffffu;
-                            }
-                            A.cell_e[o] = (uint32_t)(row + t);
-                            A.rank_e[o] = rank;
-                        }
-                    }
-                }
-                head += ng;
-                // the next group rewrites this wavefront's LDS
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            };
-            // one round per 64 pairs (the next ones' counts in flight), and a
-            // last one for what is left in the queue
-            int32_t next = tiles_of(j, 0);
-            for (int k = 0; k <= A.items; ++k) {
-                const int32_t c = next;
-                next = tiles_of(j, k + 1);
-                const uint32_t incl = (uint32_t)wave_add_scan(c);
-                const uint64_t m = __builtin_amdgcn_ballot_w64(c > 0);
-                if (c > 0) {
-                    const int q = (tail + (int)__popcll(m & lt)) & (EM_RING - 1);
-                    s_qpair[wave][q] = (uint16_t)(k * kWave + lane);
-                    s_qfirst[wave][q] = run + incl - (uint32_t)c;
-                }
-                run += (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
-                tail += (int)__popcll(m);
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                const int ng = min(tail - head, kWave);
-                if (ng == kWave || (k == A.items && ng > 0)) emit(ng);
+    }
+    int64_t done = 0;  // instances of the passes before
+    for (int64_t j = c0; j < c1; j += pass) {
+        if (j != c0) pass_offsets(j, off, tot_i, tot_v);
+        uint32_t run = off;  // first instance of the next pair, within the pass
+        int head = 0, tail = 0;
+        const uint32_t wpair = (uint32_t)(j + (int64_t)wave * (kWave * A.items));
+        // emits the queued pairs [head, head + ng), one per lane
+        auto emit = [&](int ng) {
+            uint32_t my_start = 0, my_end = 0;
+            const int q0 = head & (EM_RING - 1);
+            const uint32_t gstart = s_qfirst[wave][q0];
+            if (lane < ng) {
+                const int q = (head + lane) & (EM_RING - 1);
+                const uint32_t i = wpair + s_qpair[wave][q], f = s_qfirst[wave][q];
+                const uint4 r = A.rect[vbase + i];
+                const uint32_t x0 = r.x & 0xffffu, y0 = r.x >> 16, x1 = r.y & 0xffffu, y1 = r.y >> 16;
+                const uint32_t wr = x1 - x0 + 1, hr = y1 - y0 + 1;
+                my_start = f - gstart;
+                my_end = my_start + wr * hr;
+                A.pair_first[vbase + i] = (int32_t)(first + done + f);
+                s_info[wave][lane] = make_uint2(x0 | (y0 << 16), wr);
+                s_who[wave][lane] = make_uint2(i, r.z);
             }
-            done += tot_i;
+            const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)my_end, ng - 1);
+            const int64_t o_g = first + done + gstart;
+            int carry = 0;  // the pair of the last instance before the current 64
+            for (uint32_t b0 = 0; b0 < total; b0 += kWave) {
+                s_mark[wave][lane] = -1;
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                // starts strictly increase (a visible pair has an
+                // instance), so a slot is marked at most once
+                if (lane < ng && my_start >= b0 && my_start < b0 + kWave) s_mark[wave][my_start - b0] = lane;
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                const int lo = max(wave_max_scan(s_mark[wave][lane]), carry);
+                carry = __builtin_amdgcn_readlane(lo, kWave - 1);
+                const uint32_t k = b0 + lane;
+                const int64_t o = o_g + k;
+                const uint2 info = s_info[wave][lo], who = s_who[wave][lo];
+                // row and column of the instance in the rectangle (width
+                // info.y): the quotient is below 2^16, so a float estimate
+                // is within one of it and one correction step makes it exact
+                const uint32_t li = k - (s_qfirst[wave][(head + lo) & (EM_RING - 1)] - gstart);
+                uint32_t q = (uint32_t)((float)li * __builtin_amdgcn_rcpf((float)info.y));
+                int32_t r = (int32_t)(li - q * info.y);
+                if (r < 0) {
+                    --q;
+                    r += (int32_t)info.y;
+                } else if (r >= (int32_t)info.y) {
+                    ++q;
+                    r -= (int32_t)info.y;
+                }
+                const int t = (int)((info.x >> 16) + q) * tiles_x + (int)(info.x & 0xffffu) + r;
+                if (k < total && o < A.capacity) {
+                    uint32_t rank;
+                    if constexpr (LDS) {
+                        const int sh = (t & 1) * 16;
+                        rank = (atomicAdd(&s_cnt[t >> 1], 1u << sh) >> sh) & 0xffffu;
+                    } else {
+                        rank = atomicAdd(&A.table[(row + t) * A.stride], 1u);
+                    }
+                    A.inst_gid[o] = (int32_t)who.x;
+                    A.depth_e[o] = who.y;
+                    A.cell_e[o] = (uint32_t)(row + t);
+                    A.rank_e[o] = rank;
+                }
+            }
+            head += ng;
+            // the next group rewrites this wavefront's LDS
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        };
+        // one round per 64 pairs (the next ones' counts in flight), and a
+        // last one for what is left in the queue
+        int32_t next = tiles_of(j, 0);
+        for (int k = 0; k <= A.items; ++k) {
+            const int32_t c = next;
+            next = tiles_of(j, k + 1);
+            const uint32_t incl = (uint32_t)wave_add_scan(c);
+            const uint64_t m = __builtin_amdgcn_ballot_w64(c > 0);
+            if (c > 0) {
+                const int q = (tail + (int)__popcll(m & lt)) & (EM_RING - 1);
+                s_qpair[wave][q] = (uint16_t)(k * kWave + lane);
+                s_qfirst[wave][q] = run + incl - (uint32_t)c;
+            }
+            run += (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+            tail += (int)__popcll(m);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            const int ng = min(tail - head, kWave);
+            if (ng == kWave || (k == A.items && ng > 0)) emit(ng);
         }
+        done += tot_i;
+    }
+    if constexpr (LDS) {
         __syncthreads();
-        for (int i = tid; i < wn; i += EM_THREADS) {
-            const uint32_t x = WIDE ? s_cnt[i] : (s_cnt[i >> 1] >> ((i & 1) * 16)) & 0xffffu;
-            A.table[(row + w0 + i) * A.stride] = x;
-        }
+        for (int i = tid; i < tiles_v; i += EM_THREADS)
+            A.table[row + i] = (s_cnt[i >> 1] >> ((i & 1) * 16)) & 0xffffu;
     }
 }
 
@@ -569,8 +567,8 @@ __global__ void __launch_bounds__(SC_THREADS) k_tile_scan(uint32_t* table, int s
             if (t < tiles) ranges[t] = x > 0 ? make_int2((int)at, (int)(at + x)) : make_int2(0, 0);
         }
         __syncthreads();
-        // with stride 2 the table is the ranges themselves (one chunk per
-        // view): an entry's first place is its range's start
+        // with stride 2 the table is the ranges themselves (one entry per
+        // tile): an entry's first place is its range's start
         if (!off && t < tiles && stride == 1) {
             uint32_t at = s_at[lane];
             for (int w = 0; w < wave; ++w) at += s_part[w][lane];
@@ -914,20 +912,26 @@ struct WsLayout {
 };
 
 // Chunks of a view of n pairs: of 1024 pairs while there are few (a workgroup
-// per CU), then 4096, then 16384 or whole multiples of them, so that there
-// are at most about a thousand and their table stays small.
+// per CU), then 4096, then 16384 or, where those would be more than a
+// thousand, EM_CHUNK, so that their table stays small.  lds: k_emit counts in
+// LDS (a chunk's tiles fit there and the table, with larger chunks where it
+// has to be, in table_words).
 struct Chunks {
     int64_t chunk;
     int per_view, items;
+    bool lds;
 };
-Chunks chunks_of(int n, int n_views, int64_t total_tiles, int64_t table_words) {
+Chunks chunks_of(int n, int n_views, int64_t total_tiles, int max_tiles, int64_t table_words) {
     auto per_view = [&](int64_t c) { return (int)((n + c - 1) / c); };
     auto count = [&](int64_t c) { return (int64_t)n_views * per_view(c); };
+    auto fits = [&](int64_t c) { return per_view(c) * total_tiles <= table_words; };
     int64_t c = count(1024) <= 256 ? 1024 : (count(4096) <= 512 ? 4096 : EM_PASS);
-    while (count(c) > 1024 && c < n) c *= 2;
-    // the table has to fit; at worst a chunk is a whole view
-    while (per_view(c) * total_tiles > table_words && per_view(c) > 1) c *= 2;
-    return {c, per_view(c), (int)(c < EM_PASS ? c : EM_PASS) / EM_THREADS};
+    if (count(c) > 1024) c = EM_CHUNK;
+    int64_t larger = c;
+    while (!fits(larger) && larger < EM_CHUNK) larger *= 2;
+    const bool lds = max_tiles <= EM_LDS_TILES && fits(larger);
+    if (lds) c = larger;
+    return {c, per_view(c), (int)(c < EM_PASS ? c : EM_PASS) / EM_THREADS, lds};
 }
 
 WsLayout ws_layout(int n, int n_views, int64_t capacity) {
@@ -941,7 +945,7 @@ WsLayout ws_layout(int n, int n_views, int64_t capacity) {
     WsLayout L;
     // the (chunk, tile) table: the tiles are not known here, so 4 MB, and
     // four words per pair (at most 128 MB) where there are many; a call whose
-    // tiles need more takes larger chunks
+    // tiles need more takes larger chunks, or counts in memory
     const int64_t want = 4 * vn;
     L.table_words = want < (1 << 20) ? (1 << 20) : (want > (32 << 20) ? (32 << 20) : want);
     size_t o = 0;
@@ -978,7 +982,7 @@ hipError_t launch_binsort(const uint32_t* rect, const int32_t* touched, int n,
                           int32_t* pair_first, int32_t* ranges, int64_t* counts, hipStream_t s) {
     if (n <= 0 || n_views <= 0 || total_tiles <= 0) return hipErrorInvalidValue;
     const WsLayout L = ws_layout(n, n_views, capacity);
-    const Chunks ck = chunks_of(n, n_views, total_tiles, L.table_words);
+    const Chunks ck = chunks_of(n, n_views, total_tiles, max_tiles, L.table_words);
     char* w = static_cast<char*>(ws);
     auto words = [&](size_t off) { return reinterpret_cast<uint32_t*>(w + off); };
     BinState* st = reinterpret_cast<BinState*>(w + L.state);
@@ -1008,11 +1012,13 @@ hipError_t launch_binsort(const uint32_t* rect, const int32_t* touched, int n,
     A.inst_sums = words(L.inst_sums);
     A.vis_sums = words(L.vis_sums);
     A.st = st;
-    // a table that does not fit even with a chunk per view has one entry per
-    // tile: the first words of the tile ranges
-    const bool own = (int64_t)ck.per_view * total_tiles <= L.table_words;
+    // counted in memory, the table has one entry per tile; where that does not
+    // fit, the first words of the tile ranges
+    const int rows = ck.lds ? ck.per_view : 1;
+    const bool own = (int64_t)rows * total_tiles <= L.table_words;
     A.table = own ? words(L.table) : reinterpret_cast<uint32_t*>(ranges);
     A.stride = own ? 1 : 2;
+    const int64_t clear = ck.lds ? 0 : (int64_t)total_tiles * A.stride;
     A.cell_e = words(L.cell_e);
     A.rank_e = words(L.rank_e);
     A.depth_e = words(L.depth_e);
@@ -1021,27 +1027,25 @@ hipError_t launch_binsort(const uint32_t* rect, const int32_t* touched, int n,
     A.counts = counts;
     A.gu = gu;
     // 1. and 2.
-    const bool wide = ck.chunk > 65535;
-    const int holds = EM_LDS_BYTES / (wide ? 4 : 2);
-    A.window = max_tiles < holds ? max_tiles : holds;
-    const size_t lds = wide ? 4 * (size_t)A.window : 4 * (((size_t)A.window + 1) / 2);
+    const size_t lds = ck.lds ? 4 * (((size_t)max_tiles + 1) / 2) : 0;
     const unsigned chunks = (unsigned)(n_views * ck.per_view);
     const dim3 eb(EM_THREADS);
     if (chunks <= EM_LOOKBACK) {
-        hipLaunchKernelGGL(k_bin_reset, dim3(8), dim3(256), 0, s, st, counts);
-        hipLaunchKernelGGL((wide ? k_emit<true, true> : k_emit<true, false>), dim3(chunks), eb, lds, s, A);
+        const int64_t rb = (clear + 4095) / 4096;
+        hipLaunchKernelGGL(k_bin_reset, dim3((unsigned)(rb < 8 ? 8 : (rb < 1024 ? rb : 1024))), dim3(256), 0, s, st,
+                           counts, A.table, clear);
+        hipLaunchKernelGGL((ck.lds ? k_emit<true, true> : k_emit<true, false>), dim3(chunks), eb, lds, s, A);
     } else {
         hipLaunchKernelGGL(k_chunk_sums, dim3(chunks), eb, 0, s, touched, n, ck.per_view, ck.chunk,
-                           words(L.inst_sums), words(L.vis_sums), st, counts);
-        hipLaunchKernelGGL((wide ? k_emit<false, true> : k_emit<false, false>),
-                           dim3(chunks), eb, lds, s, A);
+                           words(L.inst_sums), words(L.vis_sums), st, counts, A.table, clear);
+        hipLaunchKernelGGL((ck.lds ? k_emit<false, true> : k_emit<false, false>), dim3(chunks), eb, lds, s, A);
     }
     // 3.
     int rounds = 1;
     while ((int64_t)SC_MAXBLK * kWave * rounds < (int64_t)total_tiles) ++rounds;
     const int64_t per = (int64_t)rounds * kWave;
     hipLaunchKernelGGL(k_tile_scan, dim3((unsigned)((total_tiles + per - 1) / per)), dim3(SC_THREADS), 0, s, A.table,
-                       A.stride, views_dev, n_views, tile, ck.per_view, total_tiles, rounds, rg, st, gu);
+                       A.stride, views_dev, n_views, tile, rows, total_tiles, rounds, rg, st, gu);
     if (capacity <= 0) return hipGetLastError();
     // 4.
     const int64_t pb = (capacity + PL_THREADS * PL_ITEMS * kXcds - 1) / (PL_THREADS * PL_ITEMS * kXcds);

@@ -116,3 +116,58 @@ def test_replays_of_a_captured_call_follow_the_scene():
         ref = oracle.bin_instances(sc, views, oracle_cfg(r.cfg))
         _check(r, ref, ref["dec"]["touched"])
         torch.ones(1000, device="cuda").sum().item()  # eager work between the replays
+
+
+@pytest.mark.parametrize("sizes,n,tile,cap", [
+    ([(2048, 1024)], 3000, 8, None),                             # 32,768 tiles: the last size counted in LDS
+    ([(2056, 1024)], 3000, 8, None),                             # 32,896: in memory
+    ([(2056, 1024)], 140000, 8, None),                           # the same without the look-back
+    ([(70, 50), (2600, 900), (33, 90)], 9000, 8, None),          # one such view among small ones
+    ([(2056, 1024), (40, 40)], 20000, 8, 50001),                 # capacity below the instances
+    ([(8200, 8200)], 140000, 8, None),                           # counters in the tile ranges, no look-back
+], ids=lambda x: "x".join(map(str, x[0])) + "*%d" % len(x) if isinstance(x, list) else str(x))
+def test_tiles_counted_in_memory(sizes, n, tile, cap):
+    sc, views = _scene(n, 9, log_scale=-5.0 if n > 20000 else -3.5), _views(sizes)
+    r, g, ref = _bin(sc, views, tile)
+    _check(r, ref, ref["dec"]["touched"])
+    if cap is not None:
+        full, inst = r, ref["count"]
+        assert inst > cap
+        r, g, _ = _bin(sc, views, tile, capacity=cap)
+        got, _, over, _ = r.instance_counts()
+        assert got == inst and over and r.trouble()
+        e = full.inst[:inst].cpu().numpy()
+        assert np.array_equal(r.inst[:cap].cpu().numpy(), e[e < cap])
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    first = [x.clone() for x in (r.ranges, r.inst[:1000], r.counts)]
+    with torch.cuda.graph(graph):
+        r.bin_sort()
+    for _ in range(2):  # the counters are cleared by every call
+        graph.replay()
+        assert all(torch.equal(a, b) for a, b in zip(first, (r.ranges, r.inst[:1000], r.counts)))
+
+
+def test_time_per_instance_holds_for_views_of_many_tiles():
+    """Binning moves the same bytes for an instance whatever the tiles: a
+    3840x2160 view at tile 8 (129,600 tiles) and a 7680x4320 one at tile 16
+    take no more than four times as long for each as at 32,400 tiles (walking
+    the pairs again for every 32,768 tiles, 12 and 12 times; now about 1)."""
+    sc = _scene(100000, 3, log_scale=-4.0)
+    took = []
+    for (w, h), tile in [((3840, 2160), 16), ((3840, 2160), 8), ((7680, 4320), 16)]:
+        from paper_2603_27781_amd import raster
+        g = raster.Gaussians.from_numpy(sc)
+        r = raster.Rasterizer(sc.n, 0, raster.Views([wl.make_view(w, h, 0.8 * w, np.eye(4))], tile), raster.Config(tile=tile))
+        r.ensure_capacity(g)
+        best = 1e9
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            r.bin_sort()
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        took.append(best / r.instance_counts().instances)
+    print(["%.1f ps" % (1e9 * t) for t in took])
+    assert max(took[1:]) <= 4 * took[0]
