@@ -182,7 +182,7 @@ __device__ __forceinline__ int lb_ticket(uint32_t* ticket, int* s_block) {
 // instance offsets and emission
 // ----------------------------------------------------------------------------
 constexpr int EM_THREADS = 1024, EM_WAVES = EM_THREADS / kWave;
-constexpr int EM_ITEMS = 16;                         // pairs per lane and pass at most
+constexpr int EM_ITEMS = 16;                         // pairs per lane and pass at most (none for some lanes in small chunks)
 constexpr int EM_PASS = EM_THREADS * EM_ITEMS;       // pairs per workgroup and pass at most
 constexpr int EM_RING = 2 * kWave;                   // queued visible pairs per wavefront
 constexpr int EM_LOOKBACK = 128;                     // up to this many chunks, offsets by look-back
@@ -260,7 +260,8 @@ struct EmitArgs {
     const gs_view* views;
     int n, n_views, tile, per_view;  // per_view: chunks of each view
     int64_t chunk, capacity;
-    int items;       // pairs per lane and pass
+    int per_wave;    // pairs per wavefront and pass
+    int items;       // the same per lane, rounded up
     const uint32_t *inst_sums, *vis_sums;  // not read with the look-back
     BinState* st;
     uint32_t* table;
@@ -318,8 +319,7 @@ __global__ void __launch_bounds__(EM_THREADS) __attribute__((amdgpu_waves_per_eu
     __shared__ uint2 s_info[EM_WAVES][kWave];  // (x0 | y0 << 16, rect width)
     __shared__ uint2 s_who[EM_WAVES][kWave];   // (Gaussian, depth bits)
     __shared__ int32_t s_mark[EM_WAVES][kWave];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int total_chunks = A.per_view * A.n_views;
     const int ch = LOOKBACK ? lb_ticket(&A.st->emit_ticket, &s_block) : (int)blockIdx.x;
     const int v = ch / A.per_view, cb = ch - v * A.per_view;
@@ -328,19 +328,26 @@ __global__ void __launch_bounds__(EM_THREADS) __attribute__((amdgpu_waves_per_eu
     const int64_t row = LDS ? table_row(vw, A.per_view, cb, tiles_v) : vw.tile_offset;
     const int64_t c0 = (int64_t)cb * A.chunk, c1 = min(c0 + A.chunk, (int64_t)A.n);
     const int64_t vbase = (int64_t)v * A.n;
-    const int pass = EM_THREADS * A.items;
+    const int pass = EM_WAVES * A.per_wave;
     // this wavefront's pairs of the pass that starts at j: item k of lane l is
-    // pair j + wave * (64 items) + 64 k + l
-    auto tiles_of = [&](int64_t j, int k) {
-        const int64_t i = j + (int64_t)wave * (kWave * A.items) + k * kWave + lane;
-        return k < A.items && i < c1 ? A.touched[vbase + i] : 0;
+    // pair j + wave * per_wave + 64 k + l; `live` of them are there
+    auto live_of = [&](int64_t j) {
+        const int64_t left = c1 - j - (int64_t)wave * A.per_wave;
+        return left < A.per_wave ? (int)left : A.per_wave;
     };
+    auto tiles_of = [&](const int32_t* pairs, int live, int k) {
+        const int q = k * kWave + lane;
+        return q < live ? pairs[q] : 0;
+    };
+    auto pairs_of = [&](int64_t j) { return A.touched + (vbase + j + (int64_t)wave * A.per_wave); };
     // first instance of this wavefront within the pass, and the pass's totals
     auto pass_offsets = [&](int64_t j, uint32_t& off, uint32_t& tot_i, uint32_t& tot_v) {
         uint32_t ni = 0, nv = 0;
+        const int32_t* pairs = pairs_of(j);
+        const int live = live_of(j);
 #pragma unroll
         for (int k = 0; k < EM_ITEMS; ++k) {
-            const int32_t c = tiles_of(j, k);
+            const int32_t c = tiles_of(pairs, live, k);
             ni += (uint32_t)c;
             nv += c > 0 ? 1u : 0u;
         }
@@ -395,7 +402,7 @@ __global__ void __launch_bounds__(EM_THREADS) __attribute__((amdgpu_waves_per_eu
         if (j != c0) pass_offsets(j, off, tot_i, tot_v);
         uint32_t run = off;  // first instance of the next pair, within the pass
         int head = 0, tail = 0;
-        const uint32_t wpair = (uint32_t)(j + (int64_t)wave * (kWave * A.items));
+        const uint32_t wpair = (uint32_t)(j + (int64_t)wave * A.per_wave);
         // emits the queued pairs [head, head + ng), one per lane
         auto emit = [&](int ng) {
             uint32_t my_start = 0, my_end = 0;
@@ -468,14 +475,17 @@ __global__ void __launch_bounds__(EM_THREADS) __attribute__((amdgpu_waves_per_eu
         };
         // one round per 64 pairs (the next ones' counts in flight), and a
         // last one for what is left in the queue
-        int32_t next = tiles_of(j, 0);
+        const int32_t* pairs = pairs_of(j);
+        const int live = live_of(j);
+        int32_t next = tiles_of(pairs, live, 0);
         for (int k = 0; k <= A.items; ++k) {
             const int32_t c = next;
-            next = tiles_of(j, k + 1);
+            next = tiles_of(pairs, live, k + 1);
             const uint32_t incl = (uint32_t)wave_add_scan(c);
             const uint64_t m = __builtin_amdgcn_ballot_w64(c > 0);
             if (c > 0) {
-                const int q = (tail + (int)__popcll(m & lt)) & (EM_RING - 1);
+                const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+                const int q = (tail + before) & (EM_RING - 1);
                 s_qpair[wave][q] = (uint16_t)(k * kWave + lane);
                 s_qfirst[wave][q] = run + incl - (uint32_t)c;
             }
@@ -911,43 +921,51 @@ struct WsLayout {
     int64_t table_words;
 };
 
-// Chunks of a view of n pairs: of 1024 pairs while there are few (a workgroup
-// per CU), then 4096, then 16384 or, where those would be more than a
-// thousand, EM_CHUNK, so that their table stays small.  lds: k_emit counts in
-// LDS (a chunk's tiles fit there and the table, with larger chunks where it
-// has to be, in table_words).
+// Chunks of a view of n pairs: of 256 pairs while the look-back reaches
+// over all of them, of 1024 up to a workgroup per CU, then 4096, then 16384 or,
+// where those would be more than a thousand, EM_CHUNK, so that their table
+// stays small.  (Few pairs can be many instances, which two chunks of 1024 would
+// leave to two workgroups: of 2000 Gaussians that reach most of a 1200x680
+// view, 6.4 M instances, the binning takes 720 us instead of 1970.  Chunks of 64
+// pairs: 370, but 3 us more for 1000 Gaussians in a 64x64 view.)
+// lds: k_emit counts in LDS (a chunk's tiles fit there and the table, with
+// larger chunks where it has to be, in table_words).
 struct Chunks {
     int64_t chunk;
-    int per_view, items;
+    int per_view, per_wave;
     bool lds;
 };
 Chunks chunks_of(int n, int n_views, int64_t total_tiles, int max_tiles, int64_t table_words) {
     auto per_view = [&](int64_t c) { return (int)((n + c - 1) / c); };
     auto count = [&](int64_t c) { return (int64_t)n_views * per_view(c); };
     auto fits = [&](int64_t c) { return per_view(c) * total_tiles <= table_words; };
-    int64_t c = count(1024) <= 256 ? 1024 : (count(4096) <= 512 ? 4096 : EM_PASS);
-    if (count(c) > 1024) c = EM_CHUNK;
+    int64_t c = EM_CHUNK;
+    if (count(256) <= EM_LOOKBACK) c = 256;
+    else if (count(1024) <= 256) c = 1024;
+    else if (count(4096) <= 512) c = 4096;
+    else if (count(EM_PASS) <= 1024) c = EM_PASS;
     int64_t larger = c;
     while (!fits(larger) && larger < EM_CHUNK) larger *= 2;
     const bool lds = max_tiles <= EM_LDS_TILES && fits(larger);
     if (lds) c = larger;
-    return {c, per_view(c), (int)(c < EM_PASS ? c : EM_PASS) / EM_THREADS, lds};
+    return {c, per_view(c), (int)(c < EM_PASS ? c : EM_PASS) / EM_WAVES, lds};
 }
 
 WsLayout ws_layout(int n, int n_views, int64_t capacity) {
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
     const int64_t vn = (int64_t)n * n_views;
     const size_t cap = (size_t)(capacity > 0 ? capacity : 1);
-    const size_t chunks = (size_t)n_views * (size_t)((n + 1023) / 1024);  // at most
+    const size_t chunks = (size_t)n_views * (size_t)((n + 1023) / 1024);  // that need sums, at most
     // entries of the long lists: a list of L keys has one up to kTsLong and
     // 2 ceil(L / kTsLong) <= L / (kTsShort + 1) beyond
     const size_t entries = cap / (kTsShort + 1) + 1;
     WsLayout L;
-    // the (chunk, tile) table: the tiles are not known here, so 4 MB, and
-    // four words per pair (at most 128 MB) where there are many; a call whose
-    // tiles need more takes larger chunks, or counts in memory
+    // the (chunk, tile) table: the tiles are not known here, so four words per
+    // pair, at least 4 and at most 16 MB; a call whose tiles need more has it
+    // in the tile keys (written by the sort, long after), takes larger chunks
+    // or counts in memory
     const int64_t want = 4 * vn;
-    L.table_words = want < (1 << 20) ? (1 << 20) : (want > (32 << 20) ? (32 << 20) : want);
+    L.table_words = want < (1 << 20) ? (1 << 20) : (want > (4 << 20) ? (4 << 20) : want);
     size_t o = 0;
     L.slab = o; o += al(8 * cap);
     L.cell_e = o; o += al(4 * cap);
@@ -982,7 +1000,8 @@ hipError_t launch_binsort(const uint32_t* rect, const int32_t* touched, int n,
                           int32_t* pair_first, int32_t* ranges, int64_t* counts, hipStream_t s) {
     if (n <= 0 || n_views <= 0 || total_tiles <= 0) return hipErrorInvalidValue;
     const WsLayout L = ws_layout(n, n_views, capacity);
-    const Chunks ck = chunks_of(n, n_views, total_tiles, max_tiles, L.table_words);
+    const Chunks ck = chunks_of(n, n_views, total_tiles, max_tiles,
+                                capacity > L.table_words ? capacity : L.table_words);
     char* w = static_cast<char*>(ws);
     auto words = [&](size_t off) { return reinterpret_cast<uint32_t*>(w + off); };
     BinState* st = reinterpret_cast<BinState*>(w + L.state);
@@ -1008,7 +1027,8 @@ hipError_t launch_binsort(const uint32_t* rect, const int32_t* touched, int n,
     A.per_view = ck.per_view;
     A.chunk = ck.chunk;
     A.capacity = capacity;
-    A.items = ck.items;
+    A.per_wave = ck.per_wave;
+    A.items = (ck.per_wave + kWave - 1) / kWave;
     A.inst_sums = words(L.inst_sums);
     A.vis_sums = words(L.vis_sums);
     A.st = st;
@@ -1016,8 +1036,8 @@ hipError_t launch_binsort(const uint32_t* rect, const int32_t* touched, int n,
     // fit, the first words of the tile ranges
     const int rows = ck.lds ? ck.per_view : 1;
     const bool own = (int64_t)rows * total_tiles <= L.table_words;
-    A.table = own ? words(L.table) : reinterpret_cast<uint32_t*>(ranges);
-    A.stride = own ? 1 : 2;
+    A.table = own ? words(L.table) : (ck.lds ? tile_keys : reinterpret_cast<uint32_t*>(ranges));
+    A.stride = own || ck.lds ? 1 : 2;
     const int64_t clear = ck.lds ? 0 : (int64_t)total_tiles * A.stride;
     A.cell_e = words(L.cell_e);
     A.rank_e = words(L.rank_e);
