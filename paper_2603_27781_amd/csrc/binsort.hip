@@ -193,7 +193,8 @@ constexpr int SC_MAXBLK = 4096;                      // blocks of k_tile_scan at
 
 // The words one call clears before it uses them.
 struct BinState {
-    uint32_t emit_ticket, scan_ticket, long_count, long_ticket;
+    uint32_t emit_ticket, scan_ticket, long_ticket;
+    uint32_t wholes, parts, levels;  // lists of one workgroup, parts of longer ones, most levels of a merge
     int64_t instances, placed;  // all of them; those below the capacity
     uint64_t emit_status[EM_LOOKBACK];
     uint64_t scan_status[SC_MAXBLK];
@@ -648,8 +649,8 @@ __global__ void __launch_bounds__(PL_THREADS) k_place(const uint32_t* __restrict
 // (8- or 9-step searches in the other sorted chunks).  k_tile_sort_short
 // gives each list of up to kTsShort one wavefront and queues the longer ones
 // for k_tile_sort_long, which gives each up to kTsLong a workgroup; beyond
-// that, one workgroup sorts each kTsLong keys of it and, when all of them are
-// sorted, each finds the places of its keys by 12-step searches in the others.
+// that, one workgroup sorts each kTsLong keys of it, and pairs of sorted runs
+// are merged, level by level, a workgroup for each kTsLong keys that come out.
 constexpr int kTsShort = 512, kTsLong = 4096;
 constexpr int kTsChunk = 512;  // keys a wavefront sorts at once (8 runs of 64)
 
@@ -735,13 +736,13 @@ __device__ __forceinline__ void wave_sort_chunk_n(int n, uint64_t (&k)[8], int (
     }
 }
 
-// Work of k_tile_sort_long: a whole list, or part `part` of one of more than
-// kTsLong keys, first to sort and then to merge with the other parts.
-// Entries of one list are consecutive, the sorts before the merges.
-enum { kWhole = 0, kSortPart = 1, kMergePart = 2 };
-struct LongItem {
-    uint32_t tile, kind, part, first;  // first: index of the list's first entry (its done counter)
+// Part `part` of a list of more than kTsLong keys, slab[begin .. begin + len).
+// The parts of one list are consecutive; `first` is the index of the first of
+// them, and done[first] counts those that are through a level.
+struct ListPart {
+    int32_t tile, part, first, begin, len;
 };
+__device__ __forceinline__ int log2_ceil(int n) { return n > 1 ? 32 - __clz(n - 1) : 0; }
 
 // Tiles in the XCD-aware order of the compositing launches (tile_of_block).
 // After a wait gave up, every list is left empty.
@@ -749,7 +750,8 @@ __global__ void __launch_bounds__(TSS_THREADS) k_tile_sort_short(int2* __restric
                                                                   int run_log2, const uint64_t* __restrict__ slab,
                                                                   uint32_t* __restrict__ tile_keys,
                                                                   int32_t* __restrict__ inst,
-                                                                  LongItem* __restrict__ items,
+                                                                  uint32_t* __restrict__ wholes,
+                                                                  ListPart* __restrict__ list_parts,
                                                                   uint32_t* __restrict__ done, BinState* st,
                                                                   const uint32_t* __restrict__ gave_up) {
     static_assert(kTsShort == kTsChunk && kTsChunk == 8 * kWave, "a short list is one chunk of eight runs");
@@ -765,16 +767,19 @@ __global__ void __launch_bounds__(TSS_THREADS) k_tile_sort_short(int2* __restric
     const int L = rg.y - rg.x;
     if (L <= 0) return;
     if (L > kTsShort) {  // uniform across the wavefront: left to k_tile_sort_long
-        const uint32_t parts = (uint32_t)(L + kTsLong - 1) / kTsLong, ne = parts > 1 ? 2 * parts : 1;
+        if (L <= kTsLong) {
+            if (lane == 0) wholes[atomicAdd(&st->wholes, 1u)] = (uint32_t)t;
+            return;
+        }
+        const uint32_t parts = (uint32_t)(L + kTsLong - 1) / kTsLong;
         uint32_t at = 0;
         if (lane == 0) {
-            at = atomicAdd(&st->long_count, ne);
+            at = atomicAdd(&st->parts, parts);
             done[at] = 0;
+            atomicMax(&st->levels, (uint32_t)log2_ceil((int)parts));
         }
         at = (uint32_t)__builtin_amdgcn_readlane((int)at, 0);
-        for (uint32_t k = lane; k < ne; k += kWave)
-            items[at + k] = {(uint32_t)t, (uint32_t)(ne == 1 ? kWhole : (k < parts ? kSortPart : kMergePart)),
-                             k % parts, at};
+        for (uint32_t k = lane; k < parts; k += kWave) list_parts[at + k] = {t, (int)k, (int)at, rg.x, L};
         return;
     }
     const uint64_t* in = slab + rg.x;
@@ -844,80 +849,139 @@ __device__ __forceinline__ void sort_long_chunk(const uint64_t* __restrict__ in,
     }
 }
 
-// The queued lists.  A fixed grid of workgroups takes the entries by tickets;
-// a merge waits for the sorts of its own list, whose tickets are earlier.
+// Number of keys of the ascending a[0 .. n) below `key`.
+__device__ __forceinline__ int lower_bound(const uint64_t* a, int n, uint64_t key) {
+    int lo = 0;
+    while (n > 0) {
+        const int h = n >> 1;
+        const bool below = a[lo + h] < key;
+        lo = below ? lo + h + 1 : lo;
+        n = below ? n - h - 1 : h;
+    }
+    return lo;
+}
+
+// How many of the first d keys of the merge of a[0 .. na) and b[0 .. nb) are
+// a's, by a whole wavefront: 64 candidates a round.
+__device__ __forceinline__ int merge_split(const uint64_t* a, int na, const uint64_t* b, int nb, int d) {
+    const int lane = threadIdx.x & (kWave - 1);
+    int lo = d > nb ? d - nb : 0, hi = d < na ? d : na;
+    while (lo < hi) {
+        const int step = (hi - lo + kWave - 1) / kWave, m = lo + lane * step;
+        // true up to the last candidate below the answer (m < na and
+        // 0 <= d - 1 - m < nb in [lo, hi))
+        const int c = (int)__popcll(__ballot(m < hi && a[m] < b[d - 1 - m]));
+        if (c == 0) return lo;
+        hi = min(hi, lo + c * step);
+        lo += (c - 1) * step + 1;
+    }
+    return lo;
+}
+
+// The queued lists.  A fixed grid of workgroups takes tickets: the parts'
+// sorts, the whole lists, then the levels of the merges, every part once in
+// each.  A merge waits until all parts of its list are through the level
+// before, whose tickets are earlier.  Level l merges pairs of runs of
+// kTsLong 2^(l-1) keys between slab and slab2 (the last one into inst): the
+// workgroup's kTsLong keys of the result are a stretch of either run, which it
+// finds by bisection and merges in LDS.  (Each key looked up in every other
+// part of its list in memory, and every wavefront fencing for itself, took 9.7
+// ms for four lists of 717 k keys and 11.4 for 336 of 54 k, now 0.6 and 2.1; one
+// workgroup's counting passes over a list, before that, 21.0 and 5.4.)
 __global__ void __launch_bounds__(TSL_THREADS) k_tile_sort_long(int2* __restrict__ ranges,
-                                                                 const LongItem* __restrict__ items,
+                                                                 const uint32_t* __restrict__ wholes,
+                                                                 const ListPart* __restrict__ list_parts,
                                                                  uint32_t* done, BinState* st, uint64_t* slab,
-                                                                 uint32_t* __restrict__ tile_keys,
+                                                                 uint64_t* slab2, uint32_t* __restrict__ tile_keys,
                                                                  int32_t* __restrict__ inst, LbGiveUp gu) {
     __shared__ LongLds S;
     __shared__ int s_item;
     __shared__ int s_ok;
-    const int count = (int)st->long_count;
+    __shared__ int s_split[2];
+    const int n_parts = (int)st->parts, n_wholes = (int)st->wholes;
+    const int64_t count = n_wholes + (int64_t)n_parts * (1 + (int)st->levels);
+    if (count == 0) return;
+    // the workgroup's writes are visible to the next level before they count:
+    // the barrier orders them before thread 0's release, which (one per
+    // workgroup, not one per wavefront) writes the XCD's L2 back
+    auto through = [&](int first) {
+        __syncthreads();
+        if (threadIdx.x == 0) __hip_atomic_fetch_add(done + first, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    };
     for (;;) {
         __syncthreads();  // the LDS is reused by the next entry
-        if (count == 0) return;  // uniform
         const int item = lb_ticket(&st->long_ticket, &s_item);
         if (item >= count) return;
-        const LongItem it = items[item];
-        const int2 rg = ranges[it.tile];
-        const int L = rg.y - rg.x;
-        if (it.kind == kWhole) {
-            sort_long_chunk(slab + rg.x, L, S, [&](int pos, uint64_t key) {
+        if (item >= n_parts && item < n_parts + n_wholes) {
+            const uint32_t tile = wholes[item - n_parts];
+            const int2 rg = ranges[tile];
+            sort_long_chunk(slab + rg.x, rg.y - rg.x, S, [&](int pos, uint64_t key) {
                 inst[rg.x + pos] = (int32_t)(uint32_t)key;
-                tile_keys[rg.x + pos] = it.tile;
+                tile_keys[rg.x + pos] = tile;
             });
             continue;
         }
-        const int parts = (L + kTsLong - 1) / kTsLong;
-        const int p0 = (int)it.part * kTsLong, np = min(kTsLong, L - p0);
-        uint64_t* mine = slab + rg.x + p0;
-        if (it.kind == kSortPart) {
+        const int m = item - n_parts - n_wholes;
+        const int level = item < n_parts ? 0 : m / n_parts + 1;
+        const ListPart lp = list_parts[item < n_parts ? item : m % n_parts];
+        const int p0 = lp.part * kTsLong, np = min(kTsLong, lp.len - p0);
+        if (level == 0) {
             // in place: every key is in LDS before the first is written
+            uint64_t* mine = slab + lp.begin + p0;
             sort_long_chunk(mine, np, S, [&](int pos, uint64_t key) { mine[pos] = key; });
-            __threadfence();  // the part is visible to the merges before it counts as done
-            __syncthreads();
-            if (threadIdx.x == 0) __hip_atomic_fetch_add(done + it.first, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            through(lp.first);
             continue;
         }
+        const int parts = (lp.len + kTsLong - 1) / kTsLong, levels = log2_ceil(parts);
+        if (level > levels) continue;
         if (threadIdx.x == 0) {
             const auto ready = [&] {
-                return (int)__hip_atomic_load(done + it.first, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) >= parts;
+                return (int)__hip_atomic_load(done + lp.first, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >=
+                       parts * level;
             };
             bool ok = ready();
-            for (int spin = 0; !ok && spin < gu.spin_limit; ++spin) ok = ready();
+            const int spins = __hip_atomic_load(gu.flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? 0 : gu.spin_limit;
+            for (int spin = 0; !ok && spin < spins; ++spin) ok = ready();
             if (!ok) {  // the list is left empty; the caller discards the call's results
                 give_up(gu);
-                ranges[it.tile] = make_int2(0, 0);
+                ranges[lp.tile] = make_int2(0, 0);
             }
             s_ok = ok;
+            // the whole workgroup reads the other parts after this and the barrier
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         }
         __syncthreads();
         if (!s_ok) continue;
-        __threadfence();      // nothing of the other parts is read from before the wait
-        for (int j = threadIdx.x; j < np; j += TSL_THREADS) {
-            const uint64_t key = mine[j];
-            int pos = j;
-            for (int q = 0; q < parts; ++q) {
-                if (q == (int)it.part) continue;
-                const uint64_t* a = slab + rg.x + q * kTsLong;
-                int lo = 0, hi = min(kTsLong, L - q * kTsLong);  // first key above `key`
-                while (lo < hi) {
-                    const int m = (lo + hi) >> 1;
-                    if (a[m] < key) lo = m + 1;
-                    else hi = m;
-                }
-                pos += lo;
-            }
-            inst[rg.x + pos] = (int32_t)(uint32_t)key;
-            tile_keys[rg.x + pos] = it.tile;
+        const uint64_t* src = ((level & 1) ? slab : slab2) + lp.begin;
+        const int run = kTsLong << (level - 1), r0 = (lp.part >> level << level) * kTsLong;
+        const int na = min(run, lp.len - r0), nb = min(run, max(lp.len - r0 - run, 0)), d = p0 - r0;
+        const uint64_t *a = src + r0, *b = a + run;
+        const int wave = threadIdx.x / kWave;
+        if (wave < 2) {
+            const int i = merge_split(a, na, b, nb, d + wave * np);
+            if ((threadIdx.x & (kWave - 1)) == 0) s_split[wave] = i;
         }
+        __syncthreads();
+        const int i0 = s_split[0], ca = s_split[1] - i0, cb = np - ca;
+        for (int j = threadIdx.x; j < np; j += TSL_THREADS) S.sorted[j] = j < ca ? a[i0 + j] : b[d - i0 + (j - ca)];
+        __syncthreads();
+        uint64_t* dst = ((level & 1) ? slab2 : slab) + lp.begin + p0;
+        for (int j = threadIdx.x; j < np; j += TSL_THREADS) {
+            const uint64_t key = S.sorted[j];
+            const int pos = j < ca ? j + lower_bound(S.sorted + ca, cb, key) : j - ca + lower_bound(S.sorted, ca, key);
+            if (level < levels) {
+                dst[pos] = key;
+            } else {
+                inst[lp.begin + p0 + pos] = (int32_t)(uint32_t)key;
+                tile_keys[lp.begin + p0 + pos] = (uint32_t)lp.tile;
+            }
+        }
+        if (level < levels) through(lp.first);
     }
 }
 
 struct WsLayout {
-    size_t slab, cell_e, rank_e, depth_e, inst_sums, vis_sums, state, items, done, table, total;
+    size_t slab, cell_e, rank_e, depth_e, inst_sums, vis_sums, state, wholes, parts, done, table, total;
     int64_t table_words;
 };
 
@@ -956,9 +1020,8 @@ WsLayout ws_layout(int n, int n_views, int64_t capacity) {
     const int64_t vn = (int64_t)n * n_views;
     const size_t cap = (size_t)(capacity > 0 ? capacity : 1);
     const size_t chunks = (size_t)n_views * (size_t)((n + 1023) / 1024);  // that need sums, at most
-    // entries of the long lists: a list of L keys has one up to kTsLong and
-    // 2 ceil(L / kTsLong) <= L / (kTsShort + 1) beyond
-    const size_t entries = cap / (kTsShort + 1) + 1;
+    // a list of L > kTsLong keys has ceil(L / kTsLong) <= L / (kTsLong / 2) parts
+    const size_t wholes = cap / (kTsShort + 1) + 1, parts = cap / (kTsLong / 2) + 1;
     WsLayout L;
     // the (chunk, tile) table: the tiles are not known here, so four words per
     // pair, at least 4 and at most 16 MB; a call whose tiles need more has it
@@ -968,14 +1031,15 @@ WsLayout ws_layout(int n, int n_views, int64_t capacity) {
     L.table_words = want < (1 << 20) ? (1 << 20) : (want > (4 << 20) ? (4 << 20) : want);
     size_t o = 0;
     L.slab = o; o += al(8 * cap);
-    L.cell_e = o; o += al(4 * cap);
+    L.cell_e = o; o += al(4 * cap);  // these two, read for the last time by k_place, are slab2 of the merges
     L.rank_e = o; o += al(4 * cap);
     L.depth_e = o; o += al(4 * cap);
     L.inst_sums = o; o += al(4 * chunks);
     L.vis_sums = o; o += al(4 * chunks);
     L.state = o; o += al(sizeof(BinState));
-    L.items = o; o += al(sizeof(LongItem) * entries);
-    L.done = o; o += al(4 * entries);
+    L.wholes = o; o += al(4 * wholes);
+    L.parts = o; o += al(sizeof(ListPart) * parts);
+    L.done = o; o += al(4 * parts);
     L.table = o; o += al(4 * (size_t)L.table_words);
     L.total = o;
     return L;
@@ -1006,7 +1070,7 @@ hipError_t launch_binsort(const uint32_t* rect, const int32_t* touched, int n,
     auto words = [&](size_t off) { return reinterpret_cast<uint32_t*>(w + off); };
     BinState* st = reinterpret_cast<BinState*>(w + L.state);
     uint64_t* slab = reinterpret_cast<uint64_t*>(w + L.slab);
-    LongItem* items = reinterpret_cast<LongItem*>(w + L.items);
+    ListPart* parts = reinterpret_cast<ListPart*>(w + L.parts);
     uint32_t* done = words(L.done);
     int2* rg = reinterpret_cast<int2*>(ranges);
 
@@ -1074,11 +1138,12 @@ hipError_t launch_binsort(const uint32_t* rect, const int32_t* touched, int n,
     // 5. and 6. (no list is longer than the Gaussians)
     const int run_log2 = tile_run_log2(tile, total_tiles);
     hipLaunchKernelGGL(k_tile_sort_short, dim3(tile_grid(total_tiles, run_log2)), dim3(TSS_THREADS), 0, s, rg,
-                       total_tiles, run_log2, slab, tile_keys, inst, items, done, st, gu.flag);
+                       total_tiles, run_log2, slab, tile_keys, inst, words(L.wholes), parts, done, st, gu.flag);
     if (n > kTsShort) {
         const int64_t max_long = capacity / (kTsShort + 1) + 1;
         hipLaunchKernelGGL(k_tile_sort_long, dim3((unsigned)(max_long < 768 ? max_long : 768)), dim3(TSL_THREADS), 0,
-                           s, rg, items, done, st, slab, tile_keys, inst, gu);
+                           s, rg, words(L.wholes), parts, done, st, slab, reinterpret_cast<uint64_t*>(w + L.cell_e),
+                           tile_keys, inst, gu);
     }
     return hipGetLastError();
 }

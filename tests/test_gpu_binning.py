@@ -148,10 +148,10 @@ def test_tiles_counted_in_memory(sizes, n, tile, cap):
         assert all(torch.equal(a, b) for a, b in zip(first, (r.ranges, r.inst[:1000], r.counts)))
 
 
-def _ps_per_instance(sc, view, tile):
+def _ps_per_instance(sc, views, tile):
     from paper_2603_27781_amd import raster
     g = raster.Gaussians.from_numpy(sc)
-    r = raster.Rasterizer(sc.n, 0, raster.Views([view], tile), raster.Config(tile=tile))
+    r = raster.Rasterizer(sc.n, 0, raster.Views(views, tile), raster.Config(tile=tile))
     r.ensure_capacity(g)
     best = 1e9
     for _ in range(5):
@@ -171,7 +171,7 @@ def test_time_per_instance_holds_for_views_of_many_tiles():
     the pairs again for every 32,768 tiles took 4.8 times as long for both;
     counting in memory 0.8)."""
     sc = _scene(100000, 3, log_scale=-4.0)
-    took = [_ps_per_instance(sc, wl.make_view(w, h, 0.8 * w, np.eye(4)), tile)
+    took = [_ps_per_instance(sc, [wl.make_view(w, h, 0.8 * w, np.eye(4))], tile)
             for (w, h), tile in [((3840, 2160), 16), ((3840, 2160), 8), ((7680, 4320), 16)]]
     print(took)
     assert max(took[1:]) <= 4 * took[0]
@@ -181,8 +181,8 @@ def test_time_per_instance_holds_for_few_large_gaussians():
     """1000 Gaussians that reach most of a view, 3.2 M instances, take no more
     than four times as long for each as 300,000 small ones (one workgroup for
     all of them: 6.5 times, four: 2.1)."""
-    view = wl.make_view(1200, 680, 960.0, np.eye(4))
-    few, many = (_ps_per_instance(_scene(n, 4, log_scale=ls), view, 16) for n, ls in ((1000, 0.0), (300000, -5.0)))
+    views = [wl.make_view(1200, 680, 960.0, np.eye(4))]
+    few, many = (_ps_per_instance(_scene(n, 4, log_scale=ls), views, 16) for n, ls in ((1000, 0.0), (300000, -5.0)))
     print(few, many)
     assert few <= 4 * many
 
@@ -197,3 +197,29 @@ def test_small_chunks_and_table_in_the_keys(sizes, n, cap):
     sc, views = _scene(n, 11, log_scale=-5.0 if n > 30000 else -3.5), _views(sizes)
     r, g, ref = _bin(sc, views, 16 if cap is None else 8, capacity=cap)
     _check(r, ref, ref["dec"]["touched"])
+
+
+@pytest.mark.parametrize("n,sizes", [
+    (8192, [(20, 20)]), (8193, [(20, 20)]),              # two parts, three (a run without a sibling)
+    (12300, [(20, 20)]), (16385, [(20, 20)] * 2),        # four and five: levels of either parity
+    (40000, [(20, 20), (10, 16)]), (70001, [(16, 16)]),  # ten, eighteen
+    (30000, [(90, 60)]),                                 # lists of one wavefront, one workgroup and parts together
+])
+def test_merged_lists(n, sizes):
+    sc = _scene(n, n, log_scale=-1.0 if len(sizes) > 1 or sizes[0][0] < 90 else -2.5, spread=0.3)
+    sc.mu[2] = np.maximum(sc.mu[2], 1.0)
+    r, g, ref = _bin(sc, [wl.make_view(w, h, 24.0, np.eye(4)) for w, h in sizes])
+    assert int((ref["ranges"][:, 1] - ref["ranges"][:, 0]).max()) > 8192 * (n < 30000) * 0.9
+    for _ in range(2):
+        r.bin_sort()
+    _check(r, ref, ref["dec"]["touched"])
+
+
+def test_time_per_instance_holds_for_long_lists():
+    """Lists of some 54,000 take no more than three times as long for each
+    instance as lists of some 1200 (every key looked up in all other parts of
+    its list: 4.5 times; merged by levels: 1.1)."""
+    few = _ps_per_instance(_scene(200000, 4, log_scale=-4.0), [wl.make_view(640, 480, 512.0, np.eye(4))], 16)
+    many = _ps_per_instance(_scene(1000000, 4, log_scale=-5.0), _views([(97, 61)] * 12), 16)
+    print(few, many)
+    assert many <= 3 * few
