@@ -515,7 +515,7 @@ __global__ void __launch_bounds__(EM_THREADS) __attribute__((amdgpu_waves_per_eu
 // instances: a single-pass scan over blocks of `rounds` groups of 64 tiles.
 // A group's tiles lie across the lanes of a wavefront, its chunks are shared
 // out over the wavefronts.
-__global__ void __launch_bounds__(SC_THREADS) k_tile_scan(uint32_t* table, int stride, const gs_view* views,
+__global__ void __launch_bounds__(SC_THREADS) k_tile_scan(uint32_t* table, const gs_view* views,
                                                           int n_views, int tile, int per_view, int tiles, int rounds,
                                                           int2* ranges, BinState* st, LbGiveUp gu) {
     __shared__ uint32_t s_part[SC_WAVES][kWave];
@@ -540,8 +540,8 @@ __global__ void __launch_bounds__(SC_THREADS) k_tile_scan(uint32_t* table, int s
             const int v = view_of_tile(views, n_views, (int)t);
             const gs_view& vw = views[v];
             const int tiles_v = ceil_div(vw.width, tile) * ceil_div(vw.height, tile);
-            col = (table_row(vw, per_view, 0, tiles_v) + (t - vw.tile_offset)) * stride;
-            step = (int64_t)tiles_v * stride;
+            col = table_row(vw, per_view, 0, tiles_v) + (t - vw.tile_offset);
+            step = tiles_v;
         }
         uint32_t sum = 0;
 #pragma unroll
@@ -578,9 +578,7 @@ __global__ void __launch_bounds__(SC_THREADS) k_tile_scan(uint32_t* table, int s
             if (t < tiles) ranges[t] = x > 0 ? make_int2((int)at, (int)(at + x)) : make_int2(0, 0);
         }
         __syncthreads();
-        // with stride 2 the table is the ranges themselves (one entry per
-        // tile): an entry's first place is its range's start
-        if (!off && t < tiles && stride == 1) {
+        if (!off && t < tiles) {
             uint32_t at = s_at[lane];
             for (int w = 0; w < wave; ++w) at += s_part[w][lane];
 #pragma unroll
@@ -596,6 +594,56 @@ __global__ void __launch_bounds__(SC_THREADS) k_tile_scan(uint32_t* table, int s
         }
         start += s_sum;
         __syncthreads();
+    }
+}
+
+// The same for a table of one entry per tile: a thread takes SC_ITEMS tiles a
+// round, instead of one column of which 15 of 16 wavefronts have no row (a
+// 16384x16384 view at tile 16, 1 M tiles: 11 us, 253 that way).
+constexpr int SC_ITEMS = 8, SC_ROUND = SC_THREADS * SC_ITEMS;
+__global__ void __launch_bounds__(SC_THREADS) k_tile_scan_one(uint32_t* table, int stride, int tiles, int rounds,
+                                                              int2* ranges, BinState* st, LbGiveUp gu) {
+    __shared__ uint32_t s_tmp[SC_WAVES];
+    __shared__ uint64_t s_prefix;
+    __shared__ int s_block;
+    const int b = lb_ticket(&st->scan_ticket, &s_block);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const bool off = *gu.flag != 0;  // of an earlier launch
+    // the counts of round r: item k of the thread is tile tile_of(r, k)
+    auto tile_of = [&](int r, int k) {
+        return ((int64_t)b * rounds + r) * SC_ROUND + wave * (kWave * SC_ITEMS) + k * kWave + lane;
+    };
+    uint32_t c[SC_ITEMS];
+    auto load = [&](int r) {
+        uint32_t sum = 0;
+#pragma unroll
+        for (int k = 0; k < SC_ITEMS; ++k) {
+            const int64_t t = tile_of(r, k);
+            c[k] = !off && t < tiles ? table[t * stride] : 0u;
+            sum += c[k];
+        }
+        return sum;
+    };
+    uint32_t total = 0, tot;
+    for (int r = 0; r < rounds; ++r) {
+        block_exclusive<SC_THREADS>(load(r), s_tmp, &tot);
+        total += tot;
+    }
+    uint32_t start = (uint32_t)lb_exchange(total, b, st->scan_status, &s_prefix, gu);
+    for (int r = 0; r < rounds; ++r) {
+        const uint32_t e = block_exclusive<SC_THREADS>(load(r), s_tmp, &tot);
+        uint32_t at = start + (uint32_t)__builtin_amdgcn_readlane((int)e, 0);  // the lanes' tiles are interleaved
+#pragma unroll
+        for (int k = 0; k < SC_ITEMS; ++k) {
+            const int64_t t = tile_of(r, k);
+            const uint32_t incl = (uint32_t)wave_add_scan((int)c[k]), p = at + incl - c[k];
+            at += (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+            if (t < tiles) {
+                ranges[t] = c[k] > 0 ? make_int2((int)p, (int)(p + c[k])) : make_int2(0, 0);
+                if (stride == 1) table[t] = p;
+            }
+        }
+        start += tot;
     }
 }
 
@@ -1125,11 +1173,16 @@ hipError_t launch_binsort(const uint32_t* rect, const int32_t* touched, int n,
         hipLaunchKernelGGL((ck.lds ? k_emit<false, true> : k_emit<false, false>), dim3(chunks), eb, lds, s, A);
     }
     // 3.
+    const int64_t round = rows > 1 ? kWave : SC_ROUND;
     int rounds = 1;
-    while ((int64_t)SC_MAXBLK * kWave * rounds < (int64_t)total_tiles) ++rounds;
-    const int64_t per = (int64_t)rounds * kWave;
-    hipLaunchKernelGGL(k_tile_scan, dim3((unsigned)((total_tiles + per - 1) / per)), dim3(SC_THREADS), 0, s, A.table,
-                       A.stride, views_dev, n_views, tile, rows, total_tiles, rounds, rg, st, gu);
+    while (SC_MAXBLK * round * rounds < (int64_t)total_tiles) ++rounds;
+    const dim3 sb((unsigned)((total_tiles + round * rounds - 1) / (round * rounds)));
+    if (rows > 1)
+        hipLaunchKernelGGL(k_tile_scan, sb, dim3(SC_THREADS), 0, s, A.table, views_dev, n_views, tile, rows,
+                           total_tiles, rounds, rg, st, gu);
+    else
+        hipLaunchKernelGGL(k_tile_scan_one, sb, dim3(SC_THREADS), 0, s, A.table, A.stride, total_tiles, rounds, rg, st,
+                           gu);
     if (capacity <= 0) return hipGetLastError();
     // 4.
     const int64_t pb = (capacity + PL_THREADS * PL_ITEMS * kXcds - 1) / (PL_THREADS * PL_ITEMS * kXcds);

@@ -223,3 +223,12 @@ def test_time_per_instance_holds_for_long_lists():
     many = _ps_per_instance(_scene(1000000, 4, log_scale=-5.0), _views([(97, 61)] * 12), 16)
     print(few, many)
     assert many <= 3 * few
+
+
+@pytest.mark.parametrize("size", [(8, 8), (64, 64), (512, 1024), (513, 1024), (1024, 4096), (1024, 4104)])
+def test_one_entry_per_tile(size):
+    """One chunk of pairs, so one table entry per tile: 1, 64, a full block of
+    the scan (8192 tiles) and a column more, eight blocks and a row more."""
+    sc = _scene(200, 2, log_scale=-3.0)
+    r, g, ref = _bin(sc, [wl.make_view(*size, 0.8 * max(size), np.eye(4))], 8)
+    _check(r, ref, ref["dec"]["touched"])
