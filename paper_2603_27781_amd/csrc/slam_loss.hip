@@ -23,9 +23,9 @@
 //      filters the maps again (the window is symmetric, so the adjoint is the
 //      same filter) and adds G*m_mu + 2 x G*m_xx + y G*m_xy to the colour
 //      gradient.  Both walk the tiles persistently, loading the next tile
-//      while the current one is filtered.  Where there are enough pixels to
-//      fill the device, k_ssim does both in one pass down strips of columns,
-//      and the maps never leave the chip.
+//      while the current one is filtered.  Where it takes less time (strip_rows),
+//      k_ssim does both in one pass down strips of columns, and the maps never
+//      leave the chip.
 //   4. a fixed-order sum of the per-block partial losses (deterministic).
 #include "loss_common.h"
 
@@ -1391,19 +1391,34 @@ int strip_blocks(const gs_view* views, int n_views, int rows, SsimStrips* pl) {
     return t;
 }
 
-// Output rows of a strip, or 0: the tiles (k_ssim_fwd, k_ssim_bwd).  A strip
-// filters 20 rows more than it owns and a workgroup alone on its CU takes
-// 2.7 us for four rows, so strips pay where short ones (24 rows) would be more
-// than the three for every CU that are resident (tiles/strips, SSIM of both
-// directions in us: 320x240 11/17, 640x480 25/31, eight 320x240 28/45,
-// 1200x680 54/49, two, four and eight 1200x680 92/83, 180/136 and 354/245), and
-// have as few rows as leave all workgroups resident, at most 72 (eight
-// 1200x680: 24 rows 278, 40 238, 72 233, 96 259).
+// Output rows of a strip, or 0: the tiles (k_ssim_fwd, k_ssim_bwd), whichever
+// takes less time by their measured rates.  Tiles: 17.2 ns for each (channel,
+// tile) item, 6 us besides.  Strips: rows + 20 rows are filtered in steps of
+// four, whose time depends on the workgroups that share a CU (three at most):
+// 3.05, 4.2 and 5.35 us; more workgroups than that follow at the same rate, the
+// last of them 0.8 us a step late.  Against 129 measured shapes, 1 to 24 views
+// of 30x3000 to 1920x1080, the choice takes 0.8 % longer than the best of tiles
+// and strips of 24, 40, 56 and 72 rows, at most 13 % (by the number of strips
+// alone 11 % and 2.2 times: views that are not nearly whole strips wide do
+// strips' work for columns that are not there).  Both in us, SSIM of both
+// directions, tiles/strips: 320x240 11/33, 1200x680 49/47 (estimated 48/58:
+// tiles), four 640x480 70/59, eight 1200x680 335/248, 256x256 x 12 49/64,
+// 30x3000 x 8 84/170.
 int strip_rows(const gs_view* views, int n_views) {
-    if (strip_blocks(views, n_views, 24, nullptr) <= 3 * 256) return 0;
-    int rows = 40;
-    while (rows < 72 && strip_blocks(views, n_views, rows, nullptr) > 3 * 256) rows += 16;
-    return rows;
+    constexpr int CUS = 256;
+    double best = 6.0 + 0.0172 * 3 * ssim_tiles(views, n_views, nullptr);
+    int height = 0, choice = 0;
+    for (int v = 0; v < n_views; ++v) height = views[v].height > height ? views[v].height : height;
+    for (int rows = 24; rows <= 72; rows += 16) {
+        const int n = strip_blocks(views, n_views, rows, nullptr);
+        const int steps = ceil_div((rows < height ? rows : height) + 4 * kSsimR, kStripR);
+        const double step = n <= CUS ? 3.05 : (n <= 2 * CUS ? 4.2 : (n <= 3 * CUS ? 5.35 : n * 5.35 / (3 * CUS) + 0.8));
+        if (steps * step < best) {
+            best = steps * step;
+            choice = rows;
+        }
+    }
+    return choice;
 }
 
 // Decoder-gradient reduction: the pixel kernel's block partials, block-major

@@ -104,3 +104,42 @@ def test_not_finite(value):
     assert np.isfinite(g[:3, :off]).all() and np.isfinite(g[:3, off + W * H:]).all()
     d = np.where(fin, g[:3, sl].astype(np.float64) - np.where(fin, ga[:3], 0.0), 0.0)
     assert np.linalg.norm(d) <= 2 * TOL * np.linalg.norm(ga[:3][fin].astype(np.float64))
+
+
+# wide and tall enough for strips of 24, 40, 56 and 72 rows once, three, six
+# and four times: whole strips and one column more or less, short last strips
+WIDE = [(944, 243), (943, 241), (1180, 145), (236, 96), (237, 73), (1, 1), (3, 20), (700, 23), (708, 71)]
+
+
+@pytest.mark.parametrize("use_obs", [False, True])
+@pytest.mark.parametrize("times", [1, 3, 6, 4])
+def test_strips_of_each_height_against_tiles(times, use_obs):
+    test_strips_against_tiles(WIDE * times, use_obs)
+
+
+def test_narrow_views_are_not_filtered_in_strips():
+    """Eight 30x3000 views have the pixels of eight 3000x30 ones and take no
+    more than twice as long (in strips, 236 columns wide, 2.4 times; in tiles
+    1.5)."""
+    from paper_2603_27781_amd import raster
+    took = []
+    for size in ((30, 3000), (3000, 30)):
+        sizes = [size] * 8
+        P = 8 * 90000
+        views = [wl.make_view(W, H, 100.0, np.eye(4)) for W, H in sizes]
+        r = raster.Rasterizer(1, 0, raster.Views(views, 16), raster.Config(), capacity=1024)
+        r.out.uniform_()
+        rgb, dep = torch.rand(3, P, device="cuda"), torch.rand(P, device="cuda")
+        o = _opts(True)
+        best = 1e9
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                r.slam_loss(rgb, dep, None, None, o)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) / 10)
+        took.append(best)
+    print(took)
+    assert took[0] <= 2 * took[1]
