@@ -114,7 +114,8 @@ typedef struct {
  *                    that pull (view, tile) items from a queue
  *   lds_batch_bwd    Gaussians staged per batch by the render backward
  *                    (64, 128 or 256; 0 = chosen by the library from
- *                    the tile, n_feat and the gradients, at most lds_batch)
+ *                    the tile, n_feat, the gradients and the number of tiles,
+ *                    at most lds_batch)
  */
 typedef struct {
     float z_near, blur, guard, alpha_min, alpha_max, T_min;

@@ -332,7 +332,7 @@ hipError_t launch_fwd_b(int B, const float* rec, const float* app, int n, const 
                         const RasterConst& c, int persistent, float* out, float* T_final, int32_t* last,
                         int32_t* queue, const FusedLoss& L, hipStream_t s) {
     // the batches fwd_batch gives for this tile and feature count
-    if constexpr (TS != 8 && !(TS == 16 && F > 16)) {
+    if constexpr (TS != 8 || F > 16) {
         if (B == 256)
             return launch_fwd_t<TS, F, 256, LK>(rec, app, n, inst, inst_gid, ranges, views, n_views, total_tiles, P, c,
                                                 persistent, out, T_final, last, queue, L, s);

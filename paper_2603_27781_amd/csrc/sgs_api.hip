@@ -280,9 +280,9 @@ int gs_render_fwd(const float* rec, const float* app, int32_t n, int32_t n_feat,
     if (cfg->persistent && !queue) return GS_EINVAL;
     if (!aligned16(rec) || !aligned16(app)) return GS_EINVAL;
     return hip_status(launch_render_fwd(rec, app, n, n_feat, inst, inst_gid, tile_ranges, views_dev, n_views,
-                                        total_tiles, P, make_const(cfg), fwd_batch(cfg->tile, n_feat, cfg->lds_batch),
-                                        cfg->persistent, out,
-                                        T_final, last, queue, reinterpret_cast<hipStream_t>(stream)));
+                                        total_tiles, P, make_const(cfg),
+                                        fwd_batch(cfg->tile, n_feat, total_tiles, cfg->lds_batch), cfg->persistent,
+                                        out, T_final, last, queue, reinterpret_cast<hipStream_t>(stream)));
 }
 
 int gs_render_fwd_loss_workspace(const gs_view* views, int32_t n_views, int32_t tile, size_t* bytes) {
@@ -320,9 +320,9 @@ int gs_render_fwd_loss(const float* rec, const float* app, int32_t n, int32_t n_
     if (ws_bytes < fused_loss_workspace_bytes(total_tiles)) return GS_ECAPACITY;
     if ((reinterpret_cast<uintptr_t>(ws) & 15u) != 0) return GS_EINVAL;
     return hip_status(launch_render_fwd_loss(rec, app, n, n_feat, inst, inst_gid, tile_ranges, views_dev, n_views,
-                                             total_tiles, P, make_const(cfg), fwd_batch(cfg->tile, n_feat, cfg->lds_batch),
-                                             cfg->persistent, out,
-                                             T_final, last, queue, rgb_target, depth_target, labels, decoder,
+                                             total_tiles, P, make_const(cfg),
+                                             fwd_batch(cfg->tile, n_feat, total_tiles, cfg->lds_batch),
+                                             cfg->persistent, out, T_final, last, queue, rgb_target, depth_target, labels, decoder,
                                              n_feat > 0 ? n_classes : 0, weights, grad_out, loss, ws,
                                              reinterpret_cast<hipStream_t>(stream)));
 }

@@ -170,28 +170,40 @@ hipError_t launch_binsort(const uint32_t* rect, const int32_t* touched, int n,
 
 // Gaussians staged per LDS batch: the caller's lds_batch at most (and its
 // lds_batch_bwd as it is), fewer where the staged batch would leave too few
-// workgroups per CU.  Forward: one wavefront per workgroup at tile 8 (78 us
-// with 64, 108 with 128; 1200x680, 1M Gaussians, F = 16), 144-byte records
-// at F = 32 (772 us with 128, 801 with 256; eight such views).
-inline int fwd_batch(int tile, int n_feat, int lds_batch) {
-    const int most = tile == 8 ? 64 : (tile == 16 && n_feat > 16 ? 128 : 256);
+// workgroups per CU, but not where the tiles are so few that all are resident
+// anyway (a larger batch has fewer barriers).  Times in us with 64, 128 and 256,
+// scenes of 100 k to 300 k Gaussians unless said.
+//
+// Forward: one wavefront per workgroup at tile 8 (1200x680, F = 16 127, 173, 270;
+// F = 32 205, 265, 503, but 64x64, 64 tiles, 102, 101, 94), 144-byte records at
+// F = 32 and tile 16, of which 256 leave three workgroups per CU (16 tiles 111,
+// 109, 102, 300 tiles 139, 128, 120, 1200 tiles 100, 96, 105, 25,800 tiles 1264,
+// 1147, 1269).
+inline int fwd_batch(int tile, int n_feat, int total_tiles, int lds_batch) {
+    constexpr int CUS = 256;
+    int most = 256;
+    if (tile == 8) most = n_feat > 16 && total_tiles <= CUS ? 256 : 64;
+    else if (tile == 16 && n_feat > 16 && total_tiles > 3 * CUS) most = 128;
     return lds_batch < most ? lds_batch : most;
 }
 // Backward, which also holds an accumulator of 10 + F (6 for the pose alone)
 // floats per staged Gaussian.  At tile 16 with parameter gradients 128 at
-// F = 16 (1249 against 1827 us with 256, eight views), and at F = 32, where
-// 128 leave three workgroups per CU, 64 once there are more tiles than
-// workgroups to go round (16 mixed views of 2M Gaussians 5149 us, 5529 with
-// 128, 10939 with 256; one 1200x680 view 354, 329 and 544 us); for the pose
-// alone 128 at F = 16 (799 against 857 us; at F = 32 256 is faster, 1205
-// against 1282 us, its registers being the limit).  At tile 8 64 (255 against
-// 387 us, one view, F = 16); at tile 32 the four times larger workgroups fit
-// as they are (323 us with 256, 410 with 128).
+// F = 16 (80 tiles 193, 185, 178, 300 tiles 235, 228, 254, 3225 tiles 387, 359,
+// 474, 25,800 tiles 2432, 2312, 3374).  At F = 32 64 or 128, within 8 % of each
+// other at every size: 128 is ahead up to 3225 tiles (300 tiles 329, 311, 490,
+// 2400 tiles 479, 470, 776, 3225 tiles 574, 552, 1069; not at 1200 tiles, 261,
+// 280, 418), 64 from 4800 on (760, 772, 1496; 8160 tiles 1052, 1078, 2139,
+// 25,800 tiles 3750, 3832, 7808; 16 mixed views of 2M Gaussians 5149, 5529,
+// 10939): the line lies between the two.  For the pose alone 128 at F = 16
+// (25,800 tiles 1449, 1386, 1515).  At tile 8 64 (1200x680, F = 16 578, 761,
+// 1522); at tile 32 the four times larger workgroups fit as they are (F = 16
+// 511, 490, 485).
 inline int bwd_batch(int tile, int n_feat, bool params, int total_tiles, int lds_batch, int lds_batch_bwd) {
+    constexpr int CUS = 256;
     if (lds_batch_bwd != 0) return lds_batch_bwd;
     int most = 256;
     if (tile == 8) most = 64;
-    else if (tile == 16 && n_feat == 16) most = 128;
+    else if (tile == 16 && n_feat == 16) most = params && total_tiles <= CUS ? 256 : 128;
     else if (tile == 16 && n_feat > 16 && params) most = total_tiles > 4096 ? 64 : 128;
     return lds_batch < most ? lds_batch : most;
 }

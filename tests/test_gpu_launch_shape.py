@@ -71,3 +71,15 @@ def test_tile_order_covers_every_tile(sizes):
 def test_chosen_lds_batches(F, tile, flags):
     r, g = _case([(130, 75)], F, tile, 10 + F + tile)
     _agree(r, g, flags)
+
+
+@pytest.mark.parametrize("size,tile", [
+    ((256, 256), 16), ((257, 256), 16),   # 256 tiles, a CU for each, and 272
+    ((512, 384), 16), ((513, 384), 16),   # 768 tiles, three for each, and 792
+    ((1040, 1024), 16),                   # 4160 tiles
+    ((128, 128), 8), ((129, 128), 8),
+], ids=str)
+@pytest.mark.parametrize("F", [16, 32])
+def test_lds_batches_chosen_by_tiles(F, size, tile):
+    r, g = _case([size], F, tile, 20 + F)
+    _agree(r, g, 3)
