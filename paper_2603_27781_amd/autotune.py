@@ -4,9 +4,11 @@ Tries tile side (8, 16, 32) x Gaussians staged per LDS batch (64, 128, 256)
 x launch mode (one workgroup per tile, or persistent workgroups pulling
 (view, tile) items from a queue), times a few eager steps of the real
 workload for each and keeps the fastest; then, for the winner, tries the
-other batch sizes for the render backward alone.  Results are cached in a JSON file
-keyed by device name and workload shape (Gaussian count, feature count,
-view sizes, gradient mode), so later runs skip the sweep.
+other batch sizes for the render backward alone.  Every configuration names its
+backward batch (0 would leave it to the library's rule), so that the sweep
+reaches each of them and a cached one stays the launch that was timed.  Results
+are cached in a JSON file keyed by device name and workload shape (Gaussian
+count, feature count, view sizes, gradient mode), so later runs skip the sweep.
 """
 from __future__ import annotations
 
@@ -29,7 +31,8 @@ CANDIDATES = [(t, b, p) for t in (8, 16, 32) for b in (64, 128, 256) for p in (0
 def _key(g, views, params, pose) -> str:
     dev = torch.cuda.get_device_name(0)
     sizes = ",".join(f"{v.width}x{v.height}" for v in views)
-    return f"{dev}|n={g.n}|F={g.n_feat}|{sizes}|params={int(params)}|pose={int(pose)}"
+    # "v2": entries without it may hold lds_batch_bwd = 0, which meant lds_batch
+    return f"v2|{dev}|n={g.n}|F={g.n_feat}|{sizes}|params={int(params)}|pose={int(pose)}"
 
 
 def tune(g, views: Sequence, rgb_t, dep_t, lab, W, weights, params=True, pose=False,
@@ -70,7 +73,7 @@ def tune(g, views: Sequence, rgb_t, dep_t, lab, W, weights, params=True, pose=Fa
         return ms
 
     for tile, batch, persistent in (candidates or CANDIDATES):
-        cfg = Config(tile=tile, lds_batch=batch, persistent=persistent)
+        cfg = Config(tile=tile, lds_batch=batch, persistent=persistent, lds_batch_bwd=batch)
         ms = trial(cfg)
         if ms < best_ms:
             best, best_ms = cfg, ms
