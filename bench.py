@@ -56,7 +56,10 @@ def byte_model(F, AS, V, N, n_vis, I, P, T, K, params=True):
     rec_floats = (n_red + 3) // 4 * 4
     m = {
         "project": V * N * (geo + 44) + N * (12 + 4 * F) + N * 4 * AS,
-        "bin_sort": n_vis * 4 * 8 * 3 + I * 8 * 3 * 2 + T * 8,
+        # tile counts twice, rectangle and first instance of the visible
+        # pairs; per instance 16 B written by the emission, 12 read, the
+        # table's entry and the 8-byte key by the placement, 16 by the sort
+        "bin_sort": V * N * 8 + n_vis * 20 + I * (16 + 24 + 16) + T * 8,
         "render_fwd": I * inst_gather + P * (4 * (5 + F) + 8) + T * 8,
         "loss_grad": P * (4 * (5 + F) * 2 + 16 + 4) + 4 * F * K,
         "render_bwd_records": I * (inst_gather + 4 + 4 * rec_floats) + P * (4 * (5 + F) + 8) + T * 8,

@@ -13,24 +13,25 @@
 //   2. k_emit: one workgroup per chunk of pairs of one view: instance offsets
 //      and emission; each instance counts itself into its tile in LDS, what
 //      the counter held is its place among the chunk's, and the chunk's
-//      counts become a row of a (chunk, tile) table;
-//   3. k_tile_scan: the table's columns to [start, end) of every tile and the
-//      first place of every (chunk, tile);
+//      counts become a row of a (chunk, tile) table (or, for a view of more
+//      tiles than fit, into one counter per tile in memory);
+//   3. k_tile_scan (k_tile_scan_one): the table's columns to [start, end) of
+//      every tile and the first place of every (chunk, tile);
 //   4. k_place: each instance's sort key to its place;
 //   5. k_tile_sort_short, 6. k_tile_sort_long: the lists in order.
 // (An LSD radix sort by tile id before them, with the visible pairs compacted
 // and their offsets scanned first, took 19 launches, most of them of a few
 // microseconds.  Alone: one 1200x680 view of 1M Gaussians 87 -> 45 us, eight
 // such views 232 -> 147, 640x480 / 200k 134 -> 80, 320x240 / 60k 62 -> 28,
-// 16 mixed views of 2M 740 -> 502.  The kernels move 60 bytes per instance and
-// 20 per pair, about 40 us of the eight views' 147 at the rate of a copy; the
-// rest is latency and, in the sort, vector work.)
+// 16 mixed views of 2M 740 -> 502.  The kernels move 56 bytes per instance, 20
+// per visible pair and 8 per pair, about 40 us of the eight views' 147 at the
+// rate of a copy; the rest is latency and, in the sort, vector work.)
 //
 // Every count that the host does not know (visible pairs, instances) stays on
 // the device; grids are sized for the capacity and blocks beyond the count
 // exit early, so the whole pipeline is graph-capturable.
 //
-// Blocks that wait (the look-back of k_emit and k_tile_scan, the merge of
+// Blocks that wait (the look-back of k_emit and the tile scans, the merges of
 // k_tile_sort_long) take a ticket first and wait only for blocks with earlier
 // tickets, which are already running and wait for none after them, so every
 // wait ends (the spin is bounded all the same).

@@ -116,19 +116,6 @@ __device__ __forceinline__ int wave_add_scan(int x) {
     return x;
 }
 
-// Lanes of the wavefront holding the same 8-bit digit as this lane, among
-// the valid lanes (8 ballots, one per digit bit).
-__device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid) {
-    uint64_t m = __ballot(valid);
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-        const bool bit = (d >> b) & 1u;
-        const uint64_t bb = __ballot(bit);
-        m &= bit ? bb : ~bb;
-    }
-    return m;
-}
-
 // Exclusive scan of the block's NT thread totals (wave scans, then the wave
 // totals in LDS); *total receives the block total.
 template <int NT>
