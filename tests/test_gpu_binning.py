@@ -232,3 +232,53 @@ def test_one_entry_per_tile(size):
     sc = _scene(200, 2, log_scale=-3.0)
     r, g, ref = _bin(sc, [wl.make_view(*size, 0.8 * max(size), np.eye(4))], 8)
     _check(r, ref, ref["dec"]["touched"])
+
+
+def _give_up_calls(r, monkeypatch):
+    """Five calls whose waits look once and give up; the ones that did."""
+    monkeypatch.setenv("SGS_LOOKBACK_SPIN", "0")
+    for _ in range(5):
+        r.clear_trouble()
+        r.bin_sort()
+        if r.instance_counts().lookback_gave_up:
+            assert r.trouble()
+            yield r.ranges.view(-1, 2).cpu().numpy().copy()
+    monkeypatch.delenv("SGS_LOOKBACK_SPIN")
+
+
+@pytest.mark.parametrize("size,tile", [((640, 480), 16), ((3840, 2160), 8)], ids=["table", "one entry per tile"])
+def test_give_up_of_the_tile_scan(monkeypatch, size, tile):
+    """More than 128 chunks, whose offsets need no wait: only the scan of the
+    tiles (19 and 16 workgroups) can give up, and every list is left empty."""
+    sc, views = _scene(140000, 12, log_scale=-5.0), _views([size])
+    r, g, ref = _bin(sc, views, tile)
+    gave_up = list(_give_up_calls(r, monkeypatch))
+    assert gave_up, "no wait gave up in five calls with a spin limit of 0"
+    assert not any(x.any() for x in gave_up)
+    r.clear_trouble()
+    r.bin_sort()
+    _check(r, ref, ref["dec"]["touched"])
+
+
+def test_give_up_of_a_merge(monkeypatch):
+    """More than 128 chunks and at most 64 tiles, one workgroup of the scan:
+    only the merges of lists of more than 4096 can give up, and they leave
+    the list they were for empty and the others as they are."""
+    sc, views = _scene(140000, 13, log_scale=-3.0, spread=0.6), [wl.make_view(90, 60, 72.0, np.eye(4))]
+    r, g, ref = _bin(sc, views)
+    want = ref["ranges"]
+    n = want[:, 1] - want[:, 0]
+    assert len(n) <= 64 and (n > 4096).any()
+    seen = False
+    for got in _give_up_calls(r, monkeypatch):
+        empty = (got == 0).all(1)
+        assert empty.any() and (empty <= (n > 4096)).all()
+        assert np.array_equal(got[~empty], want[~empty])
+        gids = r.sorted_gids(ref["count"]).cpu().numpy()
+        for a, b in got[~empty]:
+            assert np.array_equal(gids[a:b], ref["gids"][a:b])
+        seen = True
+    assert seen, "no wait gave up in five calls with a spin limit of 0"
+    r.clear_trouble()
+    r.bin_sort()
+    _check(r, ref, ref["dec"]["touched"])
