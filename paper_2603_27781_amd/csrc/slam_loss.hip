@@ -477,9 +477,10 @@ __global__ void __launch_bounds__(kSlamThreads) k_slam_loss(const float* __restr
 // that neither the lanes' accesses nor the operand loads share banks.  Each
 // 64 pixels are summed in binary32 by the MFMAs, and those sums in FP64.
 //
-// Bound by vector issue (4 F K flops per pixel, 2 F K more in the MFMAs, which
-// share the issue slots, and an exponential per class) and, at F = 16 and
-// K = 20, nearly as much by the 189 bytes per pixel.  With the logits in
+// Bound by issue (4 F K flops per pixel, 2 F K more in the MFMAs, which share
+// the issue slots, and an exponential per class: 1317 instructions per 64
+// pixels at F = 16 and K = 20, 32 of them MFMA of 33 cycles, about 260 of its
+// 400 us), then by latency.  With the logits in
 // registers, one pixel per thread and the workgroup's reduction after every
 // 256 pixels it was held by latency at three or four wavefronts per SIMD:
 // 549 us for eight 1200x680 views at F = 16, K = 20, 400 us now; a fifth
@@ -1162,8 +1163,10 @@ __device__ __forceinline__ void window_cols(const SsimConst& sc, const float (*s
 //      grad += B_mu + 2 x B_xx + y B_xy (the window is symmetric, so the
 //      adjoint is the same filter).
 // Step t's new rows complete windows 5 rows up and gradients 10 rows up.
-// Bound by instruction issue: 160 vector instructions and 12 MFMA a column and
-// row, of which the four vertical and three adjoint windows are 77; with the
+// Bound by instruction issue and, at three wavefronts a SIMD, the latency of a
+// step's two barriers: 164 vector instructions a row of 64 columns, 11 of them
+// MFMA and 77 the four vertical and three adjoint windows, which take 142 us to
+// issue, and MFMA busy 34 % of the time; with the
 // horizontal windows on the vector unit too it took 325 us for eight 1200x680
 // views (register and LDS use left two wavefronts a SIMD), now 245, and the
 // two tile kernels, which move 9 maps of every pixel through memory, 354.
