@@ -206,9 +206,9 @@ int gs_project(const gs_gaussians* g, const gs_view* views, const gs_view* views
  *                           predecessor never published within the spin
  *                           limit): the later binning kernels then stand
  *                           down, every tile list (or, where the wait was
- *                           the last kernel's, the list it was for) is left
- *                           empty and the call's results must be discarded
- *                           (call again),
+ *                           the last kernel's, the lists not yet merged by
+ *                           then) is left empty and the call's results must
+ *                           be discarded (call again),
  *                           [4] sticky: set whenever [2] or [3] is set, by
  *                           every call, and cleared only by the caller (write
  *                           0 to it), so that one check after many calls (a

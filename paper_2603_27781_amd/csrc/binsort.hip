@@ -1073,11 +1073,12 @@ WsLayout ws_layout(int n, int n_views, int64_t capacity) {
     const size_t wholes = cap / (kTsShort + 1) + 1, parts = cap / (kTsLong / 2) + 1;
     WsLayout L;
     // the (chunk, tile) table: the tiles are not known here, so four words per
-    // pair, at least 4 and at most 16 MB; a call whose tiles need more has it
-    // in the tile keys (written by the sort, long after), takes larger chunks
-    // or counts in memory
-    const int64_t want = 4 * vn;
-    L.table_words = want < (1 << 20) ? (1 << 20) : (want > (4 << 20) ? (4 << 20) : want);
+    // pair, at most 16 MB, or a byte per instance, at most 128 MB (few pairs
+    // with many instances reach many tiles), and 4 MB at least; a call whose
+    // tiles need more takes larger chunks or counts in memory
+    const int64_t by_pairs = 4 * vn < (4 << 20) ? 4 * vn : (4 << 20);
+    const int64_t want = by_pairs > (int64_t)cap / 4 ? by_pairs : (int64_t)cap / 4;
+    L.table_words = want < (1 << 20) ? (1 << 20) : (want > (32 << 20) ? (32 << 20) : want);
     size_t o = 0;
     L.slab = o; o += al(8 * cap);
     L.cell_e = o; o += al(4 * cap);  // these two, read for the last time by k_place, are slab2 of the merges
@@ -1113,8 +1114,7 @@ hipError_t launch_binsort(const uint32_t* rect, const int32_t* touched, int n,
                           int32_t* pair_first, int32_t* ranges, int64_t* counts, hipStream_t s) {
     if (n <= 0 || n_views <= 0 || total_tiles <= 0) return hipErrorInvalidValue;
     const WsLayout L = ws_layout(n, n_views, capacity);
-    const Chunks ck = chunks_of(n, n_views, total_tiles, max_tiles,
-                                capacity > L.table_words ? capacity : L.table_words);
+    const Chunks ck = chunks_of(n, n_views, total_tiles, max_tiles, L.table_words);
     char* w = static_cast<char*>(ws);
     auto words = [&](size_t off) { return reinterpret_cast<uint32_t*>(w + off); };
     BinState* st = reinterpret_cast<BinState*>(w + L.state);
@@ -1149,8 +1149,8 @@ hipError_t launch_binsort(const uint32_t* rect, const int32_t* touched, int n,
     // fit, the first words of the tile ranges
     const int rows = ck.lds ? ck.per_view : 1;
     const bool own = (int64_t)rows * total_tiles <= L.table_words;
-    A.table = own ? words(L.table) : (ck.lds ? tile_keys : reinterpret_cast<uint32_t*>(ranges));
-    A.stride = own || ck.lds ? 1 : 2;
+    A.table = own ? words(L.table) : reinterpret_cast<uint32_t*>(ranges);
+    A.stride = own ? 1 : 2;
     const int64_t clear = ck.lds ? 0 : (int64_t)total_tiles * A.stride;
     A.cell_e = words(L.cell_e);
     A.rank_e = words(L.rank_e);

@@ -191,9 +191,10 @@ def test_time_per_instance_holds_for_few_large_gaussians():
     ([(90, 60)], 256, None), ([(90, 60)], 257, None),    # one and two chunks of 256
     ([(90, 60)], 32768, None), ([(90, 60)], 32769, None),  # the last size of such chunks, chunks of 1024
     ([(90, 60), (31, 70)], 16385, None),
-    ([(1900, 1000)] * 2, 90000, 6_000_000),              # a table that fits only in the tile keys
+    ([(1900, 1000)] * 2, 90000, 24_000_000),             # a table of 5.2 M words, which the capacity makes room for
+    ([(1900, 1000)] * 2, 90000, 6_000_000),              # and too little of it: larger chunks
 ], ids=lambda x: "x".join(map(str, x[0])) + "*%d" % len(x) if isinstance(x, list) else str(x))
-def test_small_chunks_and_table_in_the_keys(sizes, n, cap):
+def test_small_chunks_and_table_sizes(sizes, n, cap):
     sc, views = _scene(n, 11, log_scale=-5.0 if n > 30000 else -3.5), _views(sizes)
     r, g, ref = _bin(sc, views, 16 if cap is None else 8, capacity=cap)
     _check(r, ref, ref["dec"]["touched"])

@@ -117,6 +117,39 @@ def test_strips_of_each_height_against_tiles(times, use_obs):
     test_strips_against_tiles(WIDE * times, use_obs)
 
 
+def test_wide_strips_against_oracle():
+    sizes, out, rgb, dep = _images(WIDE * 3)
+    o = _opts(False)
+    g, terms = _loss(sizes, out, rgb, dep, o)
+    oo = oracle.SlamLossOpts(w_color=o.w_color, w_depth=o.w_depth, w_sem=0.0, ssim_lambda=o.ssim_lambda,
+                             tau_obs=o.tau_obs, tau_unobs=o.tau_unobs, obs_factor=o.obs_factor,
+                             unobs_factor=o.unobs_factor, use_obs=False)
+    gref, tref = oracle.slam_loss(out, sizes, rgb, dep, None, None, oo)[:2]
+    assert np.linalg.norm(g[:3] - gref[:3]) <= TOL * np.linalg.norm(gref[:3])
+    assert terms[1] == pytest.approx(tref[1], rel=1e-4)
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+@pytest.mark.parametrize("times", [1, 3, 6, 4])
+def test_not_finite_in_wide_strips(value, times):
+    sizes, out, rgb, dep = _images(WIDE * times)
+    o = _opts(False)
+    off = sum(W * H for W, H in sizes[:2])  # the 1180x145 view
+    W, H = sizes[2]
+    out[1, off + 71 * W + 500] = value
+    rgb[2, off + 2 * W + 237] = value
+    out[0, off + 140 * W + 705] = -value
+    g, _ = _loss(sizes, out, rgb, dep, o)
+    sl = slice(off, off + W * H)
+    ga, _ = _loss([(W, H)], out[:, sl], rgb[:, sl], dep[sl], o)
+    fin = np.isfinite(ga[:3])
+    assert not fin.all()
+    assert np.array_equal(np.isfinite(g[:3, sl]), fin)
+    assert np.isfinite(g[:3, :off]).all() and np.isfinite(g[:3, off + W * H:]).all()
+    d = np.where(fin, g[:3, sl].astype(np.float64) - np.where(fin, ga[:3], 0.0), 0.0)
+    assert np.linalg.norm(d) <= 2 * TOL * np.linalg.norm(ga[:3][fin].astype(np.float64))
+
+
 def test_narrow_views_are_not_filtered_in_strips():
     """Eight 30x3000 views have the pixels of eight 3000x30 ones and take no
     more than twice as long (in strips, 236 columns wide, 2.4 times; in tiles
