@@ -337,7 +337,7 @@ hipError_t launch_fwd_b(int B, const float* rec, const float* app, int n, const 
             return launch_fwd_t<TS, F, 256, LK>(rec, app, n, inst, inst_gid, ranges, views, n_views, total_tiles, P, c,
                                                 persistent, out, T_final, last, queue, L, s);
     }
-    if constexpr (TS != 8) {
+    if constexpr (TS != 8 || F > 16) {
         if (B == 128)
             return launch_fwd_t<TS, F, 128, LK>(rec, app, n, inst, inst_gid, ranges, views, n_views, total_tiles, P, c,
                                                 persistent, out, T_final, last, queue, L, s);

@@ -83,3 +83,12 @@ def test_chosen_lds_batches(F, tile, flags):
 def test_lds_batches_chosen_by_tiles(F, size, tile):
     r, g = _case([size], F, tile, 20 + F)
     _agree(r, g, 3)
+
+
+@pytest.mark.parametrize("batch,batch_bwd", [(64, 0), (128, 0), (256, 0), (64, 256), (128, 64), (256, 128)])
+@pytest.mark.parametrize("persistent", [0, 1])
+@pytest.mark.parametrize("tile,size", [(8, (40, 30)), (8, (140, 130)), (16, (40, 30)), (16, (520, 400)), (32, (40, 30))])
+@pytest.mark.parametrize("F", [0, 16, 32])
+def test_every_batch_a_caller_may_pass(F, tile, size, persistent, batch, batch_bwd):
+    r, g = _case([size], F, tile, 30 + F + tile, lds_batch=batch, lds_batch_bwd=batch_bwd, persistent=persistent)
+    _agree(r, g, 3)
