@@ -603,7 +603,9 @@ __global__ void __launch_bounds__(kSlamThreads)
                         const bool y = k == lab;
                         const float zk = z[k], e = __expf(zk), pk = e * inv;
                         const float lp = zk - lse, lq = __logf(se - e) - lse;
-                        term -= y ? fmaxf(lp, -100.0f) : fmaxf(lq, -100.0f);
+                        // (of a pixel that is not finite, a row past K would
+                        // give the clamped -100, not 0)
+                        term -= k < K ? (y ? fmaxf(lp, -100.0f) : fmaxf(lq, -100.0f)) : 0.0f;
                         const bool w = y ? lp > -100.0f : lq > -100.0f;
                         const float dp =
                             w ? (y ? -__builtin_amdgcn_rcpf(pk) : __builtin_amdgcn_rcpf(1.0f - pk)) : 0.0f;

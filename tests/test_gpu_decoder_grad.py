@@ -117,3 +117,32 @@ def test_labels_outside_the_classes_are_no_class(K, bce):
         assert terms[0] == pytest.approx(terms[1], rel=1e-5)
     gW = w * r.out[5:].cpu().double() @ dz
     assert float((r.grad_decoder_w.cpu().double() - gW).abs().max()) <= tol * float(gW.abs().max())
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("K", [5, 6, 7, 8])
+def test_features_that_are_not_finite(K, value):
+    """The BCE term of a pixel with such a feature counts its K classes only,
+    as without decoder gradients (1e-5 relative: the same binary32 formulas
+    per pixel, summed in FP64)."""
+    from paper_2603_27781_amd import _lib, raster
+    F, P = 8, 300
+    g = torch.Generator().manual_seed(K)
+    r = raster.Rasterizer(1, F, raster.Views([wl.make_view(P, 1, 50.0, np.eye(4))], 16), raster.Config(), capacity=64)
+    r.out.copy_(torch.randn(5 + F, P, generator=g))
+    r.out[6, 100] = value
+    rgb, dep = torch.rand(3, P, generator=g).cuda(), torch.rand(P, generator=g).cuda()
+    labels = torch.randint(0, K, (P,), generator=g, dtype=torch.int32).cuda()
+    W = (torch.randn(F, K, generator=g) / 4).cuda()
+    o = _lib.GsSlamLossOpts()
+    _lib.check(_lib.load().gs_default_slam_loss_opts(ctypes.byref(o)), "opts")
+    o.ssim_lambda, o.flags = 0.0, _lib.GS_LOSS_BCE
+    terms, grads = [], []
+    for dec in (False, True):
+        r.slam_loss(rgb, dep, labels, W, o, decoder_grads=dec)
+        torch.cuda.synchronize()
+        terms.append(r.slam_terms.cpu().clone())
+        grads.append(r.grad_out.cpu().clone())
+    assert torch.isfinite(terms[0]).all()
+    assert float((terms[0] - terms[1]).abs().max()) <= 1e-5 * float(terms[0].abs().max())
+    assert torch.equal(torch.isfinite(grads[0]), torch.isfinite(grads[1]))
