@@ -603,9 +603,7 @@ __global__ void __launch_bounds__(kSlamThreads)
                         const bool y = k == lab;
                         const float zk = z[k], e = __expf(zk), pk = e * inv;
                         const float lp = zk - lse, lq = __logf(se - e) - lse;
-                        // (of a pixel that is not finite, a row past K would
-                        // give the clamped -100, not 0)
-                        term -= k < K ? (y ? fmaxf(lp, -100.0f) : fmaxf(lq, -100.0f)) : 0.0f;
+                        term -= y ? fmaxf(lp, -100.0f) : fmaxf(lq, -100.0f);
                         const bool w = y ? lp > -100.0f : lq > -100.0f;
                         const float dp =
                             w ? (y ? -__builtin_amdgcn_rcpf(pk) : __builtin_amdgcn_rcpf(1.0f - pk)) : 0.0f;
@@ -613,6 +611,9 @@ __global__ void __launch_bounds__(kSlamThreads)
                         z[k] = pk;
                         live |= (uint64_t)w << k;
                     }
+                    // the rows past K gave 0, but of a pixel that is not
+                    // finite (every logarithm NaN) the clamp's 100 each
+                    if (se != se) term -= 100.0f * (float)(K4 - K);
                 }
                 // dz and dL/df = W dz; the row ends as the scaled dz
                 for (int k0 = 0; k0 < K4; k0 += U2) {
